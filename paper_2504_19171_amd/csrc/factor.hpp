@@ -1,0 +1,886 @@
+// The factor of the band and arrow as one persistent launch over 64 x 64
+// blocks.
+//
+// The matrix is cut into chunks of 64 columns, whatever the tile size (tiles
+// are multiples of 64).  Block (i, c) is rows 64 i.., columns 64 c.. of the
+// band (i - c <= Wc = ceil(w / 64): the blocks below that hold only entries
+// outside the element band, which stay zero), or rows 64 r.. of the arrow.
+//
+// What bounds the factor is the chain of diagonal blocks, one after the
+// other, so one workgroup per matrix (the chain) does nothing else: per chunk
+// it factors the 64 x 64 diagonal block, solves the block row below it and
+// applies that row to the next diagonal block, all in registers and LDS, with
+// no hand-off through memory on the way (fac_chain).  Every other block is
+// left-looking: a task reads the block once, subtracts the products of the
+// finished blocks to its left, solves against the chunk's diagonal block and
+// writes it once (fac_task).  The two meet two block rows below the diagonal:
+//   G(i, c), i >= c + 3, and every arrow block: the whole sum over k < c, then
+//     the solve with chunk c;
+//   P(i, j), j in {i - 2, i - 1, i}: the early part of the sum of the blocks
+//     that are due soonest, written back in place;
+//   H1(i): the rest of block (i, i - 2) and its solve (not stored), then its
+//     product into the diagonal block (i, i), which the chain takes over;
+//   H0(i): the same solve again, stored once H1(i) has read what it replaces,
+//     and its product into block (i, i - 1), which the chain takes over too.
+//     The two run side by side, because either alone would be late for the
+//     chain;
+//   C(r, s; q): chunks 4q .. 4q + 3 into corner block (r, s).
+// Tasks are dealt by tickets in the order of fac_group; a task waits only for
+// tasks of smaller tickets and for the chain, the chain only for tasks.  The
+// chain takes the launch's first ticket, so it runs whenever any workgroup of
+// the launch does, and launches have at least two workgroups when they have
+// tasks: as long as some other launch's workgroups leave room in the end, no
+// wait can last.
+//
+// Every block is written once in its final form (P and H parts before that
+// are read only by the task or chain that goes on with them) with
+// device-coherent stores, and read by others only after its flag is up, with
+// device-coherent loads (see persist.hpp).
+#pragma once
+#include "common.hpp"
+#include "persist.hpp"
+#include "factor16.hpp"
+
+#define FC 64          // chunk width
+#define FAC_NT 256     // threads per workgroup (4 wavefronts)
+#define FAC_STAGES 4   // 16-column operand stages in LDS
+
+struct FacCtx {
+    double* Lm;
+    Lay L;
+    int c64;    // chunks per tile
+    int nc;     // chunks that hold real columns
+    int wc;     // block half-bandwidth
+    int w1;     // max(wc, 1): row length of fl
+    int na;     // arrow row blocks
+    double* Yd; // Y_p of every chunk, 4 x 256 doubles in operand order
+    int* po;    // [nc * 4]   panel p of chunk c is in memory
+    int* fl;    // [nc * w1]  block (i, k) final at fl[i * w1 + i - k - 1]: 4
+    int* fa;    // [na * nc]  arrow block (r, k) final: 4
+    int* hx;    // [nc * 2]   H0(i), H1(i) done
+    int* pp;    // [nc * 4]   P(i, i), P(i, i - 1), P(i, i - 2) done; H1(i) has read block (i, i - 2)
+    int* cc;    // [na (na + 1) / 2]  groups of four chunks in a corner block
+};
+__host__ __device__ inline int fac_chunks(const Lay& L) { return (int)((L.nb + FC - 1) / FC); }
+__host__ __device__ inline int fac_wc(const Lay& L) {
+    const int64_t wc = (L.w + FC - 1) / FC, m = fac_chunks(L) - 1;
+    return (int)(wc < m ? wc : m);
+}
+// Flag ints of one factorization (from po on, contiguous).
+__host__ __device__ inline int64_t fac_ints(const Lay& L) {
+    const int64_t nc = fac_chunks(L), wc = fac_wc(L), na = arrow_blocks(L.ap);
+    return nc * 4 + nc * (wc > 1 ? wc : 1) + na * nc + nc * 2 + nc * 4 + na * (na + 1) / 2;
+}
+__host__ __device__ inline FacCtx fac_ctx(const Lay& L, double* Lm, double* Yd, int* flags) {
+    FacCtx x;
+    x.Lm = Lm;
+    x.L = L;
+    x.c64 = L.b / FC;
+    x.nc = fac_chunks(L);
+    x.wc = fac_wc(L);
+    x.w1 = x.wc > 1 ? x.wc : 1;
+    x.na = arrow_blocks(L.ap);
+    x.Yd = Yd;
+    x.po = flags;
+    x.fl = x.po + x.nc * (int64_t)4;
+    x.fa = x.fl + x.nc * (int64_t)x.w1;
+    x.hx = x.fa + x.na * (int64_t)x.nc;
+    x.pp = x.hx + x.nc * (int64_t)2;
+    x.cc = x.pp + x.nc * (int64_t)4;
+    return x;
+}
+
+// Tasks of group c (see fac_pick for their order): the tasks that end with
+// the solve of chunk c, and the early sums that end with its blocks.
+__host__ __device__ inline int fac_group(const FacCtx& x, int c) {
+    const int left = imin_(x.wc, x.nc - 1 - c);   // block rows below the diagonal
+    int n = x.na;
+    if (left >= 2) n += 2;                        // H0, H1 (c + 2)
+    if (left >= 3) n += left - 2 + 2;             // G(c + 3 ..), P(c + 3, c + 2), P(c + 3, c + 3)
+    if (left >= 4) n += 1;                        // P(c + 4, c + 2)
+    if ((c & 3) == 3 || c == x.nc - 1) n += x.na * (x.na + 1) / 2;
+    return n;
+}
+// Leading chunks whose groups are all alike (but for the corner tasks of
+// every fourth), rounded down to a multiple of four.
+__host__ __device__ inline int fac_full4(const FacCtx& x) { return imax_(0, x.nc - 1 - imax_(x.wc, 4)) & ~3; }
+__host__ __device__ inline int64_t fac_tasks(const FacCtx& x) {
+    const int f4 = fac_full4(x);
+    int64_t t = 0;
+    if (f4 > 0)
+        for (int c = 0; c < 4; ++c) t += fac_group(x, c);
+    t *= f4 / 4;
+    for (int c = f4; c < x.nc; ++c) t += fac_group(x, c);
+    return t;
+}
+
+// ---------------------------------------------------------------------------
+// LDS
+// ---------------------------------------------------------------------------
+struct ChainSmem {
+    double Y[2][4][16 * 17];   // Y_p of the chunk (by its parity), element (i, j) at j * 17 + i
+    double Lt[2][6][256];      // tile (t, p), t > p, of the diagonal block in operand order (r * 64 + lane)
+    double R[4][4][256];       // strip s, panel p of the block row below, in operand order
+    int yd[4];                 // chunks whose Y_p is there
+    int ld[4];                 // 4 c + panels of row t there
+    int rd[4];                 // 4 c + panels of strip s there
+    int di[4];                 // chunks whose diagonal row t was taken from R
+    int fin[4];                // chunks wavefront t is done with
+};
+struct TaskSmem {
+    double st[FAC_STAGES][2][16 * 64];   // per stage: 16 columns of the column-side rows, then of the row-side rows
+};
+struct FacSmem {
+    union {
+        ChainSmem ch;
+        TaskSmem tk;
+    };
+    int sh;     // scheduler broadcast
+    int n;      // blocks ready (fac_acc)
+    int dead;   // a wait of this workgroup failed
+};
+
+// ---------------------------------------------------------------------------
+// Addresses
+// ---------------------------------------------------------------------------
+// Block (i, c) of the band, leading dimension b.
+__device__ inline double* fac_band(const FacCtx& x, int i, int c) {
+    const int I = i / x.c64, J = c / x.c64;
+    return x.Lm + x.L.band(J, I - J) + (i - I * x.c64) * FC + (int64_t)(c - J * x.c64) * FC * x.L.b;
+}
+// Arrow block (r, c), leading dimension a_p.
+__device__ inline double* fac_arrow(const FacCtx& x, int r, int c) {
+    const int J = c / x.c64;
+    return x.Lm + x.L.arrow(J) + r * FC + (int64_t)(c - J * x.c64) * FC * x.L.ap;
+}
+// A block row: band row i, or arrow row block r.
+struct FacRow {
+    int i;   // band row, or -1 - r
+};
+__device__ inline const double* fac_ptr(const FacCtx& x, FacRow w, int k) {
+    return w.i >= 0 ? fac_band(x, w.i, k) : fac_arrow(x, -1 - w.i, k);
+}
+__device__ inline int fac_ld(const FacCtx& x, FacRow w) { return w.i >= 0 ? x.L.b : x.L.ap; }
+__device__ inline int fac_valid(const FacCtx& x, FacRow w) {
+    return w.i >= 0 ? FC : imin_(FC, x.L.ap - FC * (-1 - w.i));
+}
+__device__ inline int* fac_flag(const FacCtx& x, FacRow w, int k) {
+    return w.i >= 0 ? x.fl + (int64_t)w.i * x.w1 + (w.i - k - 1) : x.fa + (int64_t)(-1 - w.i) * x.nc + k;
+}
+
+__device__ inline void fac_bar() { asm volatile("s_barrier" ::: "memory"); }
+__device__ inline void fac_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ inline void fac_up(int* f, int v) {
+    __hip_atomic_store((GLOBAL_AS int*)f, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One wavefront waits until *f >= target; false when the kernel must stop.
+__device__ inline bool fac_wait1(const Sched& sc, const int* f, int target) {
+    int v = __builtin_amdgcn_readfirstlane(ld_coh_i(f));
+    if (v >= target) return true;
+    const int64_t t0 = wall_clock64();
+    for (unsigned n = 0;; ++n) {
+        v = __builtin_amdgcn_readfirstlane(ld_coh_i(f));
+        if (v >= target) return true;
+        if ((n & 15) == 15) {
+            if (__builtin_amdgcn_readfirstlane(ld_coh_i(sc.err)) != 0) return false;
+            if (wall_clock64() - t0 > sc.spin_limit) {
+                set_error_once(sc.err, STILES_ETIMEOUT);
+                return false;
+            }
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+// Panels of chunk c in memory (the leading ones), at least `need`; 0: stop.
+__device__ inline int fac_panels(const Sched& sc, const int* po, int need) {
+    const int lane = threadIdx.x & 63;
+    int64_t t0 = -1;
+    for (unsigned n = 0;; ++n) {
+        const uint64_t m = __ballot(ld_coh_i(po + (lane & 3)) != 0) & 15;
+        const int have = __builtin_ctz(~(unsigned)m);
+        if (have >= need) return have;
+        if (t0 < 0) t0 = wall_clock64();
+        if ((n & 15) == 15) {
+            if (__builtin_amdgcn_readfirstlane(ld_coh_i(sc.err)) != 0) return 0;
+            if (wall_clock64() - t0 > sc.spin_limit) {
+                set_error_once(sc.err, STILES_ETIMEOUT);
+                return 0;
+            }
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+// Every wavefront says whether its waits succeeded; false for all when one failed.
+__device__ inline bool fac_agree(FacSmem& sm, bool ok) {
+    if (!ok) sm.dead = 1;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    fac_bar();
+    return __builtin_amdgcn_readfirstlane(*(volatile int*)&sm.dead) == 0;
+}
+
+// ---------------------------------------------------------------------------
+// The sum of products of a task
+// ---------------------------------------------------------------------------
+// Wavefront v owns rows 16 v .. 16 v + 15 of a 64 x 64 block (its strip), as
+// four 16 x 16 tiles: element r of z[t] is (row 16 v + li, column
+// 16 t + 4 r + lk), the transposed product on the matrix cores, so that every
+// access to memory runs down a column, and so that a solved strip is already
+// the operand of the next product.
+
+// The same value, but opaque: offsets formed from it are formed where they are
+// used, not hoisted out of the kernel's task loop (where they would only
+// occupy registers).
+__device__ inline int fac_opaque(int v) {
+    v = __builtin_amdgcn_readfirstlane(v);
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
+// This lane, opaque for the same reason.
+__device__ inline int fac_lane() {
+    int l = threadIdx.x & 63;
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
+// Issue the loads of stage `q` (16 columns) of block column k: columns 4 v ..
+// 4 v + 3 of the column-side rows and of the row-side rows, straight into LDS
+// (element (row x, column k) at k * 64 + (x ^ 16 (k & 3)): the four columns
+// that one matrix-core operand takes fall in different banks).
+__device__ inline void fac_issue(const double* A, int lda, int va, const double* B, int ldb, int vb, int q,
+                                 double (*st)[16 * 64]) {
+    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = fac_lane();
+    const int half = l >> 5, s = 2 * (l & 31);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int col = 4 * v + 2 * u + half;
+        const int row = s ^ (16 * ((2 * u + half) & 3));
+        const double* ga = A + imin_(row, va - 2) + (int64_t)(16 * q + col) * lda;
+        const double* gb = B + imin_(row, vb - 2) + (int64_t)(16 * q + col) * ldb;
+        __builtin_amdgcn_global_load_lds((const void*)ga, (lds_void_t*)(st[0] + (4 * v + 2 * u) * 64), 16, 0, 16);
+        __builtin_amdgcn_global_load_lds((const void*)gb, (lds_void_t*)(st[1] + (4 * v + 2 * u) * 64), 16, 0, 16);
+    }
+}
+__device__ inline void fac_issue_a(const double* A, int lda, int q, double* st) {
+    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = fac_lane();
+    const int half = l >> 5, s = 2 * (l & 31);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int col = 4 * v + 2 * u + half;
+        const int row = s ^ (16 * ((2 * u + half) & 3));
+        __builtin_amdgcn_global_load_lds((const void*)(A + row + (int64_t)(16 * q + col) * lda),
+                                         (lds_void_t*)(st + (4 * v + 2 * u) * 64), 16, 0, 16);
+    }
+}
+
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+// Operands of eight columns (two matrix-core steps): .x of the first four
+// columns, .y of the next four.  Reads and their wait in one block, as the
+// compiler would also wait for every load into LDS still in flight.
+__device__ inline void fac_read(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t b, dbl2 (&a)[4], dbl2& bv) {
+    asm volatile(
+        "ds_read2st64_b64 %4, %9 offset1:4\n\t"
+        "ds_read2st64_b64 %0, %5 offset1:4\n\t"
+        "ds_read2st64_b64 %1, %6 offset1:4\n\t"
+        "ds_read2st64_b64 %2, %7 offset1:4\n\t"
+        "ds_read2st64_b64 %3, %8 offset1:4\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(bv)
+        : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(b)
+        : "memory");
+}
+__device__ inline void fac_read_a(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, dbl2 (&a)[4]) {
+    asm volatile(
+        "ds_read2st64_b64 %0, %4 offset1:4\n\t"
+        "ds_read2st64_b64 %1, %5 offset1:4\n\t"
+        "ds_read2st64_b64 %2, %6 offset1:4\n\t"
+        "ds_read2st64_b64 %3, %7 offset1:4\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
+        : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
+        : "memory");
+}
+
+// Wait until the oldest of this wavefront's load stages has landed, `later`
+// stages (4 loads each, 2 for the one-operand form) issued after it.
+template <int PER>
+__device__ inline void fac_landed(int later) {
+    if (PER == 4) {
+        if (later >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if (later == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
+        if (later >= 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else if (later == 1) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+}
+
+// acc[t] += (row w, k) (col-side row u, k)^T over k0 <= k < k1, tiles t < nt,
+// as the blocks' flags come up.  act: this wavefront's strip has rows.
+__device__ inline bool fac_acc(const FacCtx& x, const Sched& sc, FacSmem& sm, dbl4 (&acc)[4], FacRow w, FacRow u,
+                               int k0, int k1, int nt, bool act) {
+    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
+    const int ldw = fac_ld(x, w), ldu = fac_ld(x, u), vw = fac_valid(x, w), vu = fac_valid(x, u);
+    uint32_t oa[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) oa[t] = lds_addr(sm.tk.st[0][0]) + 8u * (uint32_t)(lk * 64 + 16 * (t ^ lk) + li);
+    const uint32_t ob = lds_addr(sm.tk.st[0][1]) + 8u * (uint32_t)(lk * 64 + 16 * (v ^ lk) + li);
+    for (int k = k0; k < k1;) {
+        // leading blocks that are ready, up to 32: lanes 0..31 read the row
+        // side's flags, lanes 32..63 the column side's
+        if (v == 0) {
+            const int m = imin_(k1 - k, 32), e = imin_(lane & 31, m - 1);
+            const int* f = lane < 32 ? fac_flag(x, w, k + e) : fac_flag(x, u, k + e);
+            int n = 0;
+            int64_t t0 = -1;
+            for (unsigned polls = 0;; ++polls) {
+                const uint64_t b = __ballot(ld_coh_i(f) >= 4);
+                const uint32_t both = (uint32_t)b & (uint32_t)(b >> 32);
+                n = both == 0xffffffffu ? 32 : __builtin_ctz(~both);
+                n = imin_(n, m);
+                if (n > 0) break;
+                if (t0 < 0) t0 = wall_clock64();
+                if ((polls & 15) == 15) {
+                    if (__builtin_amdgcn_readfirstlane(ld_coh_i(sc.err)) != 0) break;
+                    if (wall_clock64() - t0 > sc.spin_limit) {
+                        set_error_once(sc.err, STILES_ETIMEOUT);
+                        break;
+                    }
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (lane == 0) sm.n = n;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        fac_bar();
+        const int n = __builtin_amdgcn_readfirstlane(*(volatile int*)&sm.n);
+        if (n == 0) return false;
+        const int total = 4 * n;
+        auto issue = [&](int it) {
+            const int kk = k + (it >> 2);
+            fac_issue(uniform_ptr(fac_ptr(x, u, kk)), ldu, vu, uniform_ptr(fac_ptr(x, w, kk)), ldw, vw, it & 3,
+                      sm.tk.st[it & 3]);
+        };
+#pragma unroll
+        for (int it = 0; it < FAC_STAGES - 1; ++it) issue(it);   // a block has four stages
+        for (int it = 0; it < total; ++it) {
+            fac_landed<4>(total - 1 - it);
+            fac_bar();   // ... for every wavefront, and stage it - 1 has been read
+            if (it + FAC_STAGES - 1 < total) issue(it + FAC_STAGES - 1);
+            if (act) {
+                const uint32_t so = (uint32_t)(it & 3) * (uint32_t)(2 * 16 * 64 * 8);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    dbl2 a[4], b;
+                    const uint32_t o = so + (uint32_t)h * (8 * 64 * 8);
+                    fac_read(oa[0] + o, oa[1] + o, oa[2] + o, oa[3] + o, ob + o, a, b);
+                    if (nt == 4) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b.x, acc[t], 0, 0, 0);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b.y, acc[t], 0, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < 3; ++t)
+                            if (t < nt) {
+                                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b.x, acc[t], 0, 0, 0);
+                                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b.y, acc[t], 0, 0, 0);
+                            }
+                    }
+                }
+            }
+        }
+        k += n;
+    }
+    fac_bar();   // every wavefront has read the last stage: the LDS may be reused
+    return true;
+}
+
+// Strip rows of a block at `base` (leading dimension ld), tiles t < nt.
+__device__ inline void fac_load(const double* base, int ld, int v, dbl4 (&z)[4], int nt) {
+    ld = fac_opaque(ld);
+    const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
+    const double* b = uniform_ptr(base);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t < nt) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[t][r] = ld_coh_s(b, (uint32_t)((16 * v + li) + (16 * t + 4 * r + lk) * ld));
+        }
+}
+__device__ inline void fac_store(double* base, int ld, int v, const dbl4 (&z)[4], int nt) {
+    ld = fac_opaque(ld);
+    const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
+    double* b = (double*)uniform_ptr(base);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t < nt) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st_coh_s(b, (uint32_t)((16 * v + li) + (16 * t + 4 * r + lk) * ld), z[t][r]);
+        }
+}
+
+// Solve of a strip with the diagonal block of chunk c, o[p] = R_p^T =
+// Y_p Z_p^T, Z_t^T -= L_tp R_p^T, panel by panel as the chain announces them.
+// The strip never leaves the wavefront's registers.  R (may be nullptr): the
+// strip's block in memory.
+__device__ inline bool fac_solve(const FacCtx& x, const Sched& sc, int c, dbl4 (&z)[4], dbl4 (&o)[4], double* R, int ldr,
+                                 int v) {
+    const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
+    const double* D = uniform_ptr(fac_band(x, c, c));
+    const double* Y = uniform_ptr(x.Yd + (int64_t)c * 1024);
+    const int b = fac_opaque(x.L.b);
+    double yv[4][4], lv[4][4][4];
+    auto fetch = [&](int p) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) yv[p][r] = ld_coh_s(Y, (uint32_t)(p * 256 + r * 64 + lane));
+#pragma unroll
+        for (int t = p + 1; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                lv[p][t][r] = ld_coh_s(D, (uint32_t)((16 * t + li) + (16 * p + 4 * r + lk) * b));
+    };
+    auto step = [&](int p) {
+        o[p] = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(yv[p][r], z[p][r], o[p], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int t = p + 1; t < 4; ++t)
+                z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-lv[p][t][r], o[p][r], z[t], 0, 0, 0);
+    };
+    const int* po = x.po + (int64_t)c * 4;
+    int have = fac_panels(sc, po, 1);
+    if (have == 0) return false;
+    if (have == 4) {   // late: everything at once
+#pragma unroll
+        for (int p = 0; p < 4; ++p) fetch(p);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) step(p);
+    } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if (have <= p) {
+                have = fac_panels(sc, po, p + 1);
+                if (have == 0) return false;
+            }
+            fetch(p);
+            step(p);
+        }
+    }
+    if (R) fac_store(R, ldr, v, o, 4);
+    return true;
+}
+
+// Which task is index u of group c.
+enum { FT_G = 0, FT_H0, FT_H1, FT_P, FT_ARROW, FT_CORNER };
+struct FacTask {
+    int kind, i, j;   // G: block (i, c); P: block (i, j); ARROW: row block i; CORNER: block (i, j)
+};
+__device__ inline FacTask fac_pick(const FacCtx& x, int c, int u) {
+    const int left = imin_(x.wc, x.nc - 1 - c);
+    FacTask k;
+    k.i = c + 2;
+    k.j = c;
+    if (left >= 2) {
+        if (u < 2) { k.kind = u == 0 ? FT_H1 : FT_H0; return k; }
+        u -= 2;
+    }
+    if (left >= 3) {
+        k.i = c + 3;
+        if (u == 0) { k.kind = FT_G; return k; }
+        k.kind = FT_P;
+        if (u < 3) { k.j = c + 1 + u; return k; }
+        u -= 3;
+    }
+    if (left >= 4) {
+        k.i = c + 4;
+        if (u == 0) { k.kind = FT_G; return k; }
+        k.kind = FT_P;
+        if (u == 1) { k.j = c + 2; return k; }
+        u -= 2;
+        if (u < left - 4) { k.kind = FT_G; k.i = c + 5 + u; return k; }
+        u -= left - 4;
+    }
+    if (u < x.na) { k.kind = FT_ARROW; k.i = u; return k; }
+    k.kind = FT_CORNER;
+    tri_decode(u - x.na, k.i, k.j);
+    return k;
+}
+
+// Task u of group c; false when the kernel must stop.  ticket: the launch's
+// ticket (the test hook Sched::withhold names one whose signal is not sent).
+__device__ inline bool fac_task(const FacCtx& x, const Sched& sc, FacSmem& sm, int c, int u, int ticket) {
+    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = fac_lane();
+    const FacTask k = fac_pick(x, c, u);
+    const int b = x.L.b, ap = x.L.ap;
+    const bool quiet = ticket == sc.withhold;
+    dbl4 acc[4], z[4], o[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = z[t] = o[t] = dbl4{0.0, 0.0, 0.0, 0.0};
+    if (k.kind == FT_G || k.kind == FT_ARROW) {
+        const bool band = k.kind == FT_G;
+        const FacRow w{band ? k.i : -1 - k.i};
+        const bool act = 16 * v < fac_valid(x, w);
+        double* R = band ? fac_band(x, k.i, c) : fac_arrow(x, k.i, c);
+        const int ld = band ? b : ap;
+        if (act) fac_load(R, ld, v, z, 4);
+        if (!fac_acc(x, sc, sm, acc, w, FacRow{c}, imax_(0, (band ? k.i : c) - x.wc), c, 4, act)) return false;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) z[t] -= acc[t];
+        bool ok = true;
+        if (act) ok = fac_solve(x, sc, c, z, o, R, ld, v);
+        fac_vm0();
+        if (!fac_agree(sm, ok)) return false;
+        if (threadIdx.x == 0 && !quiet) fac_up(fac_flag(x, w, c), 4);
+        return true;
+    }
+    if (k.kind == FT_P) {
+        const int nt = k.i == k.j ? v + 1 : 4;
+        double* O = fac_band(x, k.i, k.j);
+        fac_load(O, b, v, z, nt);
+        if (!fac_acc(x, sc, sm, acc, FacRow{k.i}, FacRow{k.j}, imax_(0, k.i - x.wc), c + 1, nt, true)) return false;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) z[t] -= acc[t];
+        fac_store(O, b, v, z, nt);
+        fac_vm0();
+        fac_bar();
+        if (threadIdx.x == 0 && !quiet) fac_up(x.pp + k.i * (int64_t)4 + (k.i - k.j), 1);
+        return true;
+    }
+    if (k.kind == FT_CORNER) {
+        const FacRow w{-1 - k.i}, s{-1 - k.j};
+        const int vs = fac_valid(x, s);
+        const bool act = 16 * v < fac_valid(x, w);
+        const int nt = k.i == k.j ? imin_(v + 1, vs / 16) : vs / 16;
+        if (!fac_acc(x, sc, sm, acc, w, s, c & ~3, c + 1, nt, act)) return false;
+        int* cnt = x.cc + (k.i * (k.i + 1) / 2 + k.j);
+        if (!sched_wait(sc, cnt, c >> 2, &sm.sh)) return false;
+        double* O = x.Lm + x.L.corner() + FC * k.i + (int64_t)FC * k.j * ap;
+        if (act) {
+            fac_load(O, ap, v, z, nt);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) z[t] -= acc[t];
+            fac_store(O, ap, v, z, nt);
+        }
+        fac_vm0();
+        fac_bar();
+        if (threadIdx.x == 0 && !quiet) add_coh_i(cnt, 1);
+        return true;
+    }
+    // H0, H1: block (i, i - 2) and its solve, i = c + 2
+    const int i = k.i;
+    double* R = fac_band(x, i, c);
+    if (x.wc >= 4 && i >= 4 && !sched_wait(sc, x.pp + i * (int64_t)4 + 2, 1, &sm.sh)) return false;
+    fac_load(R, b, v, z, 4);
+    if (k.kind == FT_H1) {   // H0 may replace the block from now on
+        fac_vm0();
+        fac_bar();
+        if (threadIdx.x == 0) fac_up(x.pp + i * (int64_t)4 + 3, 1);
+    }
+    if (x.wc >= 3 && i >= 3 && !fac_acc(x, sc, sm, acc, FacRow{i}, FacRow{c}, i - 3, c, 4, true)) return false;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        z[t] -= acc[t];
+        acc[t] = dbl4{0.0, 0.0, 0.0, 0.0};
+    }
+    const bool ok = fac_solve(x, sc, c, z, o, nullptr, b, v);
+    const bool part = x.wc >= 3 && i >= 3;   // P(i, i - 1) and P(i, i) exist
+    if (k.kind == FT_H0) {
+        // block (i, i - 1) -= R (i - 1, i - 2)^T
+        if (!fac_agree(sm, ok)) return false;
+        SchedDeps d;
+        d.n = 0;
+        deps_add(d, fac_flag(x, FacRow{i - 1}, c), 4);
+        deps_add(d, x.pp + i * (int64_t)4 + 3, 1);
+        if (part) deps_add(d, x.pp + i * (int64_t)4 + 1, 1);
+        if (!sched_wait_deps(sc, d, &sm.sh)) return false;
+        fac_store(R, b, v, o, 4);
+        const double* A = uniform_ptr(fac_band(x, i - 1, c));
+        double* O = fac_band(x, i, i - 1);
+        const int li = lane & 15, lk = lane >> 4;
+        uint32_t oa[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) oa[t] = lds_addr(sm.tk.st[0][0]) + 8u * (uint32_t)(lk * 64 + 16 * (t ^ lk) + li);
+        fac_load(O, b, v, z, 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) fac_issue_a(A, b, q, sm.tk.st[q][0]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q == 0) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+            else fac_landed<2>(3 - q);
+            fac_bar();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                dbl2 a[4];
+                const uint32_t so = (uint32_t)q * (uint32_t)(2 * 16 * 64 * 8) + (uint32_t)h * (8 * 64 * 8);
+                fac_read_a(oa[0] + so, oa[1] + so, oa[2] + so, oa[3] + so, a);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, o[q][2 * h], acc[t], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, o[q][2 * h + 1], acc[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) z[t] -= acc[t];
+        fac_store(O, b, v, z, 4);
+        fac_vm0();
+        fac_bar();
+        if (threadIdx.x == 0 && !quiet) {
+            fac_up(x.hx + i * (int64_t)2, 1);
+            fac_up(fac_flag(x, FacRow{i}, c), 4);
+        }
+        return true;
+    }
+    // H1: block (i, i) -= R R^T, the strips exchanged through LDS
+    double* X = &sm.tk.st[0][0][0];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) X[(v * 4 + p) * 256 + r * 64 + lane] = o[p][r];
+    if (!fac_agree(sm, ok)) return false;
+    if (part && !sched_wait(sc, x.pp + i * (int64_t)4, 1, &sm.sh)) return false;
+    double* O = fac_band(x, i, i);
+    fac_load(O, b, v, z, v + 1);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t <= v) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(X[(t * 4 + p) * 256 + r * 64 + lane], o[p][r], acc[t], 0, 0, 0);
+        }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z[t] -= acc[t];
+    fac_store(O, b, v, z, v + 1);
+    fac_vm0();
+    fac_bar();
+    if (threadIdx.x == 0 && !quiet) fac_up(x.hx + i * (int64_t)2 + 1, 1);
+    return true;
+}
+
+// ---------------------------------------------------------------------------
+// The chain
+// ---------------------------------------------------------------------------
+// Wavefront S owns row tile S of the diagonal block (tiles z[t], t <= S, in
+// registers) and strip S of the block below it, and factors panel S: the
+// panel's 16 x 16 block goes from wavefront to wavefront only as Y_p in LDS,
+// and the next wavefront has its own block up to date as soon as it has
+// solved one tile with it.  The wavefronts meet through progress words in LDS
+// rather than barriers, so a wavefront that is still busy with its strip does
+// not hold up the others.
+
+__device__ inline bool ch_wait(const Sched& sc, FacSmem& sm, const int* f, int target) {
+    int64_t t0 = -1;
+    for (unsigned n = 0;; ++n) {
+        const int v = __builtin_amdgcn_readfirstlane(*(volatile const int*)f);
+        if (v >= target) break;
+        if ((n & 255) == 255) {
+            if (__builtin_amdgcn_readfirstlane(*(volatile int*)&sm.dead) != 0) return false;
+            if (__builtin_amdgcn_readfirstlane(ld_coh_i(sc.err)) != 0) return false;
+            if (t0 < 0) t0 = wall_clock64();
+            if (wall_clock64() - t0 > sc.spin_limit) {
+                set_error_once(sc.err, STILES_ETIMEOUT);
+                return false;
+            }
+        }
+    }
+    asm volatile("" ::: "memory");
+    return true;
+}
+__device__ inline void ch_set(int* f, int v) {
+    // LDS operations of one wavefront complete in order
+    asm volatile("" ::: "memory");
+    *(volatile int*)f = v;
+    asm volatile("" ::: "memory");
+}
+// Y Z^T for one tile (two chains of two products)
+__device__ inline dbl4 ch_solve(const double* Y, const dbl4& z, int li, int lk) {
+    double y[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = Y[(4 * r + lk) * 17 + li];
+    dbl4 p = dbl4{0.0, 0.0, 0.0, 0.0}, q = p;
+    p = __builtin_amdgcn_mfma_f64_16x16x4f64(y[0], z[0], p, 0, 0, 0);
+    q = __builtin_amdgcn_mfma_f64_16x16x4f64(y[1], z[1], q, 0, 0, 0);
+    p = __builtin_amdgcn_mfma_f64_16x16x4f64(y[2], z[2], p, 0, 0, 0);
+    q = __builtin_amdgcn_mfma_f64_16x16x4f64(y[3], z[3], q, 0, 0, 0);
+    return p + q;
+}
+#define CH_TILE(t, p) ((t) * ((t)-1) / 2 + (p))
+
+template <int S>
+__device__ inline bool fac_chain_wave(const FacCtx& x, const Sched& sc, FacSmem& fs, int c0, int c1, int* info,
+                                      bool quiet) {
+    ChainSmem& sm = fs.ch;
+    const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
+    const int b0 = x.L.b;
+    dbl4 o[4];        // strip S of the block row below the previous chunk
+    int* pend = nullptr;
+    if (c0 > 0 && x.wc >= 1) {   // a later launch of the same factor: that block row from memory
+        fac_load(fac_band(x, c0, c0 - 1), b0, S, o, 4);
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sm.R[S][p][r * 64 + lane] = o[p][r];
+        ch_set(&sm.rd[S], 4 * c0);
+    }
+    for (int c = c0; c < c1; ++c) {
+        if (x.wc == 0 && c > c0 + 1) {   // nothing else keeps the wavefronts within two chunks
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (!ch_wait(sc, fs, &sm.fin[t], c - 1)) return false;
+        }
+        const int b = fac_opaque(b0);
+        double(&Yc)[4][16 * 17] = sm.Y[c & 1];
+        double(&Lc)[6][256] = sm.Lt[c & 1];
+        double* D = (double*)uniform_ptr(fac_band(x, c, c));
+        // row S of the diagonal block, up to date with every chunk before c
+        if (x.wc >= 2 && c >= 2 && !fac_wait1(sc, x.hx + c * (int64_t)2 + 1, 1)) return false;
+        dbl4 z[S + 1];
+#pragma unroll
+        for (int t = 0; t < S; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[t][r] = ld_coh_s(D, (uint32_t)((16 * S + li) + (16 * t + 4 * r + lk) * b));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {   // symmetric from the lower triangle
+            const int i = imax_(li, 4 * r + lk), j = imin_(li, 4 * r + lk);
+            z[S][r] = ld_coh_s(D, (uint32_t)((16 * S + i) + (16 * S + j) * b));
+        }
+        if (c > 0 && x.wc >= 1) {
+            dbl4 acc[S + 1];
+#pragma unroll
+            for (int t = 0; t <= S; ++t) {
+                acc[t] = dbl4{0.0, 0.0, 0.0, 0.0};
+                if (t < S && !ch_wait(sc, fs, &sm.rd[t], 4 * c)) return false;
+                dbl4 a2 = acc[t];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const double a = t == S ? o[p][r] : sm.R[t][p][r * 64 + lane];
+                        dbl4& q = (r & 1) ? a2 : acc[t];
+                        q = __builtin_amdgcn_mfma_f64_16x16x4f64(a, o[p][r], q, 0, 0, 0);
+                    }
+                acc[t] += a2;
+            }
+#pragma unroll
+            for (int t = 0; t <= S; ++t) z[t] -= acc[t];
+        }
+        ch_set(&sm.di[S], c + 1);
+        if (S > 0 && pend) {   // the strip stored during the last chunk is in memory by now
+            fac_vm0();
+            if (lane == 0) add_coh_i(pend, 1);
+            pend = nullptr;
+        }
+        // panels before this wavefront's own
+#pragma unroll
+        for (int p = 0; p < S; ++p) {
+            if (!ch_wait(sc, fs, &sm.yd[p], c + 1)) return false;
+            const dbl4 l = ch_solve(Yc[p], z[p], li, lk);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Lc[CH_TILE(S, p)][r * 64 + lane] = l[r];
+            ch_set(&sm.ld[S], 4 * c + p + 1);
+            dbl4 q = dbl4{0.0, 0.0, 0.0, 0.0};
+            z[S] = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[0], l[0], z[S], 0, 0, 0);
+            q = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[1], l[1], q, 0, 0, 0);
+            z[S] = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[2], l[2], z[S], 0, 0, 0);
+            q = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[3], l[3], q, 0, 0, 0);
+            z[S] += q;
+#pragma unroll
+            for (int t = p + 1; t < S; ++t) {
+                if (!ch_wait(sc, fs, &sm.ld[t], 4 * c + p + 1)) return false;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Lc[CH_TILE(t, p)][r * 64 + lane], -l[r], z[t], 0, 0, 0);
+            }
+        }
+        // its own
+        double ld4[4], yv[4];
+        int fail = -1;
+        f16_factor(z[S], ld4, yv, fail);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Yc[S][li * 17 + 4 * q + lk] = yv[q];
+        ch_set(&sm.yd[S], c + 1);
+        if (fail >= 0 && lane == 0) atomicMin(info, c * FC + 16 * S + fail + 1);
+        // panel S to memory: L_SS, Y_S and the tiles below, then its flag
+        {
+            double* Yg = (double*)uniform_ptr(x.Yd + (int64_t)c * 1024 + S * 256);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) st_coh_s(D, (uint32_t)((16 * S + li) + (16 * S + 4 * q + lk) * b), ld4[q]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st_coh_s(Yg, (uint32_t)(r * 64 + lane), Yc[S][(4 * r + lk) * 17 + li]);
+#pragma unroll
+            for (int t = S + 1; t < 4; ++t) {
+                if (!ch_wait(sc, fs, &sm.ld[t], 4 * c + S + 1)) return false;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    st_coh_s(D, (uint32_t)((16 * t + li) + (16 * S + 4 * r + lk) * b), Lc[CH_TILE(t, S)][r * 64 + lane]);
+            }
+            fac_vm0();
+            if (lane == 0) {
+                if (!quiet) fac_up(x.po + c * (int64_t)4 + S, 1);
+                if (pend) add_coh_i(pend, 1);
+            }
+            pend = nullptr;
+        }
+        // strip S of the block row below
+        if (x.wc >= 1 && c + 1 < x.nc) {
+            if (x.wc >= 2 && c >= 1 && !fac_wait1(sc, x.hx + (c + 1) * (int64_t)2, 1)) return false;
+            double* Rb = (double*)uniform_ptr(fac_band(x, c + 1, c));
+            dbl4 y[4];
+            fac_load(Rb, b, S, y, 4);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)   // the strips of the last chunk have been read
+                if (!ch_wait(sc, fs, &sm.di[t], c + 1)) return false;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                if (!ch_wait(sc, fs, &sm.yd[p], c + 1)) return false;
+                o[p] = ch_solve(Yc[p], y[p], li, lk);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sm.R[S][p][r * 64 + lane] = o[p][r];
+                ch_set(&sm.rd[S], 4 * c + p + 1);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    st_coh_s(Rb, (uint32_t)((16 * S + li) + (16 * p + 4 * r + lk) * b), o[p][r]);
+#pragma unroll
+                for (int t = p + 1; t < 4; ++t) {
+                    if (!ch_wait(sc, fs, &sm.ld[t], 4 * c + p + 1)) return false;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        y[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Lc[CH_TILE(t, p)][r * 64 + lane], -o[p][r], y[t], 0, 0, 0);
+                }
+            }
+            pend = fac_flag(x, FacRow{c + 1}, c);
+        }
+        ch_set(&sm.fin[S], c + 1);
+    }
+    fac_vm0();
+    if (pend && lane == 0) add_coh_i(pend, 1);
+    return true;
+}
+
+// Chunks c0 .. c1 - 1 of one matrix; false when the kernel must stop.
+__device__ inline bool fac_chain(const FacCtx& x, const Sched& sc, FacSmem& sm, int c0, int c1, int* info, bool quiet) {
+    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        sm.ch.yd[threadIdx.x] = sm.ch.ld[threadIdx.x] = sm.ch.rd[threadIdx.x] = 0;
+        sm.ch.di[threadIdx.x] = sm.ch.fin[threadIdx.x] = 0;
+    }
+    __syncthreads();
+    bool ok;
+    if (v == 0) ok = fac_chain_wave<0>(x, sc, sm, c0, c1, info, quiet);
+    else if (v == 1) ok = fac_chain_wave<1>(x, sc, sm, c0, c1, info, quiet);
+    else if (v == 2) ok = fac_chain_wave<2>(x, sc, sm, c0, c1, info, quiet);
+    else ok = fac_chain_wave<3>(x, sc, sm, c0, c1, info, quiet);
+    fac_vm0();
+    return fac_agree(sm, ok);
+}

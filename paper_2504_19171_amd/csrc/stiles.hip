@@ -19,7 +19,7 @@
 #include "tile_ops.hpp"
 #include "persist.hpp"
 #include "wave_gemm.hpp"
-#include "potrf3.hpp"
+#include "factor.hpp"
 
 #define NT 256
 #define WS_HEAD 256  // bytes reserved at the start of every workspace (info and scheduler words)
@@ -312,471 +312,86 @@ __global__ __launch_bounds__(NT) void k_trsm_generic(double* C, int64_t ld, int 
 // Factor kernels of the band tile columns
 // ---------------------------------------------------------------------------
 
-// Strict upper triangles of the band diagonal tiles set to 0 (the layout's
-// convention for L; the diagonal-tile POTRF leaves them, as nothing in the
-// factorization reads them).  Eight workgroups per tile, b/8 columns each.
-__device__ inline void zero_upper_body(double* Lm, const Lay& L, int bid) {
+// Compensated sum over a wavefront of the pairs (s, c) of its lanes, joined
+// pairwise in a fixed order (the lower lane of each pair is the left operand,
+// so all lanes agree).
+__device__ inline void neumaier_join(double& s, double& c) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double qs = __shfl_xor(s, o), qc = __shfl_xor(c, o);
+        const bool lo = (lane & o) == 0;
+        const double a = lo ? s : qs, b = lo ? qs : s;
+        const double t = a + b;
+        const double e = (fabs(a) >= fabs(b)) ? (a - t) + b : (b - t) + a;
+        c = (lo ? c + qc : qc + c) + e;
+        s = t;
+    }
+}
+
+// After the band: the strict upper triangles of its diagonal tiles set to 0
+// (the layout's convention for L; nothing in the factorization reads them),
+// eight workgroups per tile, b/8 columns each; the first of the eight also
+// sums the tile's part of log det, 2 log L_jj over its columns (off the
+// chain, which only stores the diagonal).
+__device__ inline void factor_tail_body(double* Lm, const Lay& L, int bid, double* ldp) {
     const int64_t J = bid >> 3;
     const int cw = L.b / 8, c0 = (bid & 7) * cw;
-    double* T = Lm + L.band(J, 0);
+    double* T = (double*)(GLOBAL_AS double*)(Lm + L.band(J, 0));
     for (int c = c0; c < c0 + cw; ++c)
         for (int i = threadIdx.x; i < c; i += NT) T[i + (int64_t)c * L.b] = 0.0;
-}
-__global__ __launch_bounds__(NT) void k_zero_upper(double* Lm, Lay L) { zero_upper_body(Lm, L, blockIdx.x); }
-
-// Panel TRSM of one 16-row block C (16 x b, leading dimension ld), R = C
-// L_JJ^{-T} in place, one 16-column panel p per step:
-//   Z_p = C_p - sum_{p' < p} R_p' L_{p,p'}^T,   R_p = Z_p Y_p^T   (Y_p = L_pp^{-1}),
-// with the transposed products on the matrix cores (Z_p^T = C_p^T - L_{p,p'}
-// R_p'^T, R_p^T = Y_p Z_p^T) so every global access runs down a column.  The
-// reduction of a step is spread over the 4 wavefronts (panels p' = w, w+4,
-// ... of wavefront w) and summed in LDS in a fixed order; the tiles L_{p,p'}
-// of the next step are loaded while the current one is multiplied.  R stays in
-// LDS ([column][row]) and is zero where not yet computed, so a product with a
-// panel that is not there yet adds nothing and the loop has no branches.
-//
-// Concurrent mode (fpo != nullptr): L_JJ is being factored (potrf3) at the
-// same time; step p waits until *fpo > p, reads L and Y with device-coherent
-// loads, writes R with device-coherent stores and raises *ftr after each step.
-#define TR_LD 16
-struct TrSmem {
-    double R[256 * TR_LD];
-    double P[4][256];
-    int sh;
-};
-__device__ inline bool tr_panel(double* C, int ld, const double* Ljj, const double* Yd, int b, const int* fpo,
-                                int* ftr, const Sched& sc, TrSmem& sm, int ticket) {
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int np = b / 16;
-    const bool coh = fpo != nullptr;
-    C = (double*)uniform_ptr(C);
-    Ljj = uniform_ptr(Ljj);
-    Yd = uniform_ptr(Yd);
-    for (int e = threadIdx.x; e < b * TR_LD; e += blockDim.x) sm.R[e] = 0.0;
-    auto ldL = [&](uint32_t idx) { return coh ? ld_coh_s(Ljj, idx) : ld_s(Ljj, idx); };
-    // A operands of step s for this wavefront: -L_{s,p'} for p' = w + 4t (the
-    // tile column clamped into the finished part; its product is then with a
-    // zero panel of R)
-    auto fetchA = [&](double (&a)[4][4], int s) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int pa = imax_(0, imin_(w + 4 * t, s - 1));
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) a[t][kk] = -ldL((uint32_t)((16 * s + li) + (16 * pa + 4 * kk + lk) * b));
-        }
-    };
-    double acur[4][4], anext[4][4];
-    dbl4 cn;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) cn[r] = coh ? ld_coh_s(C, (uint32_t)(li + (4 * r + lk) * ld)) : ld_s(C, (uint32_t)(li + (4 * r + lk) * ld));
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) acur[t][kk] = 0.0;
-    __syncthreads();
-    for (int p = 0; p < np; ++p) {
-        if (coh && !sched_wait(sc, (int*)fpo, p + 1, &sm.sh)) return false;
-        // loads for this step's Y and the next step's operands (panels <= p
-        // are finished, so the tiles L_{p+1,p'}, p' <= p, are there)
-        double yv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t yi = (uint32_t)(p * 256 + li + 16 * (4 * r + lk));
-            yv[r] = coh ? ld_coh_s(Yd, yi) : ld_s(Yd, yi);
-        }
-        const int pn = imin_(p + 1, np - 1);
-        fetchA(anext, pn);
-        dbl4 cnext;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t ci = (uint32_t)(li + (16 * pn + 4 * r + lk) * ld);
-            cnext[r] = coh ? ld_coh_s(C, ci) : ld_s(C, ci);
-        }
-        // this wavefront's part of Z_p^T (wavefronts past the fourth, if the
-        // workgroup has them, only keep the barriers)
-        if (w < 4) {
-            dbl4 z;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) z[r] = (w == 0) ? cn[r] : 0.0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int p2 = imin_(w + 4 * t, np - 1);
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-                    z = __builtin_amdgcn_mfma_f64_16x16x4f64(acur[t][kk], sm.R[(16 * p2 + 4 * kk + lk) * TR_LD + li], z,
-                                                             0, 0, 0);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sm.P[w][r * 64 + lane] = z[r];
-        }
-        __syncthreads();
-        if (w == 0) {
-            // Z_p^T in the D layout is the B operand of R_p^T = Y_p Z_p^T as it stands
-            dbl4 zs, o = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                zs[r] = ((sm.P[0][r * 64 + lane] + sm.P[1][r * 64 + lane]) + sm.P[2][r * 64 + lane]) +
-                        sm.P[3][r * 64 + lane];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o = __builtin_amdgcn_mfma_f64_16x16x4f64(yv[r], zs[r], o, 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                sm.R[(16 * p + 4 * r + lk) * TR_LD + li] = o[r];
-                const uint32_t ci = (uint32_t)(li + (16 * p + 4 * r + lk) * ld);
-                if (coh) st_coh_s(C, ci, o[r]);
-                else st_s(C, ci, o[r]);
-            }
-        }
-        if (ftr) sched_signal(sc, ftr, ticket);   // waits for the stores, then a barrier
-        else __syncthreads();
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) acur[t][kk] = anext[t][kk];
-        cn = cnext;
-    }
-    return true;
-}
-
-// ---------------------------------------------------------------------------
-// The factorization of one tile column J as one persistent launch: POTRF of
-// the diagonal tile, the panel TRSM of every 16-row block below it and the
-// trailing update of every 64 x 64 target block, run concurrently and
-// pipelined on the 16-column panels of L_JJ through device counters.
-// ---------------------------------------------------------------------------
-
-// Per tile column counters (ints, zeroed once per factorization): the ticket
-// counter, the number of panels of L_JJ announced by POTRF, then per 16-row
-// block of the TRSM the number of its finished steps.
-#define CF_TICKET 0
-#define CF_PO 1
-#define CF_TR 4
-__host__ __device__ inline int col_tr_blocks(const Lay& L, int64_t J) { return L.s(J) * (L.b / 16) + L.ap / 16; }
-__host__ __device__ inline int col_stride(const Lay& L) { return CF_TR + L.bt * (L.b / 16) + L.ap / 16; }
-
-// Trailing-update target blocks of tile column J, 64 x 64, in this order:
-//   band (J+d, J+e), 1 <= e <= d <= s:  -= L_{J+d,J} L_{J+e,J}^T   (lower blocks when d == e)
-//   arrow (A, J+e):                      -= L_{A,J} L_{J+e,J}^T
-//   corner (lower blocks):               -= L_{A,J} L_{A,J}^T
-// (the block of (J+1, J+1) that the next POTRF needs first comes first).
-struct UpBlock {
-    const double* A;   // operand rows (64-row block), leading dimension lda, rows_a valid in its tile
-    const double* B;
-    double* O;         // target block, leading dimension ldo
-    int lda, ldb, ldo;
-    int rows_a, rows_b;   // valid rows from the block's first row on (<= 64)
-    int ga, gb;           // TRSM row blocks (16 rows) of the first rows of A and B
-    int diag;             // a diagonal block of a symmetric target: lower part only
-    int* cnt;             // single-launch factor: updates applied to the target so far (else nullptr)
-    int before;           // ... and how many come before this one
-};
-
-// Single-launch factor: per 64 x 64 target block, the number of tile columns
-// whose update of it is done.  Band tile (K+d, K), block (i, j); arrow tile
-// K, block (i, j); corner block (i, j).  Tile (I, K) of the band is updated
-// by the columns max(0, I - B) .. K - 1, arrow tile K by max(0, K - B) ..
-// K - 1, the corner by every column.
-__host__ __device__ inline int64_t upd_band(const Lay& L, int64_t K, int d, int i, int j) {
-    const int C64 = L.b / 64;
-    return ((K * (L.bt + 1) + d) * C64 + i) * C64 + j;
-}
-__host__ __device__ inline int64_t upd_arrow(const Lay& L, int64_t K, int i, int j) {
-    const int C64 = L.b / 64, na = (L.ap + 63) / 64;
-    return L.nt * (int64_t)(L.bt + 1) * C64 * C64 + (K * na + i) * C64 + j;
-}
-__host__ __device__ inline int64_t upd_corner(const Lay& L, int i, int j) {
-    const int C64 = L.b / 64, na = (L.ap + 63) / 64;
-    return L.nt * (int64_t)(L.bt + 1) * C64 * C64 + L.nt * (int64_t)na * C64 + (int64_t)i * na + j;
-}
-__host__ __device__ inline int64_t upd_ints(const Lay& L) {
-    const int na = (L.ap + 63) / 64;
-    return upd_corner(L, 0, 0) + (int64_t)na * na;
-}
-__host__ __device__ inline int col_up_blocks(const Lay& L, int64_t J) {
-    const int C64 = L.b / 64, s = L.s(J), na = (L.ap + 63) / 64;
-    int cnt = 0;
-    for (int d = 1; d <= s; ++d)
-        for (int e = 1; e <= d; ++e) cnt += (d == e) ? C64 * (C64 + 1) / 2 : C64 * C64;
-    if (L.ap > 0) cnt += s * na * C64 + na * (na + 1) / 2;
-    return cnt;
-}
-__device__ inline UpBlock col_up_decode(double* Lm, const Lay& L, int64_t J, int t, int* upd) {
-    const int C64 = L.b / 64, s = L.s(J), na = (L.ap + 63) / 64, nbr = L.b / 16, b = L.b;
-    UpBlock u;
-    u.cnt = nullptr;
-    u.before = 0;
-    for (int d = 1; d <= s; ++d) {
-        for (int e = 1; e <= d; ++e) {
-            const int cnt = (d == e) ? C64 * (C64 + 1) / 2 : C64 * C64;
-            if (t < cnt) {
-                int i, j;
-                if (d == e) tri_decode(t, i, j);
-                else { i = t % C64; j = t / C64; }
-                u.A = Lm + L.band(J, d) + 64 * i; u.lda = b; u.rows_a = 64; u.ga = (d - 1) * nbr + 4 * i;
-                u.B = Lm + L.band(J, e) + 64 * j; u.ldb = b; u.rows_b = 64; u.gb = (e - 1) * nbr + 4 * j;
-                u.O = Lm + L.band(J + e, d - e) + 64 * i + (int64_t)64 * j * b; u.ldo = b;
-                u.diag = (d == e && i == j);
-                if (upd) {
-                    u.cnt = upd + upd_band(L, J + e, d - e, i, j);
-                    u.before = (int)(J - imax64(0, J + d - L.bt));
-                }
-                return u;
-            }
-            t -= cnt;
+    if ((bid & 7) == 0 && threadIdx.x < 64) {
+        double s = 0.0, c = 0.0;
+        for (int j = threadIdx.x; j < L.b; j += 64) neumaier(s, c, 2.0 * log(T[j * (int64_t)(L.b + 1)]));
+        neumaier_join(s, c);
+        if (threadIdx.x == 0) {
+            ldp[2 * J] = s;
+            ldp[2 * J + 1] = c;
         }
     }
-    const int ga0 = s * nbr;
-    if (t < s * na * C64) {
-        const int e = 1 + t / (na * C64), r = t % (na * C64), i = r % na, j = r / na;
-        u.A = Lm + L.arrow(J) + 64 * i; u.lda = L.ap; u.rows_a = imin_(64, L.ap - 64 * i); u.ga = ga0 + 4 * i;
-        u.B = Lm + L.band(J, e) + 64 * j; u.ldb = b; u.rows_b = 64; u.gb = (e - 1) * nbr + 4 * j;
-        u.O = Lm + L.arrow(J + e) + 64 * i + (int64_t)64 * j * L.ap; u.ldo = L.ap;
-        u.diag = 0;
-        if (upd) {
-            u.cnt = upd + upd_arrow(L, J + e, i, j);
-            u.before = (int)(J - imax64(0, J + e - L.bt));
-        }
-        return u;
-    }
-    t -= s * na * C64;
-    int i, j;
-    tri_decode(t, i, j);
-    u.A = Lm + L.arrow(J) + 64 * i; u.lda = L.ap; u.rows_a = imin_(64, L.ap - 64 * i); u.ga = ga0 + 4 * i;
-    u.B = Lm + L.arrow(J) + 64 * j; u.ldb = L.ap; u.rows_b = imin_(64, L.ap - 64 * j); u.gb = ga0 + 4 * j;
-    u.O = Lm + L.corner() + 64 * i + (int64_t)64 * j * L.ap; u.ldo = L.ap;
-    u.diag = (i == j);
-    if (upd) {
-        u.cnt = upd + upd_corner(L, i, j);
-        u.before = (int)J;
-    }
-    return u;
+}
+__global__ __launch_bounds__(NT) void k_factor_tail(double* Lm, Lay L, double* ldp) {
+    factor_tail_body(Lm, L, blockIdx.x, ldp);
 }
 
-// Thread 0 waits until every flag[k], k < n, is at least target; then the
-// workgroup goes on (false: stop, the kernel is being abandoned).
-__device__ inline bool col_wait(const Sched& sc, const int* flag, int n, int target, int* sh) {
-    if (threadIdx.x == 0) {
-        int ok = 1;
-        const int64_t t0 = wall_clock64();
-        for (int k = 0; k < n && ok; ++k) {
-            while (ld_coh_i(flag + k) < target) {
-                if (ld_coh_i(sc.err) != 0) { ok = 0; break; }
-                if (wall_clock64() - t0 > sc.spin_limit) {
-                    set_error_once(sc.err, STILES_ETIMEOUT);
-                    ok = 0;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(2);
-            }
-        }
-        *sh = ok;
-    }
-    __syncthreads();
-    const bool ok = __builtin_amdgcn_readfirstlane(*sh) != 0;
-    __syncthreads();
-    return ok;
-}
-
-// One 64 x 64 target block, accumulated one 16-column panel of tile column J
-// at a time as the TRSM steps of its rows are announced.  Wavefront w < 4
-// owns the 32 x 32 quarter (w/2, w%2), four 16 x 16 tiles; tiles past the
-// valid rows, and tiles above the diagonal of a diagonal block, are not
-// stored (a fifth wavefront's quarter lies past the block: it stores nothing).
-__device__ inline bool col_update(const UpBlock& u, const int* ftr, int np, const Sched& sc, int* sh, int ticket) {
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    const int qi = w >> 1, qj = w & 1;
-    const double* A = uniform_ptr(u.A);
-    const double* B = uniform_ptr(u.B);
-    double* O = (double*)uniform_ptr(u.O);
-    const int ta = (u.rows_a + 15) / 16, tb = (u.rows_b + 15) / 16;   // valid 16-row tiles
-    int ra[2], rb[2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        ra[x] = imin_(2 * qi + x, ta - 1);
-        rb[x] = imin_(2 * qj + x, tb - 1);
-    }
-    dbl4 acc[2][2];
-    double ov[2][2][4];
-    // the target as the earlier tile columns left it (device-coherent: in the
-    // single-launch factor they are other workgroups of the same kernel)
-    if (u.cnt && u.before > 0 && !sched_wait(sc, u.cnt, u.before, sh)) return false;
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            acc[x][y] = dbl4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                ov[x][y][r] = ld_coh_s(O, (uint32_t)((16 * ra[x] + li) + (16 * rb[y] + 4 * r + lk) * u.ldo));
-        }
-    // the operands of panel p + 1 are loaded (once its TRSM steps are
-    // announced) while panel p is multiplied
-    double av[2][4], bv[2][4], an[2][4], bn[2][4];
-    auto load = [&](double (&a)[2][4], double (&b)[2][4], int p) {
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                a[x][kk] = ld_coh_s(A, (uint32_t)((16 * ra[x] + li) + (16 * p + 4 * kk + lk) * u.lda));
-                b[x][kk] = ld_coh_s(B, (uint32_t)((16 * rb[x] + li) + (16 * p + 4 * kk + lk) * u.ldb));
-            }
-    };
-    if (!col_wait(sc, ftr + u.ga, ta, 1, sh)) return false;
-    if (!col_wait(sc, ftr + u.gb, tb, 1, sh)) return false;
-    load(av, bv, 0);
-    for (int p = 0; p < np; ++p) {
-        if (p + 1 < np) {
-            if (!col_wait(sc, ftr + u.ga, ta, p + 2, sh)) return false;
-            if (!col_wait(sc, ftr + u.gb, tb, p + 2, sh)) return false;
-            load(an, bn, p + 1);
-        }
-        // element r of acc[x][y]: sum_k A[16 ra + li][k] B[16 rb + 4r + lk][k]
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[y][kk], av[x][kk], acc[x][y], 0, 0, 0);
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                av[x][kk] = an[x][kk];
-                bv[x][kk] = bn[x][kk];
-            }
-    }
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            const int ti = 2 * qi + x, tj = 2 * qj + y;
-            if (ti < ta && tj < tb && !(u.diag && ti < tj)) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    st_coh_s(O, (uint32_t)((16 * ti + li) + (16 * tj + 4 * r + lk) * u.ldo), ov[x][y][r] - acc[x][y][r]);
-            }
-        }
-    if (u.cnt) sched_signal(sc, u.cnt, ticket);   // waits for the stores, then a barrier
-    return true;
-}
-
-// Tickets, in an order where every task waits only for smaller ones (so the
-// launch cannot deadlock, however many workgroups are resident): 0 is the
-// POTRF of L_JJ, then the TRSM row blocks (tile J+1 first), then the update
-// blocks.  The factorization of the next tile column is the next launch.
-template <int NPOOL>
-union ColSmemT {
-    P3SmemT<NPOOL> po;
-    TrSmem tr;
-};
-using ColSmem = ColSmemT<P3_POOL>;
-// Task t of tile column J; false when the kernel must stop (a wait failed).
-// upd (single-launch factor, else nullptr): the POTRF waits until the
-// earlier columns' updates of its tile are in, a TRSM block until those of
-// its rows are; the update blocks wait for the earlier updates of their
-// targets (col_update).  gt: the task's ticket in the launch (the test hook
-// Sched::withhold names one whose signals are never sent).
-template <int NPOOL>
-__device__ inline bool col_task(ColSmemT<NPOOL>& sm, int& sh, double* Lm, const Lay& L, int64_t J, double* Yd, int* cf,
-                                const Sched& st, double* ldp, int* info, int t, int* upd, int gt) {
-    const int ntr = col_tr_blocks(L, J);
-    const int nbr = L.b / 16, s = L.s(J), C64 = L.b / 64;
-    int* fpo = cf + CF_PO;
-    int* ftr = cf + CF_TR;
-    {
-        TRACE(gt, 3, (unsigned long long)(t == 0 ? 0 : (t <= ntr ? 1 : 2)) | ((unsigned long long)J << 8) |
-                         ((unsigned long long)t << 40));
-        if (t == 0) {
-            if (upd) {
-                const int need = (int)(J - imax64(0, J - L.bt));
-                for (int i = 0; i < C64 && need > 0; ++i)
-                    if (!col_wait(st, upd + upd_band(L, J, 0, i, 0), i + 1, need, &sh)) return false;
-            }
-            TRACE(gt, 1, wall_clock64());
-            int fail;
-            double ls, lc;
-            potrf3(Lm + L.band(J, 0), L.b, L.b, Yd, sm.po, &fail, &ls, &lc, gt == st.withhold ? nullptr : fpo);
-            if (threadIdx.x == 0) {
-                ldp[0] = ls;
-                ldp[1] = lc;
-                if (fail >= 0) atomicMin(info, (int)(J * L.b + fail + 1));
-            }
-        } else if (t <= ntr) {
-            const int g = t - 1;
-            double* C;
-            int ld;
-            if (g < s * nbr) { C = Lm + L.band(J, 1 + g / nbr) + (g % nbr) * 16; ld = L.b; }
-            else { C = Lm + L.arrow(J) + (g - s * nbr) * 16; ld = L.ap; }
-            if (upd) {
-                bool ok = true;
-                if (g < s * nbr) {
-                    const int d = 1 + g / nbr;
-                    const int need = (int)(J - imax64(0, J + d - L.bt));
-                    if (need > 0) ok = col_wait(st, upd + upd_band(L, J, d, (g % nbr) / 4, 0), C64, need, &sh);
-                } else {
-                    const int need = (int)(J - imax64(0, J - L.bt));
-                    if (need > 0) ok = col_wait(st, upd + upd_arrow(L, J, (g - s * nbr) / 4, 0), C64, need, &sh);
-                }
-                if (!ok) return false;
-            }
-            TRACE(gt, 1, wall_clock64());
-            if (!tr_panel(C, ld, Lm + L.band(J, 0), Yd, L.b, fpo, ftr + g, st, sm.tr, gt)) return false;
-        } else {
-            const UpBlock u = col_up_decode(Lm, L, J, t - 1 - ntr, upd);
-            TRACE(gt, 1, wall_clock64());
-            if (!col_update(u, ftr, L.b / 16, st, &sh, gt)) return false;
-        }
-    }
-    TRACE(gt, 2, wall_clock64());
-    return true;
-}
-// The whole factor of the band tile columns in one persistent launch.
-// Ticket g is task g - off[J] of tile column J (off: first ticket of each
-// column, off[N] = all), so the tasks go column by column and, inside a
-// column, in the order above: every wait is for a smaller ticket, and the
-// launch cannot deadlock however many workgroups are resident.  Across
-// columns the tasks wait on the update counters (col_task): the POTRF of
-// column J+1 starts as soon as column J's updates of its tile are in, while
-// the rest of column J's trailing update goes on.
-__global__ __launch_bounds__(P3_NT) void k_factor_all(double* Lm, Lay L, double* Yd, int* cf, int* upd, const int* off,
-                                                   Sched sc, double* ldp, int* info) {
-    __shared__ ColSmem sm;
-    __shared__ int sh;
-    const int64_t N = L.nt;
-    const int ntot = off[N];
-    const int cstride = col_stride(L);
-    for (;;) {
-        const int g = sched_next(sc, ntot, &sh);
-        if (g < 0) return;
-        TRACE(g, 0, wall_clock64());
-        int lo = 0, hi = (int)N;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (off[mid] <= g) lo = mid; else hi = mid;
-        }
-        const int64_t J = lo;
-        if (!col_task(sm, sh, Lm, L, J, Yd + J * (int64_t)L.b * 16, cf + J * cstride, sc, ldp + 2 * J, info,
-                      g - off[J], upd, g))
+// Group and index inside it of task t of one matrix.
+__device__ inline void fac_ticket(const FacCtx& x, int t, int& c, int& u) {
+    const int f4 = fac_full4(x);
+    if (f4 > 0) {
+        const int n = fac_group(x, 0), n4 = 3 * n + fac_group(x, 3);
+        const int q = t / n4;
+        if (q < f4 / 4) {
+            const int r = t - q * n4, e = imin_(r / n, 3);
+            c = 4 * q + e;
+            u = r - e * n;
             return;
+        }
+        t -= f4 / 4 * n4;
     }
+    for (c = f4; c < x.nc - 1; ++c) {
+        const int n = fac_group(x, c);
+        if (t < n) break;
+        t -= n;
+    }
+    u = t;
 }
 
-// First ticket of every tile column (off[N] = all tickets), and the ticket counter.
-// A column's task count depends on J only through s(J): every column before
-// J1 = N - B has the full count, so off[J] is J1 (or J) times that count plus
-// at most B tail terms, one thread per entry.
-__global__ void k_factor_offsets(Lay L, int* off, int* ticket) {
-    const int64_t N = L.nt, J1 = imax64(0, N - L.bt);
-    const int64_t cs = J1 > 0 ? 1 + col_tr_blocks(L, 0) + col_up_blocks(L, 0) : 0;
-    for (int64_t J = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; J <= N; J += (int64_t)gridDim.x * blockDim.x) {
-        int64_t acc = (J < J1 ? J : J1) * cs;
-        for (int64_t K = J1; K < J; ++K) acc += 1 + col_tr_blocks(L, K) + col_up_blocks(L, K);
-        off[J] = (int)acc;
+// The band factor of one matrix in one persistent launch (factor.hpp): ticket
+// 0 is the chain, ticket 1 + t task t.
+__global__ __launch_bounds__(FAC_NT, 2) void k_factor_all(FacCtx x, int ntask, Sched sc, int* info) {
+    __shared__ FacSmem sm;
+    if (threadIdx.x == 0) sm.dead = 0;
+    for (;;) {
+        const int g = sched_next(sc, 1 + ntask, &sm.sh);
+        if (g < 0) return;
+        if (g == 0) {
+            if (!fac_chain(x, sc, sm, 0, x.nc, info, g == sc.withhold)) return;
+            continue;
+        }
+        int c, u;
+        fac_ticket(x, g - 1, c, u);
+        if (!fac_task(x, sc, sm, c, u, g)) return;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
 }
 
 // C (rows x rows, lower blocks) -= P P^T, P rows x K (generic, corner blocking).
@@ -798,21 +413,23 @@ __global__ void k_zero_block(double* C, int64_t ld, int rows, int cols) {
         C[(idx % rows) + (int64_t)(idx / rows) * ld] = 0.0;
 }
 
-// Final log det (Neumaier sum of the per-block partials, in order) and info.
+// Final log det (compensated sum of the partial pairs in a fixed order: each
+// lane of the one wavefront every 64th, then joined) and info.
 __device__ inline void factor_final_body(const double* ldp, int nparts, const int* info_ws, const int* err,
                                          double* logdet, int* info) {
     double s = 0.0, c = 0.0;
-    for (int i = 0; i < nparts; ++i) {
+    for (int i = threadIdx.x; i < nparts; i += 64) {
         neumaier(s, c, ldp[2 * i]);
         neumaier(s, c, ldp[2 * i + 1]);
     }
+    neumaier_join(s, c);
+    if (threadIdx.x != 0) return;
     const int f = (*err != 0) ? *err : *info_ws;
     *info = (f == 0x7fffffff) ? 0 : f;
     *logdet = (f == 0x7fffffff) ? (s + c) : __builtin_nan("");
 }
-__global__ void k_factor_final(const double* ldp, int nparts, const int* info_ws, const int* err, double* logdet,
-                               int* info) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ __launch_bounds__(64) void k_factor_final(const double* ldp, int nparts, const int* info_ws, const int* err,
+                                                     double* logdet, int* info) {
     factor_final_body(ldp, nparts, info_ws, err, logdet, info);
 }
 
@@ -1361,26 +978,36 @@ __global__ void k_selinv_final(const int* info_ws, const int* err, int* info) {
 struct FactorWs {
     int* winfo;     // first failing column (atomicMin), 0x7fffffff when none
     int* err;       // scheduler error word
+    int* ticket;
     double* ldp;    // log det partial pairs, N + 2 of them
     double* Xc;     // 256 x 256 inverse of the blocked corner
     double* Yd;     // 16 x 16 diagonal-block inverses of every L_JJ
-    int* cf;        // per tile column counters
-    int* upd;       // update counters of the single-launch factor (upd_ints)
-    int* off;       // first ticket of every tile column (N + 1)
-    int* ticket;
+    int* flags;     // fac_ints(L) flags
 };
 __host__ __device__ inline FactorWs factor_ws(const Lay& L, char* ws) {
     FactorWs f;
     f.winfo = (int*)ws;
     f.err = f.winfo + 16;
+    f.ticket = f.winfo + 32;
     f.ldp = (double*)(ws + WS_HEAD);
     f.Xc = f.ldp + 2 * (L.nt + 2);
     f.Yd = f.Xc + 256 * 256;
-    f.cf = (int*)(f.Yd + L.nt * (int64_t)L.b * 16);
-    f.upd = f.cf + L.nt * (int64_t)col_stride(L);
-    f.off = f.upd + upd_ints(L);
-    f.ticket = f.winfo + 32;
+    f.flags = (int*)(f.Yd + L.nt * (int64_t)L.b * 16);
     return f;
+}
+
+// Before a factor: no failing column, no error, first ticket, no flag up.
+__device__ inline void factor_setup_body(const Lay& L, const FactorWs& f, int64_t at, int64_t step) {
+    if (at == 0) {
+        *f.winfo = 0x7fffffff;
+        *f.err = 0;
+        *f.ticket = 0;
+    }
+    const int64_t n = fac_ints(L);
+    for (int64_t i = at; i < n; i += step) f.flags[i] = 0;
+}
+__global__ __launch_bounds__(NT) void k_factor_setup(Lay L, FactorWs f) {
+    factor_setup_body(L, f, threadIdx.x + (int64_t)blockIdx.x * NT, (int64_t)NT * gridDim.x);
 }
 
 // Sub-buffers of a selinv workspace.
@@ -1463,81 +1090,79 @@ __device__ inline int bseg_find(const BSeg* seg, int nseg, int b) {
 // 762 us per pass; not used here.)
 #define BATCH_DECODE(a, I, bid, nblk) BATCH_DECODE_AT(a, I, bid, nblk, (int)blockIdx.x)
 
-// Factor set-up of every matrix (one workgroup per matrix): info and error
-// words, tile column counters and update counters (contiguous).
+// Factor set-up of every matrix (eight workgroups each).
 __global__ __launch_bounds__(NT) void kb_factor_setup(const BInst* bi) {
-    const BInst& I = bi[blockIdx.x];
-    const FactorWs f = factor_ws(I.L, I.ws);
-    if (threadIdx.x == 0) {
-        *f.winfo = 0x7fffffff;
-        *f.err = 0;
-    }
-    const int64_t n = I.L.nt * (int64_t)col_stride(I.L) + upd_ints(I.L);
-    for (int64_t i = threadIdx.x; i < n; i += NT) f.cf[i] = 0;
+    const BInst& I = bi[blockIdx.x >> 3];
+    factor_setup_body(I.L, factor_ws(I.L, I.ws), threadIdx.x + (int64_t)(blockIdx.x & 7) * NT, 8 * NT);
 }
 
-// Tile columns J0 .. J0 + ncol - 1 of every matrix (those with N > J) in one
-// launch, all their tasks on one ticket queue, column after column.  Inside
-// column c, ticket tb[c] + g is local task t of matrix order[g - off[t]] (the
-// matrices sorted by decreasing task count, so those with more than t tasks
-// come first), i.e. task 0 (the POTRFs) of every matrix first, then task 1 of
-// every matrix, and so on.  Each matrix's tasks keep their order, and the
-// tasks of a column wait for the earlier columns' updates of their tiles
-// through the per-block update counters (as in k_factor_all), so every task
-// waits only for smaller tickets: the POTRF of column J0 + 1 starts as soon as
-// column J0's updates of its tile are in, while the rest of column J0 goes on.
-#define KB_COL_WG_PER_CU 2   // workgroups per compute unit of kb_column at tiles <= 128 (registers: 252 VGPRs)
-#define KB_COL_MAX 16        // tile columns per kb_column launch, at most
-struct BColArgs {
+// Chunks c0 .. c0 + ncol - 1 (64 columns each) of the matrices [m0, m1) of the
+// batch's order (decreasing chunk count, so those that still have a chunk c
+// come first) in one launch.  The first tickets are the chains, one per
+// matrix; then every group's tasks chunk after chunk, matrix after matrix.
+// Each matrix's tasks keep their order, so a task waits only for smaller
+// tickets and chains.  A chain goes on from where the launch before left it.
+// At most KB_SLICE matrices share a launch, so that the chains never take
+// more than half of its workgroups.
+#define KB_COL_MAX 64        // chunks per launch, at most
+#define KB_SLICE 128
+struct BFacArgs {
     const BInst* bi;
     const int* ints;                 // the queue tables
-    int ncol;
-    int tb[KB_COL_MAX + 1];          // first ticket of each column; tb[ncol]: all
-    int off_at[KB_COL_MAX];          // ints + off_at[c]: off of column c, [T[c] + 1]
-    int order_at[KB_COL_MAX];        // ints + order_at[c]: its matrices, by decreasing task count
-    int T[KB_COL_MAX];               // most tasks of one matrix in column c
+    int order_at;                    // ints + order_at: the matrices in order
+    int m0, m1;
+    int c0, ncol;
+    int tb[KB_COL_MAX + 1];          // first ticket of each chunk; tb[0]: the chains; tb[ncol]: all
+    int pre_at[KB_COL_MAX];          // ints + pre_at[g]: tasks of the matrices before each, in chunk c0 + g
+    int act[KB_COL_MAX];             // matrices of the slice that have chunk c0 + g
     int* ticket;
     int* err;                        // the batch's error word
     int64_t spin_limit;
 };
-// NPOOL = P3_POOL_128 when every tile of the batch is at most 128 wide: the
-// smaller LDS footprint (49 KB against 147 KB) lets two workgroups share a
-// compute unit, so the many small TRSM and update tasks of a column run twice
-// as wide.
-template <int NPOOL>
-__global__ __launch_bounds__(P3_NT) void kb_column(BColArgs a, int64_t J0) {
-    __shared__ ColSmemT<NPOOL> sm;
-    __shared__ int sh;
+__global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BFacArgs a) {
+    __shared__ FacSmem sm;
+    if (threadIdx.x == 0) sm.dead = 0;
     Sched sc;
     sc.ticket = a.ticket;
     sc.err = a.err;
     sc.spin_limit = a.spin_limit;
     sc.withhold = -1;
     for (;;) {
-        const int g = sched_next(sc, a.tb[a.ncol], &sh);
+        const int g = sched_next(sc, a.tb[a.ncol], &sm.sh);
         if (g < 0) return;
-        int c = 0;
-        while (c + 1 < a.ncol && g >= a.tb[c + 1]) ++c;
-        const int gl = g - a.tb[c];
-        const int* off = a.ints + a.off_at[c];
-        int lo = 0, hi = a.T[c];
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (off[mid] <= gl) lo = mid; else hi = mid;
+        int m, c = a.c0, u = 0;
+        if (g < a.tb[0]) {
+            m = a.m0 + g;
+        } else {
+            int e = 0;
+            while (e + 1 < a.ncol && g >= a.tb[e + 1]) ++e;
+            c = a.c0 + e;
+            // the matrix: entries of the prefix sums at or below the ticket,
+            // 64 at a time
+            const int* pre = a.ints + a.pre_at[e] + a.m0;
+            const int lane = threadIdx.x & 63, n = a.act[e];
+            const int want = g - a.tb[e] + pre[0];
+            int k = 0;
+            for (int j = 0; j < n; j += 64)
+                k += __popcll(__ballot(j + lane < n && pre[imin_(j + lane, n - 1) + 1] <= want));
+            k = imin_(k, n - 1);
+            m = a.m0 + k;
+            u = want - pre[k];
         }
-        const int t = lo;
-        const BInst& I = a.bi[a.ints[a.order_at[c] + gl - off[t]]];
-        const int64_t J = J0 + c;
+        const BInst& I = a.bi[a.ints[a.order_at + m]];
         const FactorWs f = factor_ws(I.L, I.ws);
-        if (!col_task(sm, sh, I.Lm, I.L, J, f.Yd + J * (int64_t)I.L.b * 16, f.cf + J * col_stride(I.L), sc,
-                      f.ldp + 2 * J, f.winfo, t, f.upd, g))
+        const FacCtx x = fac_ctx(I.L, I.Lm, f.Yd, f.flags);
+        if (g < a.tb[0]) {
+            if (!fac_chain(x, sc, sm, a.c0, imin_(a.c0 + a.ncol, x.nc), f.winfo, false)) return;
+        } else if (!fac_task(x, sc, sm, c, u, g)) {
             return;
+        }
     }
 }
 
-__global__ __launch_bounds__(NT) void kb_zero_upper(BArgs a) {
+__global__ __launch_bounds__(NT) void kb_factor_tail(BArgs a) {
     BATCH_DECODE(a, I, bid, nblk);
-    zero_upper_body(I.Lm, I.L, bid);
+    factor_tail_body(I.Lm, I.L, bid, factor_ws(I.L, I.ws).ldp);
 }
 
 // Corner POTRF (a_p <= 256) of the matrices listed in idx, one workgroup each.
@@ -1548,8 +1173,7 @@ __global__ __launch_bounds__(NT) void kb_corner(const BInst* bi, const int* idx)
     potrf_body(I.Lm + I.L.corner(), (int64_t)I.L.ap, I.L.ap, nullptr, 0, f.ldp + 2 * I.L.nt, f.winfo, I.L.nb, smem);
 }
 
-__global__ void kb_factor_final(const BInst* bi, const int* err) {
-    if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(64) void kb_factor_final(const BInst* bi, const int* err) {
     const BInst& I = bi[blockIdx.x];
     const FactorWs f = factor_ws(I.L, I.ws);
     factor_final_body(f.ldp, I.nparts, f.winfo, err, I.logdet, I.info);
@@ -1918,18 +1542,14 @@ static int64_t spin_limit_ticks(const DevInfo& di) {
     return (int64_t)(ms * (double)di.clock_khz);
 }
 
-// Tile columns per batched column launch: STILES_KB_COLS (1 .. KB_COL_MAX),
-// default 8.  Measured on 64 matrices at tile 64: batched factor 64.4 / 55.6 /
-// 52.1 / 49.9 / 49.1 ms at 1 / 2 / 4 / 8 / 16 columns per launch; served
-// capacity (three concurrent lanes) 130 / 131 / 131 / 120 jobs/s at 1 / 4 / 8
-// / 16, as a launch that holds every compute unit longer leaves the other
-// lanes less room.
-static int kb_cols_per_launch() {
+// Chunks (64 columns) per batched factor launch.  STILES_KB_COLS (1 .. 16)
+// sets it in tile columns of the batch's largest tile.
+static int kb_chunks_per_launch(int maxb) {
     if (const char* e = getenv("STILES_KB_COLS")) {
         const int v = atoi(e);
-        if (v >= 1 && v <= KB_COL_MAX) return v;
+        if (v >= 1 && v <= 16) return std::min(v * (maxb / FC), KB_COL_MAX);
     }
-    return 8;
+    return 32;
 }
 
 static int debug_withhold() {
@@ -1989,16 +1609,16 @@ struct BPlan {
     size_t table_f = 0;        // bytes of the factor's table area (at the start of the workspace)
     size_t table = 0;          // bytes of both table areas (the selected inverse's follows the factor's)
     size_t total = 0;
-    int64_t maxN = 0;
+    int64_t maxC = 0;          // most chunks of a matrix
 };
 // factor workspace (FactorWs): head (info, error words) + log det partials
 // (N + 2 pairs) + the 256 x 256 inverse of the blocked corner + the 16 x 16
-// diagonal-block inverses of every L_JJ + the per tile column counters.
+// diagonal-block inverses of every L_JJ + the flags of the persistent launch.
 static size_t fws_bytes(const stiles_layout& l) {
     const Lay L = to_dev(l);
     return WS_HEAD + sizeof(double) * (size_t)(2 * (l.nt + 2)) +
            sizeof(double) * (size_t)(256 * 256 + l.nt * (int64_t)l.tile * 16) +
-           sizeof(int) * (size_t)(l.nt * (int64_t)col_stride(L) + upd_ints(L) + l.nt + 1);
+           sizeof(int) * (size_t)fac_ints(L);
 }
 // selinv workspace (SelinvWs): head (info, ticket, error words), the Phase 1
 // tiles (inverted diagonal tiles, Lhat, corner inverse) in the tile layout,
@@ -2009,27 +1629,24 @@ static size_t sws_bytes(const stiles_layout& l) {
 static int batch_plan(const stiles_batch_item* items, int count, bool need_sigma, BPlan& pl) {
     pl.lay.resize(count);
     pl.off.resize(count);
-    int64_t sumN = 0;
+    int64_t sumC = 0;
     for (int k = 0; k < count; ++k) {
         const stiles_batch_item& it = items[k];
         if (make_layout(it.n, it.bandwidth, it.arrow, it.tile, &pl.lay[k])) return -1;
         if (it.reserved != 0 || !it.A || !it.L || !it.logdet || !it.info) return -1;
         if (need_sigma && (!it.Sigma || it.Sigma == it.L)) return -1;
         if (need_sigma && p2_total_tasks(to_dev(pl.lay[k])) > 0x7fffffff) return -1;
-        sumN += pl.lay[k].nt;
-        pl.maxN = std::max(pl.maxN, pl.lay[k].nt);
+        const int64_t nc = fac_chunks(to_dev(pl.lay[k]));
+        sumC += nc;
+        pl.maxC = std::max(pl.maxC, nc);
     }
     // segment tables of at most six per-matrix launches; ints: the corner
-    // list, the error word and a ticket per tile column, and the queue tables
-    // of the tile-column launches (off: at most tmax + 1 per column; order:
-    // sum of N)
-    int64_t tmax = 0;
-    for (int k = 0; k < count; ++k) {
-        const Lay L = to_dev(pl.lay[k]);
-        tmax = std::max<int64_t>(tmax, 1 + col_tr_blocks(L, 0) + col_up_blocks(L, 0));
-    }
+    // list, the error word, a ticket per factor launch (at most one per chunk
+    // and slice), and the queue tables (the order, then per chunk the prefix
+    // sums over the matrices that have it)
     const size_t nseg = 6 * ((size_t)count + 1);
-    const size_t nint = (size_t)count + 1 + (size_t)pl.maxN + (size_t)pl.maxN * (size_t)(tmax + 1) + (size_t)sumN;
+    const size_t slices = ((size_t)count + KB_SLICE - 1) / KB_SLICE;
+    const size_t nint = (size_t)count + 1 + (size_t)pl.maxC * slices + (size_t)count + (size_t)sumC + (size_t)pl.maxC;
     pl.table_f = align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg) + align256(sizeof(int) * nint);
     pl.table = pl.table_f + align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg);
     size_t o = pl.table;
@@ -2161,11 +1778,13 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
     hipStream_t st = S_(stream);
     Lay L = to_dev(lay);
     const FactorWs f = factor_ws(L, (char*)workspace);
-    const int cstride = col_stride(L);
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
+    const FacCtx x = fac_ctx(L, Lm, f.Yd, f.flags);
+    const int64_t ntask = fac_tasks(x);
+    if (ntask >= 0x7fffffff) return -3;
     Sched sc;
-    sc.ticket = nullptr;
+    sc.ticket = f.ticket;
     sc.err = f.err;
     sc.spin_limit = spin_limit_ticks(di);
     sc.withhold = debug_withhold();
@@ -2175,22 +1794,10 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
         HIPCHK(hipMemcpyAsync(Lm, A, sizeof(double) * (size_t)L.total, hipMemcpyDeviceToDevice, st));
         tm_end(tm, STILES_TK_OTHER, st);
     }
-    LAUNCH(STILES_TK_OTHER, k_set_int, dim3(1), dim3(64), 0, st, f.winfo, 0x7fffffff);
-    LAUNCH(STILES_TK_OTHER, k_set_int, dim3(1), dim3(64), 0, st, f.err, 0);
-    LAUNCH(STILES_TK_OTHER, k_zero_ints, dim3(grid_for(L.nt * (int64_t)cstride + upd_ints(L))), dim3(NT), 0, st,
-           f.cf, L.nt * (int64_t)cstride + upd_ints(L));
-    LAUNCH(STILES_TK_OTHER, k_factor_offsets, dim3((unsigned)((L.nt + NT) / NT)), dim3(NT), 0, st, L, f.off, f.ticket);
-    // One persistent launch: per tile column the POTRF of the diagonal tile,
-    // the panel TRSM below it and the trailing updates, pipelined on the
-    // 16-column panels, and the columns overlapped through the update
-    // counters (k_factor_all).
-    int64_t ntot = 0;
-    for (int64_t J = 0; J < L.nt; ++J) ntot += 1 + col_tr_blocks(L, J) + col_up_blocks(L, J);
-    if (ntot > 0x7fffffff) return -3;
-    sc.ticket = f.ticket;
-    LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(ntot, di.cus)), dim3(P3_NT), 0, st, Lm, L,
-           f.Yd, f.cf, f.upd, (const int*)f.off, sc, f.ldp, f.winfo);
-    LAUNCH(STILES_TK_OTHER, k_zero_upper, dim3((unsigned)(8 * L.nt)), dim3(NT), 0, st, Lm, L);
+    LAUNCH(STILES_TK_OTHER, k_factor_setup, dim3(grid_for(fac_ints(L))), dim3(NT), 0, st, L, f);
+    LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(1 + ntask, 2 * (int64_t)di.cus)), dim3(FAC_NT),
+           0, st, x, (int)ntask, sc, f.winfo);
+    LAUNCH(STILES_TK_OTHER, k_factor_tail, dim3((unsigned)(8 * L.nt)), dim3(NT), 0, st, Lm, L, f.ldp);
     rc = enqueue_corner(Lm, L, f, st);
     if (rc) return rc;
     LAUNCH(STILES_TK_OTHER, k_factor_final, dim3(1), dim3(64), 0, st, (const double*)f.ldp, factor_nparts(L),
@@ -2512,8 +2119,10 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     const size_t zu_at = t.begin;
     const int zu_grid = t.grid, zu_n = t.finish(segs);
     // ints: [0, count) corner list, [count] error word, then one ticket per
-    // tile column (zero as uploaded), then the queue tables
-    std::vector<int> ints((size_t)count + 1 + (size_t)pl.maxN, 0);
+    // factor launch (zero as uploaded), then the queue tables
+    const int slices = (count + KB_SLICE - 1) / KB_SLICE;
+    const size_t nticket = (size_t)pl.maxC * slices;
+    std::vector<int> ints((size_t)count + 1 + nticket, 0);
     int ncorner = 0, corner_smem = 0;
     for (int k = 0; k < count; ++k)
         if (bi[k].L.ap > 0 && bi[k].L.ap <= 256) {
@@ -2521,27 +2130,29 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
             corner_smem = std::max(corner_smem, (int)sizeof(double) * potrf_smem_doubles(bi[k].L.ap));
         }
     const size_t err_at = (size_t)count, tick_at = (size_t)count + 1;
-    struct ColQ { size_t off_at, order_at; int T, ntot; };
-    std::vector<ColQ> cq(pl.maxN);
-    std::vector<std::pair<int, int>> nt_k;
-    for (int64_t J = 0; J < pl.maxN; ++J) {
-        nt_k.clear();
-        for (int k = 0; k < count; ++k)
-            if (bi[k].L.nt > J) nt_k.push_back({1 + col_tr_blocks(bi[k].L, J) + col_up_blocks(bi[k].L, J), k});
-        std::stable_sort(nt_k.begin(), nt_k.end(), [](const std::pair<int, int>& x, const std::pair<int, int>& y) {
-            return x.first > y.first;
-        });
-        ColQ& q = cq[J];
-        q.T = nt_k.empty() ? 0 : nt_k.front().first;
-        q.off_at = ints.size();
-        int acc = 0;
-        for (int tt = 0; tt <= q.T; ++tt) {
-            ints.push_back(acc);
-            for (const auto& e : nt_k) acc += e.first > tt;
+    std::vector<FacCtx> fx(count);
+    for (int k = 0; k < count; ++k) fx[k] = fac_ctx(bi[k].L, nullptr, nullptr, nullptr);
+    const size_t order_at = ints.size();
+    std::vector<int> order(count);
+    for (int k = 0; k < count; ++k) order[k] = k;
+    std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return fx[p].nc > fx[q].nc; });
+    ints.insert(ints.end(), order.begin(), order.end());
+    std::vector<size_t> pre_at(pl.maxC);
+    std::vector<int> act(pl.maxC);
+    {
+        int n = count;
+        for (int64_t c = 0; c < pl.maxC; ++c) {
+            while (n > 0 && fx[order[n - 1]].nc <= c) --n;
+            act[c] = n;
+            pre_at[c] = ints.size();
+            int64_t acc = 0;
+            ints.push_back(0);
+            for (int m = 0; m < n; ++m) {
+                acc += fac_group(fx[order[m]], (int)c);
+                if (acc > 0x7fffffff / KB_COL_MAX) return -1;
+                ints.push_back((int)acc);
+            }
         }
-        q.ntot = acc;
-        q.order_at = ints.size();
-        for (const auto& e : nt_k) ints.push_back(e.second);
     }
     int rc = 0;
     if (mode & BATCH_UPLOAD) {
@@ -2554,46 +2165,50 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     int* dint = (int*)(ws + int0);
     const int64_t spin = spin_limit_ticks(di);
 
-    // the error word and the tile-column tickets start at zero on every run
-    LAUNCH(STILES_TK_OTHER, k_zero_ints, dim3(grid_for(1 + pl.maxN)), dim3(NT), 0, st, dint + err_at, 1 + pl.maxN);
+    // the error word and the launches' tickets start at zero on every run
+    LAUNCH(STILES_TK_OTHER, k_zero_ints, dim3(grid_for(1 + (int64_t)nticket)), dim3(NT), 0, st, dint + err_at,
+           1 + (int64_t)nticket);
     for (int k = 0; k < count; ++k) {
         if (bi[k].A == bi[k].Lm) continue;
         hipEvent_t tm = tm_begin(st);
         HIPCHK(hipMemcpyAsync(bi[k].Lm, bi[k].A, sizeof(double) * (size_t)bi[k].L.total, hipMemcpyDeviceToDevice, st));
         tm_end(tm, STILES_TK_OTHER, st);
     }
-    LAUNCH(STILES_TK_OTHER, kb_factor_setup, dim3(count), dim3(NT), 0, st, dbi);
+    LAUNCH(STILES_TK_OTHER, kb_factor_setup, dim3((unsigned)(8 * count)), dim3(NT), 0, st, dbi);
     int maxb = 0;
     for (int k = 0; k < count; ++k) maxb = std::max(maxb, bi[k].L.b);
-    const int cols = kb_cols_per_launch();
-    for (int64_t J0 = 0; J0 < pl.maxN; J0 += cols) {
-        BColArgs a;
-        memset(&a, 0, sizeof(a));
-        a.bi = dbi;
-        a.ints = dint;
-        a.ncol = (int)std::min<int64_t>(cols, pl.maxN - J0);
-        for (int c = 0; c < a.ncol; ++c) {
-            const ColQ& q = cq[J0 + c];
-            a.off_at[c] = (int)q.off_at;
-            a.order_at[c] = (int)q.order_at;
-            a.T[c] = q.T;
-            a.tb[c + 1] = a.tb[c] + q.ntot;
-        }
-        a.ticket = dint + tick_at + J0;
-        a.err = dint + err_at;
-        a.spin_limit = spin;
-        const int ntot = a.tb[a.ncol];
-        if (maxb <= 128) {
-            LAUNCH(STILES_TK_FACTOR, kb_column<P3_POOL_128>, dim3((unsigned)std::min(ntot, KB_COL_WG_PER_CU * di.cus)),
-                   dim3(P3_NT), 0, st, a, J0);
-        } else {
-            LAUNCH(STILES_TK_FACTOR, kb_column<P3_POOL>, dim3((unsigned)std::min(ntot, di.cus)), dim3(P3_NT), 0, st, a,
-                   J0);
+    const int cols = kb_chunks_per_launch(maxb);
+    int launch = 0;
+    for (int64_t c0 = 0; c0 < pl.maxC; c0 += cols) {
+        for (int m0 = 0; m0 < act[c0]; m0 += KB_SLICE) {
+            BFacArgs a;
+            memset(&a, 0, sizeof(a));
+            a.bi = dbi;
+            a.ints = dint;
+            a.order_at = (int)order_at;
+            a.m0 = m0;
+            a.m1 = std::min(m0 + KB_SLICE, act[c0]);
+            a.c0 = (int)c0;
+            a.ncol = (int)std::min<int64_t>(cols, pl.maxC - c0);
+            int64_t ntot = a.tb[0] = a.m1 - m0;
+            for (int g = 0; g < a.ncol; ++g) {
+                const int c = (int)c0 + g, me = std::min(a.m1, act[c]);
+                a.pre_at[g] = (int)pre_at[c];
+                a.act[g] = std::max(0, me - m0);
+                if (a.act[g] > 0) ntot += ints[pre_at[c] + me] - ints[pre_at[c] + m0];
+                a.tb[g + 1] = (int)ntot;
+            }
+            if (ntot > 0x7fffffff) return -1;
+            a.ticket = dint + tick_at + launch++;
+            a.err = dint + err_at;
+            a.spin_limit = spin;
+            LAUNCH(STILES_TK_FACTOR, kb_factor, dim3((unsigned)std::min<int64_t>(ntot, 2 * (int64_t)di.cus)), dim3(FAC_NT), 0,
+                   st, a);
         }
     }
     {
         const BArgs a{dbi, dseg + zu_at, zu_n, spin};
-        LAUNCH(STILES_TK_OTHER, kb_zero_upper, dim3((unsigned)zu_grid), dim3(NT), 0, st, a);
+        LAUNCH(STILES_TK_OTHER, kb_factor_tail, dim3((unsigned)zu_grid), dim3(NT), 0, st, a);
     }
     if (ncorner > 0) {
         LAUNCH(STILES_TK_POTRF, kb_corner, dim3((unsigned)ncorner), dim3(NT), corner_smem, st, dbi, (const int*)dint);
