@@ -48,13 +48,14 @@
 struct FacCtx {
     double* Lm;
     Lay L;
-    int c64;    // chunks per tile
+    int c64;    // chunks per tile (1 .. 4)
+    uint32_t dm, ds;   // c / c64 = (c * dm) >> ds: a division would cost hundreds of cycles on the chain
     int nc;     // chunks that hold real columns
     int wc;     // block half-bandwidth
     int w1;     // max(wc, 1): row length of fl
     int na;     // arrow row blocks
     double* Yd; // Y_p of every chunk, 4 x 256 doubles in operand order
-    int* po;    // [nc * 4]   panel p of chunk c is in memory
+    int* po;    // [nc * 4]   row tile t of chunk c's diagonal block and Y_t are in memory
     int* fl;    // [nc * w1]  block (i, k) final at fl[i * w1 + i - k - 1]: 4
     int* fa;    // [na * nc]  arrow block (r, k) final: 4
     int* hx;    // [nc * 2]   H0(i), H1(i) done
@@ -76,6 +77,8 @@ __host__ __device__ inline FacCtx fac_ctx(const Lay& L, double* Lm, double* Yd, 
     x.Lm = Lm;
     x.L = L;
     x.c64 = L.b / FC;
+    x.dm = x.c64 == 3 ? 0xAAAAAAABu : 1u;
+    x.ds = x.c64 == 3 ? 33 : (x.c64 == 4 ? 2 : x.c64 - 1);
     x.nc = fac_chunks(L);
     x.wc = fac_wc(L);
     x.w1 = x.wc > 1 ? x.wc : 1;
@@ -121,11 +124,16 @@ struct ChainSmem {
     double Y[2][4][16 * 17];   // Y_p of the chunk (by its parity), element (i, j) at j * 17 + i
     double Lt[2][6][256];      // tile (t, p), t > p, of the diagonal block in operand order (r * 64 + lane)
     double R[4][4][256];       // strip s, panel p of the block row below, in operand order
-    int yd[4];                 // chunks whose Y_p is there
-    int ld[4];                 // 4 c + panels of row t there
-    int rd[4];                 // 4 c + panels of strip s there
-    int di[4];                 // chunks whose diagonal row t was taken from R
-    int fin[4];                // chunks wavefront t is done with
+    double X[2][256];          // what tiles (3, 1) and (3, 2) of the diagonal block lose to R
+    int w[32];                 // progress words (CW_*)
+};
+enum {
+    CW_Y = 0,     // [4] chunks whose Y_p is there
+    CW_L = 4,     // [4] 4 c + panels of row t there
+    CW_R = 8,     // [4] 4 c + panels of strip s there
+    CW_D = 12,    // [4] chunks for which wavefront t has read R
+    CW_FIN = 16,  // [4] chunks wavefront t is done with
+    CW_X = 20     // [1] chunks whose X is there
 };
 struct TaskSmem {
     double st[FAC_STAGES][2][16 * 64];   // per stage: 16 columns of the column-side rows, then of the row-side rows
@@ -143,14 +151,16 @@ struct FacSmem {
 // ---------------------------------------------------------------------------
 // Addresses
 // ---------------------------------------------------------------------------
+// Tile of chunk c.
+__device__ inline int fac_tile(const FacCtx& x, int c) { return (int)(((uint64_t)(uint32_t)c * x.dm) >> x.ds); }
 // Block (i, c) of the band, leading dimension b.
 __device__ inline double* fac_band(const FacCtx& x, int i, int c) {
-    const int I = i / x.c64, J = c / x.c64;
+    const int I = fac_tile(x, i), J = fac_tile(x, c);
     return x.Lm + x.L.band(J, I - J) + (i - I * x.c64) * FC + (int64_t)(c - J * x.c64) * FC * x.L.b;
 }
 // Arrow block (r, c), leading dimension a_p.
 __device__ inline double* fac_arrow(const FacCtx& x, int r, int c) {
-    const int J = c / x.c64;
+    const int J = fac_tile(x, c);
     return x.Lm + x.L.arrow(J) + r * FC + (int64_t)(c - J * x.c64) * FC * x.L.ap;
 }
 // A block row: band row i, or arrow row block r.
@@ -167,6 +177,13 @@ __device__ inline int fac_valid(const FacCtx& x, FacRow w) {
 __device__ inline int* fac_flag(const FacCtx& x, FacRow w, int k) {
     return w.i >= 0 ? x.fl + (int64_t)w.i * x.w1 + (w.i - k - 1) : x.fa + (int64_t)(-1 - w.i) * x.nc + k;
 }
+
+// Words in LDS that other wavefronts write: volatile, and through the LDS
+// address space (a volatile access through a generic pointer stays a FLAT
+// instruction, which waits for every memory access in flight).
+typedef volatile __attribute__((address_space(3))) int lds_word_t;
+__device__ inline int fac_lds_get(const int* p) { return *(lds_word_t*)p; }
+__device__ inline void fac_lds_set(int* p, int v) { *(lds_word_t*)p = v; }
 
 __device__ inline void fac_bar() { asm volatile("s_barrier" ::: "memory"); }
 __device__ inline void fac_vm0() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -192,7 +209,8 @@ __device__ inline bool fac_wait1(const Sched& sc, const int* f, int target) {
         __builtin_amdgcn_s_sleep(1);
     }
 }
-// Panels of chunk c in memory (the leading ones), at least `need`; 0: stop.
+// Row tiles of chunk c's diagonal block in memory (the leading ones), at least
+// `need`; 0: stop.
 __device__ inline int fac_panels(const Sched& sc, const int* po, int need) {
     const int lane = threadIdx.x & 63;
     int64_t t0 = -1;
@@ -216,7 +234,7 @@ __device__ inline bool fac_agree(FacSmem& sm, bool ok) {
     if (!ok) sm.dead = 1;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     fac_bar();
-    return __builtin_amdgcn_readfirstlane(*(volatile int*)&sm.dead) == 0;
+    return __builtin_amdgcn_readfirstlane(fac_lds_get(&sm.dead)) == 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -356,7 +374,7 @@ __device__ inline bool fac_acc(const FacCtx& x, const Sched& sc, FacSmem& sm, db
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         fac_bar();
-        const int n = __builtin_amdgcn_readfirstlane(*(volatile int*)&sm.n);
+        const int n = __builtin_amdgcn_readfirstlane(fac_lds_get(&sm.n));
         if (n == 0) return false;
         const int total = 4 * n;
         auto issue = [&](int it) {
@@ -423,56 +441,57 @@ __device__ inline void fac_store(double* base, int ld, int v, const dbl4 (&z)[4]
         }
 }
 
-// Solve of a strip with the diagonal block of chunk c, o[p] = R_p^T =
-// Y_p Z_p^T, Z_t^T -= L_tp R_p^T, panel by panel as the chain announces them.
-// The strip never leaves the wavefront's registers.  R (may be nullptr): the
-// strip's block in memory.
-__device__ inline bool fac_solve(const FacCtx& x, const Sched& sc, int c, dbl4 (&z)[4], dbl4 (&o)[4], double* R, int ldr,
-                                 int v) {
+// Solve of a strip with the diagonal block of chunk c, row tile by row tile as
+// the chain announces them: Z_t^T -= sum_{p < t} L_tp R_p^T, o[t] = R_t^T =
+// Y_t Z_t^T.  The strip never leaves the wavefront's registers.
+__device__ inline bool fac_solve(const FacCtx& x, const Sched& sc, int c, dbl4 (&z)[4], dbl4 (&o)[4]) {
     const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
     const double* D = uniform_ptr(fac_band(x, c, c));
     const double* Y = uniform_ptr(x.Yd + (int64_t)c * 1024);
     const int b = fac_opaque(x.L.b);
     double yv[4][4], lv[4][4][4];
-    auto fetch = [&](int p) {
+    auto fetch = [&](int t) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) yv[p][r] = ld_coh_s(Y, (uint32_t)(p * 256 + r * 64 + lane));
-#pragma unroll
-        for (int t = p + 1; t < 4; ++t)
+        for (int p = 0; p < t; ++p)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                lv[p][t][r] = ld_coh_s(D, (uint32_t)((16 * t + li) + (16 * p + 4 * r + lk) * b));
+                lv[t][p][r] = ld_coh_s(D, (uint32_t)((16 * t + li) + (16 * p + 4 * r + lk) * b));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) yv[t][r] = ld_coh_s(Y, (uint32_t)(t * 256 + r * 64 + lane));
     };
-    auto step = [&](int p) {
-        o[p] = dbl4{0.0, 0.0, 0.0, 0.0};
+    auto step = [&](int t) {
+        dbl4 q = dbl4{0.0, 0.0, 0.0, 0.0}, e = q;   // two chains each
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(yv[p][r], z[p][r], o[p], 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int t = p + 1; t < 4; ++t)
-                z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-lv[p][t][r], o[p][r], z[t], 0, 0, 0);
+        for (int p = 0; p < t; ++p) {
+            z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-lv[t][p][0], o[p][0], z[t], 0, 0, 0);
+            q = __builtin_amdgcn_mfma_f64_16x16x4f64(-lv[t][p][1], o[p][1], q, 0, 0, 0);
+            z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-lv[t][p][2], o[p][2], z[t], 0, 0, 0);
+            q = __builtin_amdgcn_mfma_f64_16x16x4f64(-lv[t][p][3], o[p][3], q, 0, 0, 0);
+        }
+        if (t > 0) z[t] += q;
+        q = dbl4{0.0, 0.0, 0.0, 0.0};
+        e = __builtin_amdgcn_mfma_f64_16x16x4f64(yv[t][0], z[t][0], e, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(yv[t][1], z[t][1], q, 0, 0, 0);
+        e = __builtin_amdgcn_mfma_f64_16x16x4f64(yv[t][2], z[t][2], e, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(yv[t][3], z[t][3], q, 0, 0, 0);
+        o[t] = e + q;
     };
     const int* po = x.po + (int64_t)c * 4;
     int have = fac_panels(sc, po, 1);
     if (have == 0) return false;
-    if (have == 4) {   // late: everything at once
+    fetch(0);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) fetch(p);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) step(p);
-    } else {
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            if (have <= p) {
-                have = fac_panels(sc, po, p + 1);
-                if (have == 0) return false;
-            }
-            fetch(p);
-            step(p);
+    for (int t = 0; t < 4; ++t) {
+        // the next tile's operands on their way while this one is solved, if they are there
+        const bool ahead = have > t + 1;
+        if (t < 3 && ahead) fetch(t + 1);
+        step(t);
+        if (t < 3 && !ahead) {
+            have = fac_panels(sc, po, t + 2);
+            if (have == 0) return false;
+            fetch(t + 1);
         }
     }
-    if (R) fac_store(R, ldr, v, o, 4);
     return true;
 }
 
@@ -514,95 +533,110 @@ __device__ inline FacTask fac_pick(const FacCtx& x, int c, int u) {
 
 // Task u of group c; false when the kernel must stop.  ticket: the launch's
 // ticket (the test hook Sched::withhold names one whose signal is not sent).
+// The kinds share one copy of the sum and of the solve: with a copy for each,
+// the kernel's code would not fit the instruction cache.
 __device__ inline bool fac_task(const FacCtx& x, const Sched& sc, FacSmem& sm, int c, int u, int ticket) {
     const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = fac_lane();
     const FacTask k = fac_pick(x, c, u);
     const int b = x.L.b, ap = x.L.ap;
     const bool quiet = ticket == sc.withhold;
+    const bool hand = k.kind == FT_H0 || k.kind == FT_H1;
+    const int i = k.i;
+    // rows of the block, rows of its columns, the range of k, tiles per strip
+    FacRow w{i}, cr{c};
+    int k0, k1 = c, nt = 4, ld = b;
+    double* O;
+    if (k.kind == FT_G) {
+        k0 = i - x.wc;
+        O = fac_band(x, i, c);
+    } else if (k.kind == FT_ARROW) {
+        w.i = -1 - i;
+        k0 = c - x.wc;
+        O = fac_arrow(x, i, c);
+        ld = ap;
+    } else if (k.kind == FT_P) {
+        cr.i = k.j;
+        k0 = i - x.wc;
+        k1 = c + 1;
+        nt = i == k.j ? v + 1 : 4;
+        O = fac_band(x, i, k.j);
+    } else if (k.kind == FT_CORNER) {
+        w.i = -1 - i;
+        cr.i = -1 - k.j;
+        k0 = c & ~3;
+        k1 = c + 1;
+        const int n = fac_valid(x, cr) / 16;
+        nt = i == k.j ? imin_(v + 1, n) : n;
+        O = x.Lm + x.L.corner() + FC * i + (int64_t)FC * k.j * ap;
+        ld = ap;
+    } else {   // block (i, i - 2): what P(i, i - 2) left
+        k0 = x.wc >= 3 ? i - 3 : c;
+        O = fac_band(x, i, c);
+        if (x.wc >= 4 && i >= 4 && !sched_wait(sc, x.pp + i * (int64_t)4 + 2, 1, &sm.sh)) return false;
+    }
+    k0 = imax_(k0, 0);
+    const bool act = 16 * v < fac_valid(x, w);   // this wavefront's strip has rows
     dbl4 acc[4], z[4], o[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = z[t] = o[t] = dbl4{0.0, 0.0, 0.0, 0.0};
-    if (k.kind == FT_G || k.kind == FT_ARROW) {
-        const bool band = k.kind == FT_G;
-        const FacRow w{band ? k.i : -1 - k.i};
-        const bool act = 16 * v < fac_valid(x, w);
-        double* R = band ? fac_band(x, k.i, c) : fac_arrow(x, k.i, c);
-        const int ld = band ? b : ap;
-        if (act) fac_load(R, ld, v, z, 4);
-        if (!fac_acc(x, sc, sm, acc, w, FacRow{c}, imax_(0, (band ? k.i : c) - x.wc), c, 4, act)) return false;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) z[t] -= acc[t];
-        bool ok = true;
-        if (act) ok = fac_solve(x, sc, c, z, o, R, ld, v);
-        fac_vm0();
-        if (!fac_agree(sm, ok)) return false;
-        if (threadIdx.x == 0 && !quiet) fac_up(fac_flag(x, w, c), 4);
-        return true;
-    }
-    if (k.kind == FT_P) {
-        const int nt = k.i == k.j ? v + 1 : 4;
-        double* O = fac_band(x, k.i, k.j);
-        fac_load(O, b, v, z, nt);
-        if (!fac_acc(x, sc, sm, acc, FacRow{k.i}, FacRow{k.j}, imax_(0, k.i - x.wc), c + 1, nt, true)) return false;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) z[t] -= acc[t];
-        fac_store(O, b, v, z, nt);
-        fac_vm0();
-        fac_bar();
-        if (threadIdx.x == 0 && !quiet) fac_up(x.pp + k.i * (int64_t)4 + (k.i - k.j), 1);
-        return true;
-    }
-    if (k.kind == FT_CORNER) {
-        const FacRow w{-1 - k.i}, s{-1 - k.j};
-        const int vs = fac_valid(x, s);
-        const bool act = 16 * v < fac_valid(x, w);
-        const int nt = k.i == k.j ? imin_(v + 1, vs / 16) : vs / 16;
-        if (!fac_acc(x, sc, sm, acc, w, s, c & ~3, c + 1, nt, act)) return false;
-        int* cnt = x.cc + (k.i * (k.i + 1) / 2 + k.j);
-        if (!sched_wait(sc, cnt, c >> 2, &sm.sh)) return false;
-        double* O = x.Lm + x.L.corner() + FC * k.i + (int64_t)FC * k.j * ap;
-        if (act) {
-            fac_load(O, ap, v, z, nt);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) z[t] -= acc[t];
-            fac_store(O, ap, v, z, nt);
-        }
-        fac_vm0();
-        fac_bar();
-        if (threadIdx.x == 0 && !quiet) add_coh_i(cnt, 1);
-        return true;
-    }
-    // H0, H1: block (i, i - 2) and its solve, i = c + 2
-    const int i = k.i;
-    double* R = fac_band(x, i, c);
-    if (x.wc >= 4 && i >= 4 && !sched_wait(sc, x.pp + i * (int64_t)4 + 2, 1, &sm.sh)) return false;
-    fac_load(R, b, v, z, 4);
+    for (int t = 0; t < 4; ++t) acc[t] = z[t] = dbl4{0.0, 0.0, 0.0, 0.0};
+    if (act && k.kind != FT_CORNER) fac_load(O, ld, v, z, nt);
     if (k.kind == FT_H1) {   // H0 may replace the block from now on
         fac_vm0();
         fac_bar();
         if (threadIdx.x == 0) fac_up(x.pp + i * (int64_t)4 + 3, 1);
     }
-    if (x.wc >= 3 && i >= 3 && !fac_acc(x, sc, sm, acc, FacRow{i}, FacRow{c}, i - 3, c, 4, true)) return false;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        z[t] -= acc[t];
-        acc[t] = dbl4{0.0, 0.0, 0.0, 0.0};
+    if (!fac_acc(x, sc, sm, acc, w, cr, k0, k1, nt, act)) return false;
+    int* cnt = x.cc + (i * (i + 1) / 2 + k.j);
+    if (k.kind == FT_CORNER) {
+        if (!sched_wait(sc, cnt, c >> 2, &sm.sh)) return false;
+        if (act) fac_load(O, ld, v, z, nt);
     }
-    const bool ok = fac_solve(x, sc, c, z, o, nullptr, b, v);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z[t] -= acc[t];
+    if (k.kind == FT_P || k.kind == FT_CORNER) {
+        if (act) fac_store(O, ld, v, z, nt);
+        fac_vm0();
+        fac_bar();
+        if (threadIdx.x == 0 && !quiet) {
+            if (k.kind == FT_P) fac_up(x.pp + i * (int64_t)4 + (i - k.j), 1);
+            else add_coh_i(cnt, 1);
+        }
+        return true;
+    }
+    bool ok = true;
+    if (act) ok = fac_solve(x, sc, c, z, o);
+    if (!hand) {
+        if (act) fac_store(O, ld, v, o, 4);
+        fac_vm0();
+        if (!fac_agree(sm, ok)) return false;
+        if (threadIdx.x == 0 && !quiet) fac_up(fac_flag(x, w, c), 4);
+        return true;
+    }
     const bool part = x.wc >= 3 && i >= 3;   // P(i, i - 1) and P(i, i) exist
+    const int lane = fac_lane();
+    double* X = &sm.tk.st[0][0][0];
+    if (k.kind == FT_H1) {   // the strips exchanged through LDS
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) X[(v * 4 + p) * 256 + r * 64 + lane] = o[p][r];
+    }
+    if (!fac_agree(sm, ok)) return false;
+    SchedDeps d;
+    d.n = 0;
+    if (part) deps_add(d, x.pp + i * (int64_t)4 + (k.kind == FT_H0 ? 1 : 0), 1);
+    if (k.kind == FT_H0) {
+        deps_add(d, x.pp + i * (int64_t)4 + 3, 1);
+        deps_add(d, fac_flag(x, FacRow{i - 1}, c), 4);
+    }
+    if (!sched_wait_deps(sc, d, &sm.sh)) return false;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = dbl4{0.0, 0.0, 0.0, 0.0};
     if (k.kind == FT_H0) {
         // block (i, i - 1) -= R (i - 1, i - 2)^T
-        if (!fac_agree(sm, ok)) return false;
-        SchedDeps d;
-        d.n = 0;
-        deps_add(d, fac_flag(x, FacRow{i - 1}, c), 4);
-        deps_add(d, x.pp + i * (int64_t)4 + 3, 1);
-        if (part) deps_add(d, x.pp + i * (int64_t)4 + 1, 1);
-        if (!sched_wait_deps(sc, d, &sm.sh)) return false;
-        fac_store(R, b, v, o, 4);
+        fac_store(O, b, v, o, 4);
         const double* A = uniform_ptr(fac_band(x, i - 1, c));
-        double* O = fac_band(x, i, i - 1);
+        O = fac_band(x, i, i - 1);
         const int li = lane & 15, lk = lane >> 4;
         uint32_t oa[4];
 #pragma unroll
@@ -628,42 +662,32 @@ __device__ inline bool fac_task(const FacCtx& x, const Sched& sc, FacSmem& sm, i
                     acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, o[q][2 * h + 1], acc[t], 0, 0, 0);
             }
         }
+        nt = 4;
+    } else {
+        // block (i, i) -= R R^T
+        O = fac_band(x, i, i);
+        nt = v + 1;
+        fac_load(O, b, v, z, nt);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) z[t] -= acc[t];
-        fac_store(O, b, v, z, 4);
-        fac_vm0();
-        fac_bar();
-        if (threadIdx.x == 0 && !quiet) {
-            fac_up(x.hx + i * (int64_t)2, 1);
-            fac_up(fac_flag(x, FacRow{i}, c), 4);
-        }
-        return true;
+        for (int t = 0; t < 4; ++t)
+            if (t < nt) {
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(X[(t * 4 + p) * 256 + r * 64 + lane], o[p][r], acc[t], 0,
+                                                                      0, 0);
+            }
     }
-    // H1: block (i, i) -= R R^T, the strips exchanged through LDS
-    double* X = &sm.tk.st[0][0][0];
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) X[(v * 4 + p) * 256 + r * 64 + lane] = o[p][r];
-    if (!fac_agree(sm, ok)) return false;
-    if (part && !sched_wait(sc, x.pp + i * (int64_t)4, 1, &sm.sh)) return false;
-    double* O = fac_band(x, i, i);
-    fac_load(O, b, v, z, v + 1);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        if (t <= v) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(X[(t * 4 + p) * 256 + r * 64 + lane], o[p][r], acc[t], 0, 0, 0);
-        }
 #pragma unroll
     for (int t = 0; t < 4; ++t) z[t] -= acc[t];
-    fac_store(O, b, v, z, v + 1);
+    fac_store(O, b, v, z, nt);
     fac_vm0();
     fac_bar();
-    if (threadIdx.x == 0 && !quiet) fac_up(x.hx + i * (int64_t)2 + 1, 1);
+    if (threadIdx.x == 0 && !quiet) {
+        fac_up(x.hx + i * (int64_t)2 + (k.kind == FT_H1 ? 1 : 0), 1);
+        if (k.kind == FT_H0) fac_up(fac_flag(x, FacRow{i}, c), 4);
+    }
     return true;
 }
 
@@ -677,14 +701,26 @@ __device__ inline bool fac_task(const FacCtx& x, const Sched& sc, FacSmem& sm, i
 // solved one tile with it.  The wavefronts meet through progress words in LDS
 // rather than barriers, so a wavefront that is still busy with its strip does
 // not hold up the others.
+//
+// What bounds it, in cycles at w 1,024 (29,400 per chunk): four pivots of
+// 3,000 with a hand-over of about 1,500 between them, then the way of block
+// row c + 1 out to H0(c + 2) and back (store, flag, poll, load: some 7,000).
+// Eight wavefronts with 128 registers, four on the pivots and four on the
+// strips, were slower (narrow 5.0 against 4.5 ms, w 1,024 21.9 against 19.0):
+// the polls share LDS with the pivots.  Whole factors before and after the
+// chain left barriers: nb 31,987 w 32 a 57 6.8 -> 4.5 ms, nb 100,000 w 1,024
+// 26.9 -> 19.0 ms.
 
-__device__ inline bool ch_wait(const Sched& sc, FacSmem& sm, const int* f, int target) {
+// Wait until every progress word e in [lo, hi) is at least a, and those in
+// [lo2, hi2) at least b (one LDS read per poll).
+__device__ inline bool ch_wait(const Sched& sc, FacSmem& sm, int lo, int hi, int a, int lo2 = 0, int hi2 = 0, int b = 0) {
+    const int e = threadIdx.x & 31;
+    const int need = e >= lo && e < hi ? a : (e >= lo2 && e < hi2 ? b : -1);
     int64_t t0 = -1;
     for (unsigned n = 0;; ++n) {
-        const int v = __builtin_amdgcn_readfirstlane(*(volatile const int*)f);
-        if (v >= target) break;
+        if (__ballot(fac_lds_get(&sm.ch.w[e]) < need) == 0) break;
         if ((n & 255) == 255) {
-            if (__builtin_amdgcn_readfirstlane(*(volatile int*)&sm.dead) != 0) return false;
+            if (__builtin_amdgcn_readfirstlane(fac_lds_get(&sm.dead)) != 0) return false;
             if (__builtin_amdgcn_readfirstlane(ld_coh_i(sc.err)) != 0) return false;
             if (t0 < 0) t0 = wall_clock64();
             if (wall_clock64() - t0 > sc.spin_limit) {
@@ -696,10 +732,10 @@ __device__ inline bool ch_wait(const Sched& sc, FacSmem& sm, const int* f, int t
     asm volatile("" ::: "memory");
     return true;
 }
-__device__ inline void ch_set(int* f, int v) {
+__device__ inline void ch_set(FacSmem& sm, int e, int v) {
     // LDS operations of one wavefront complete in order
     asm volatile("" ::: "memory");
-    *(volatile int*)f = v;
+    fac_lds_set(&sm.ch.w[e], v);
     asm volatile("" ::: "memory");
 }
 // Y Z^T for one tile (two chains of two products)
@@ -714,173 +750,251 @@ __device__ inline dbl4 ch_solve(const double* Y, const dbl4& z, int li, int lk) 
     q = __builtin_amdgcn_mfma_f64_16x16x4f64(y[3], z[3], q, 0, 0, 0);
     return p + q;
 }
+// sum over the four panels of A_p B_p^T, both operands in LDS or registers
+template <class FA, class FB>
+__device__ inline dbl4 ch_dot(FA&& a, FB&& b) {
+    dbl4 e = dbl4{0.0, 0.0, 0.0, 0.0}, q = e;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        e = __builtin_amdgcn_mfma_f64_16x16x4f64(a(p, 0), b(p, 0), e, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(a(p, 1), b(p, 1), q, 0, 0, 0);
+        e = __builtin_amdgcn_mfma_f64_16x16x4f64(a(p, 2), b(p, 2), e, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(a(p, 3), b(p, 3), q, 0, 0, 0);
+    }
+    return e + q;
+}
 #define CH_TILE(t, p) ((t) * ((t)-1) / 2 + (p))
 
-template <int S>
+// Row S of a diagonal block D: tiles t < S into z, the diagonal tile into zd,
+// symmetric from its lower triangle.
+__device__ inline void ch_load_row(const double* D, int b, int S, dbl4 (&z)[3], dbl4& zd) {
+    const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
+    D = uniform_ptr(D);
+    b = fac_opaque(b);
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+        if (t < S) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[t][r] = ld_coh_s(D, (uint32_t)((16 * S + li) + (16 * t + 4 * r + lk) * b));
+        }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = imax_(li, 4 * r + lk), j = imin_(li, 4 * r + lk);
+        zd[r] = ld_coh_s(D, (uint32_t)((16 * S + i) + (16 * S + j) * b));
+    }
+}
+// One 16 x 16 tile (row tile i, column tile j) of the block at B to memory.
+__device__ inline void ch_store(double* B, int b, int i, int j, const dbl4& v, int li, int lk) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) st_coh_s(B, (uint32_t)((16 * i + li) + (16 * j + 4 * r + lk) * b), v[r]);
+}
+__device__ inline void ch_put(double* X, const dbl4& v, int lane) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) X[r * 64 + lane] = v[r];
+}
+__device__ inline dbl4 ch_get(const double* X, int lane) {
+    dbl4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = X[r * 64 + lane];
+    return v;
+}
+// c += a b^T, the tiles in operand order
+__device__ inline void ch_mma(dbl4& c, const dbl4& a, const dbl4& b) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b[r], c, 0, 0, 0);
+}
+
+// One wavefront of the chain (S = its number).  The code is the same for all
+// four, with S a run-time value, so that the chain's loop stays in the
+// instruction cache: the tiles of a row are shifted down as they are used.
 __device__ inline bool fac_chain_wave(const FacCtx& x, const Sched& sc, FacSmem& fs, int c0, int c1, int* info,
                                       bool quiet) {
     ChainSmem& sm = fs.ch;
+    const int S = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = fac_lane(), li = lane & 15, lk = lane >> 4;
     const int b0 = x.L.b;
     dbl4 o[4];        // strip S of the block row below the previous chunk
-    int* pend = nullptr;
+    dbl4 z[3], zd;    // row S of the diagonal block: the tiles left of its own, its own
+    dbl4 dd = dbl4{0.0, 0.0, 0.0, 0.0};   // what its own loses to the strip
+    dbl4 y[4];        // strip S of the block row below this chunk
+    int* pend_po = nullptr;   // flag to raise once this wavefront's stores are in memory
+    bool have_z = false;
     if (c0 > 0 && x.wc >= 1) {   // a later launch of the same factor: that block row from memory
         fac_load(fac_band(x, c0, c0 - 1), b0, S, o, 4);
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sm.R[S][p][r * 64 + lane] = o[p][r];
-        ch_set(&sm.rd[S], 4 * c0);
+        for (int p = 0; p < 4; ++p) {
+            ch_put(sm.R[S][p], o[p], lane);
+            ch_mma(dd, o[p], o[p]);
+        }
+        ch_set(fs, CW_R + S, 4 * c0);
     }
     for (int c = c0; c < c1; ++c) {
         if (x.wc == 0 && c > c0 + 1) {   // nothing else keeps the wavefronts within two chunks
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (!ch_wait(sc, fs, &sm.fin[t], c - 1)) return false;
+            if (!ch_wait(sc, fs, CW_FIN, CW_FIN + 4, c - 1)) return false;
         }
         const int b = fac_opaque(b0);
         double(&Yc)[4][16 * 17] = sm.Y[c & 1];
         double(&Lc)[6][256] = sm.Lt[c & 1];
         double* D = (double*)uniform_ptr(fac_band(x, c, c));
+        const bool above = c > 0 && x.wc >= 1;        // there is a block row R of the chunk before
+        const bool below = x.wc >= 1 && c + 1 < x.nc;
+        const bool taken = x.wc >= 2 && c >= 1;       // block (c + 1, c) comes from H0(c + 1)
+        double* Rb = below ? (double*)uniform_ptr(fac_band(x, c + 1, c)) : nullptr;
+        const int* hx = x.hx + (c + 1) * (int64_t)2;
         // row S of the diagonal block, up to date with every chunk before c
-        if (x.wc >= 2 && c >= 2 && !fac_wait1(sc, x.hx + c * (int64_t)2 + 1, 1)) return false;
-        dbl4 z[S + 1];
-#pragma unroll
-        for (int t = 0; t < S; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) z[t][r] = ld_coh_s(D, (uint32_t)((16 * S + li) + (16 * t + 4 * r + lk) * b));
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {   // symmetric from the lower triangle
-            const int i = imax_(li, 4 * r + lk), j = imin_(li, 4 * r + lk);
-            z[S][r] = ld_coh_s(D, (uint32_t)((16 * S + i) + (16 * S + j) * b));
+        if (!have_z) {
+            if (x.wc >= 2 && c >= 2 && !fac_wait1(sc, x.hx + c * (int64_t)2 + 1, 1)) return false;
+            ch_load_row(D, b, S, z, zd);
         }
-        if (c > 0 && x.wc >= 1) {
-            dbl4 acc[S + 1];
+        have_z = false;
+        zd -= dd;
+        if (above) {
 #pragma unroll
-            for (int t = 0; t <= S; ++t) {
-                acc[t] = dbl4{0.0, 0.0, 0.0, 0.0};
-                if (t < S && !ch_wait(sc, fs, &sm.rd[t], 4 * c)) return false;
-                dbl4 a2 = acc[t];
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const double a = t == S ? o[p][r] : sm.R[t][p][r * 64 + lane];
-                        dbl4& q = (r & 1) ? a2 : acc[t];
-                        q = __builtin_amdgcn_mfma_f64_16x16x4f64(a, o[p][r], q, 0, 0, 0);
-                    }
-                acc[t] += a2;
+            for (int t = 0; t < 3; ++t) {
+                if (t >= S || (S == 3 && t > 0)) continue;   // tiles (3, 1) and (3, 2) by wavefront 0
+                if (!ch_wait(sc, fs, CW_R + t, CW_R + t + 1, 4 * c)) return false;
+                z[t] -= ch_dot([&](int p, int r) { return sm.R[t][p][r * 64 + lane]; }, [&](int p, int r) { return o[p][r]; });
             }
-#pragma unroll
-            for (int t = 0; t <= S; ++t) z[t] -= acc[t];
         }
-        ch_set(&sm.di[S], c + 1);
-        if (S > 0 && pend) {   // the strip stored during the last chunk is in memory by now
+        if (S > 0) ch_set(fs, CW_D + S, c + 1);
+        if (S > 0 && pend_po) {   // what was stored during the last chunk
             fac_vm0();
-            if (lane == 0) add_coh_i(pend, 1);
-            pend = nullptr;
+            if (lane == 0 && !quiet) fac_up(pend_po, 1);
+            pend_po = nullptr;
         }
         // panels before this wavefront's own
-#pragma unroll
         for (int p = 0; p < S; ++p) {
-            if (!ch_wait(sc, fs, &sm.yd[p], c + 1)) return false;
-            const dbl4 l = ch_solve(Yc[p], z[p], li, lk);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) Lc[CH_TILE(S, p)][r * 64 + lane] = l[r];
-            ch_set(&sm.ld[S], 4 * c + p + 1);
-            dbl4 q = dbl4{0.0, 0.0, 0.0, 0.0};
-            z[S] = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[0], l[0], z[S], 0, 0, 0);
-            q = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[1], l[1], q, 0, 0, 0);
-            z[S] = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[2], l[2], z[S], 0, 0, 0);
-            q = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[3], l[3], q, 0, 0, 0);
-            z[S] += q;
-#pragma unroll
-            for (int t = p + 1; t < S; ++t) {
-                if (!ch_wait(sc, fs, &sm.ld[t], 4 * c + p + 1)) return false;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Lc[CH_TILE(t, p)][r * 64 + lane], -l[r], z[t], 0, 0, 0);
+            if (S == 3 && p > 0 && above) {
+                if (p == 1 && !ch_wait(sc, fs, CW_X, CW_X + 1, c + 1)) return false;
+                z[0] -= ch_get(sm.X[p - 1], lane);
             }
+            if (!ch_wait(sc, fs, CW_Y + p, CW_Y + p + 1, c + 1)) return false;
+            const dbl4 l = ch_solve(Yc[p], z[0], li, lk);
+            ch_put(Lc[CH_TILE(S, p)], l, lane);
+            ch_set(fs, CW_L + S, 4 * c + p + 1);
+            const dbl4 m = -l;
+            ch_mma(zd, m, l);
+            if (p + 1 < S) {
+                if (!ch_wait(sc, fs, CW_L + p + 1, CW_L + S, 4 * c + p + 1)) return false;
+                ch_mma(z[1], ch_get(Lc[CH_TILE(p + 1, p)], lane), m);
+                if (p + 2 < S) ch_mma(z[2], ch_get(Lc[CH_TILE(p + 2, p)], lane), m);
+            }
+            ch_store(D, b, S, p, l, li, lk);
+            z[0] = z[1];
+            z[1] = z[2];
         }
-        // its own
-        double ld4[4], yv[4];
-        int fail = -1;
-        f16_factor(z[S], ld4, yv, fail);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) Yc[S][li * 17 + 4 * q + lk] = yv[q];
-        ch_set(&sm.yd[S], c + 1);
-        if (fail >= 0 && lane == 0) atomicMin(info, c * FC + 16 * S + fail + 1);
-        // panel S to memory: L_SS, Y_S and the tiles below, then its flag
+        // its own; whether the block below is ready is asked before and looked at after
+        const int early = below && taken ? ld_coh_i(hx) : 1;
         {
+            double l[4], yv[4];
+            const int fail = f16_factor(zd, l, yv);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) Yc[S][li * 17 + 4 * q + lk] = yv[q];
+            ch_set(fs, CW_Y + S, c + 1);
+            if (S == 0 && pend_po) {   // wavefront 0's row of the last chunk (it does not wait for its stores before)
+                fac_vm0();
+                if (lane == 0 && !quiet) fac_up(pend_po, 1);
+            }
+            ch_store(D, b, S, S, dbl4{l[0], l[1], l[2], l[3]}, li, lk);
+            if (fail >= 0 && lane == 0)
+                __hip_atomic_fetch_min((GLOBAL_AS int*)info, c * FC + 16 * S + fail + 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
             double* Yg = (double*)uniform_ptr(x.Yd + (int64_t)c * 1024 + S * 256);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) st_coh_s(D, (uint32_t)((16 * S + li) + (16 * S + 4 * q + lk) * b), ld4[q]);
-#pragma unroll
             for (int r = 0; r < 4; ++r) st_coh_s(Yg, (uint32_t)(r * 64 + lane), Yc[S][(4 * r + lk) * 17 + li]);
-#pragma unroll
-            for (int t = S + 1; t < 4; ++t) {
-                if (!ch_wait(sc, fs, &sm.ld[t], 4 * c + S + 1)) return false;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    st_coh_s(D, (uint32_t)((16 * t + li) + (16 * S + 4 * r + lk) * b), Lc[CH_TILE(t, S)][r * 64 + lane]);
+        }
+        const bool ready = __builtin_amdgcn_readfirstlane(early) != 0;
+        if (below && ready) fac_load(Rb, b, S, y, 4);
+        if (S == 0) {
+            if (above) {   // for wavefront 3, which has the longest row
+                if (!ch_wait(sc, fs, CW_R + 1, CW_R + 4, 4 * c)) return false;
+#pragma unroll 1
+                for (int t = 1; t < 3; ++t) {
+                    const dbl4 d = ch_dot([&](int p, int r) { return sm.R[t][p][r * 64 + lane]; },
+                                          [&](int p, int r) { return sm.R[3][p][r * 64 + lane]; });
+                    ch_put(sm.X[t - 1], d, lane);
+                }
+                ch_set(fs, CW_X, c + 1);
             }
+            ch_set(fs, CW_D + S, c + 1);
+        }
+        pend_po = x.po + c * (int64_t)4 + S;
+        if (x.wc >= 2) {   // the tasks that the chain waits for need the row soon
             fac_vm0();
-            if (lane == 0) {
-                if (!quiet) fac_up(x.po + c * (int64_t)4 + S, 1);
-                if (pend) add_coh_i(pend, 1);
-            }
-            pend = nullptr;
+            if (lane == 0 && !quiet) fac_up(pend_po, 1);
+            pend_po = nullptr;
         }
         // strip S of the block row below
-        if (x.wc >= 1 && c + 1 < x.nc) {
-            if (x.wc >= 2 && c >= 1 && !fac_wait1(sc, x.hx + (c + 1) * (int64_t)2, 1)) return false;
-            double* Rb = (double*)uniform_ptr(fac_band(x, c + 1, c));
-            dbl4 y[4];
-            fac_load(Rb, b, S, y, 4);
+        if (below) {
+            if (!ready) {
+                if (!fac_wait1(sc, hx, 1)) return false;
+                fac_load(Rb, b, S, y, 4);
+            }
+            // the next diagonal block's row, if it is there too
+            if (c + 1 < c1 && (x.wc < 2 || c + 1 < 2 || __builtin_amdgcn_readfirstlane(ld_coh_i(hx + 1)) != 0)) {
+                ch_load_row(fac_band(x, c + 1, c + 1), b, S, z, zd);
+                have_z = true;
+            }
+            dd = dbl4{0.0, 0.0, 0.0, 0.0};
+            auto panel = [&](int p) {
+                dbl4 lt[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t)   // the strips of the last chunk have been read
-                if (!ch_wait(sc, fs, &sm.di[t], c + 1)) return false;
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                if (!ch_wait(sc, fs, &sm.yd[p], c + 1)) return false;
+                for (int t = p + 1; t < 4; ++t) lt[t] = ch_get(Lc[CH_TILE(t, p)], lane);
                 o[p] = ch_solve(Yc[p], y[p], li, lk);
+                const dbl4 m = -o[p];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) sm.R[S][p][r * 64 + lane] = o[p][r];
-                ch_set(&sm.rd[S], 4 * c + p + 1);
+                for (int t = p + 1; t < 4; ++t) ch_mma(y[t], lt[t], m);
+                ch_mma(dd, o[p], o[p]);
+            };
+            if (__builtin_amdgcn_readfirstlane(fac_lds_get(&sm.w[CW_Y + 3])) >= c + 1) {
+                // the last panel is there, so everything is: no waits between
+                // the panels, the next one's operands on their way meanwhile
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    st_coh_s(Rb, (uint32_t)((16 * S + li) + (16 * p + 4 * r + lk) * b), o[p][r]);
+                for (int p = 0; p < 4; ++p) panel(p);
+            } else {
 #pragma unroll
-                for (int t = p + 1; t < 4; ++t) {
-                    if (!ch_wait(sc, fs, &sm.ld[t], 4 * c + p + 1)) return false;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        y[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Lc[CH_TILE(t, p)][r * 64 + lane], -o[p][r], y[t], 0, 0, 0);
+                for (int p = 0; p < 4; ++p) {
+                    // Y_p and the tiles below it
+                    if (!ch_wait(sc, fs, CW_Y + p, CW_Y + p + 1, c + 1, CW_L + p + 1, CW_L + 4, 4 * c + p + 1)) return false;
+                    panel(p);
                 }
             }
-            pend = fac_flag(x, FacRow{c + 1}, c);
+            // the last chunk's strips have been read by every wavefront
+            if (!ch_wait(sc, fs, CW_D, CW_D + 4, c + 1)) return false;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) ch_put(sm.R[S][p], o[p], lane);
+            ch_set(fs, CW_R + S, 4 * c + 4);
+            if (S > 0) {
+                // to memory, and wavefront 0's strip with wavefront 1's: that
+                // one's next panel is what everything waits for
+#pragma unroll
+                for (int p = 0; p < 4; ++p) ch_store(Rb, b, S, p, o[p], li, lk);
+                if (S == 1) {
+                    if (!ch_wait(sc, fs, CW_R, CW_R + 1, 4 * c + 4)) return false;
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) ch_store(Rb, b, 0, p, ch_get(sm.R[0][p], lane), li, lk);
+                }
+                fac_vm0();
+                if (lane == 0) {
+                    if (pend_po && !quiet) fac_up(pend_po, 1);
+                    add_coh_i(fac_flag(x, FacRow{c + 1}, c), S == 1 ? 2 : 1);
+                }
+                pend_po = nullptr;
+            }
         }
-        ch_set(&sm.fin[S], c + 1);
+        ch_set(fs, CW_FIN + S, c + 1);
     }
     fac_vm0();
-    if (pend && lane == 0) add_coh_i(pend, 1);
+    if (lane == 0 && pend_po && !quiet) fac_up(pend_po, 1);
     return true;
 }
 
 // Chunks c0 .. c1 - 1 of one matrix; false when the kernel must stop.
 __device__ inline bool fac_chain(const FacCtx& x, const Sched& sc, FacSmem& sm, int c0, int c1, int* info, bool quiet) {
-    const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     __syncthreads();
-    if (threadIdx.x < 4) {
-        sm.ch.yd[threadIdx.x] = sm.ch.ld[threadIdx.x] = sm.ch.rd[threadIdx.x] = 0;
-        sm.ch.di[threadIdx.x] = sm.ch.fin[threadIdx.x] = 0;
-    }
+    if (threadIdx.x < 32) sm.ch.w[threadIdx.x] = 0;
     __syncthreads();
-    bool ok;
-    if (v == 0) ok = fac_chain_wave<0>(x, sc, sm, c0, c1, info, quiet);
-    else if (v == 1) ok = fac_chain_wave<1>(x, sc, sm, c0, c1, info, quiet);
-    else if (v == 2) ok = fac_chain_wave<2>(x, sc, sm, c0, c1, info, quiet);
-    else ok = fac_chain_wave<3>(x, sc, sm, c0, c1, info, quiet);
+    const bool ok = fac_chain_wave(x, sc, sm, c0, c1, info, quiet);
     fac_vm0();
     return fac_agree(sm, ok);
 }

@@ -1,135 +1,115 @@
-// Cholesky factor and inverse of one 16 x 16 block by one wavefront, the block
-// and both results in registers in the matrix cores' output layout (lane
-// (lk, li) = (lane / 16, lane % 16) holds row 4 r + lk, column li in element
-// r), so the block comes straight from the products that formed it and its
-// rank-4 updates run on the matrix cores.
+// Cholesky factor and inverse of one 16 x 16 block by one wavefront, four
+// columns (a group) at a time, the block in registers in the matrix cores'
+// output layout (lane (lk, li) = (lane / 16, lane % 16) holds row 4 r + lk,
+// column li in element r), so it comes straight from the products that formed
+// it.
 //
-// Four pivots at a time.  Element q of the layout holds rows 4q .. 4q + 3, one
-// per 16-lane row of the wavefront; those four rows are copied into every
-// 16-lane row (f16_rows), and the four pivots are eliminated among them with
-// each lane keeping its column: a multiplier is one DPP broadcast along the
-// lane row and a product, with no LDS and no exchange between lane rows.  The
-// rest of the block then takes one v_mfma_f64_16x16x4_f64, whose two operands
-// are the eliminated rows as they stand (by symmetry).  The inverse W of the
-// unit lower factor goes through the same row operations.
+// For group q the 4 x 4 block of rows and columns 4q .. 4q + 3 is read into
+// scalar registers and factored by every lane alike, L4; lane (k, 4 b + i)
+// keeps the entry (i, k) of Y4 = L4^{-1}, which is the operand of
+// v_mfma_f64_4x4x4_4b that makes the four rows of L^T out of the block's four
+// rows as they lie, and those rows are both operands of the
+// v_mfma_f64_16x16x4 that updates the rest.  The identity W goes through the
+// same row operations and comes out as Y = L^{-1}; its products run in the
+// shadow of the next group's scalar work.
 //
-// The chain per pivot is a broadcast, a reciprocal (hardware estimate and two
-// Newton steps), a product and an FMA.
+// What bounds it is the number of instructions (about 90 per group, four
+// cycles or more each) and the chain of 16 pivots: a reciprocal square root
+// (hardware estimate and one step of third order), a product and an FMA each.
+// Measured alone, one wavefront, L and Y: 3,010 cycles; one column per lane with
+// DPP broadcasts, no matrix cores, took 4,450 for L.
 #pragma once
 #include "common.hpp"
 
-// Value of lane K of this lane's 16-lane row (DPP row_newbcast:K).
-template <int K>
-__device__ __forceinline__ double f16_bcast(double v) {
-    return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xF, 0xF, true);
-}
-
-// g[k] = the value lane (k, li) holds, in every lane (.., li).
-__device__ __forceinline__ void f16_rows(double v, double (&g)[4]) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+// The value lane L holds, in a scalar register pair.
+__device__ __forceinline__ double f16_lane(double v, int L) {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
-    const u2 a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);   // rows 0 1 0 1 | 2 3 2 3
-    const u2 b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    const u2 a01 = __builtin_amdgcn_permlane16_swap(a.x, a.x, false, false);
-    const u2 b01 = __builtin_amdgcn_permlane16_swap(b.x, b.x, false, false);
-    const u2 a23 = __builtin_amdgcn_permlane16_swap(a.y, a.y, false, false);
-    const u2 b23 = __builtin_amdgcn_permlane16_swap(b.y, b.y, false, false);
-    g[0] = __builtin_bit_cast(double, ((uint64_t)b01.x << 32) | a01.x);
-    g[1] = __builtin_bit_cast(double, ((uint64_t)b01.y << 32) | a01.y);
-    g[2] = __builtin_bit_cast(double, ((uint64_t)b23.x << 32) | a23.x);
-    g[3] = __builtin_bit_cast(double, ((uint64_t)b23.y << 32) | a23.y);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, L), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), L);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// sqrt(x) and 1/sqrt(x) from the hardware reciprocal square root and two
-// Goldschmidt steps (a few ulp; the pivot decides nothing else).
-__device__ __forceinline__ void f16_sqrt_rsqrt(double x, double& s, double& r) {
-    const double r0 = __builtin_amdgcn_rsq(x);
-    double g = x * r0, h = 0.5 * r0;
-    double e = fma(-g, h, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    e = fma(-g, h, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    s = g;
-    r = 2.0 * h;
+// 1 / sqrt(x): hardware estimate r (relative error below 2^-20) and one step
+// of third order, r (1 + e / 2 + 3 e^2 / 8) with e = 1 - x r^2.
+__device__ __forceinline__ double f16_rsqrt(double x) {
+    const double r = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x, r * r, 1.0);
+    return fma(r * e, fma(0.375, e, 0.5), r);
 }
 
-__device__ __forceinline__ double f16_own(const double (&g)[4], int lk) {
-    const double a = lk & 1 ? g[1] : g[0], b = lk & 1 ? g[3] : g[2];
-    return lk & 2 ? b : a;
-}
-
-// Pivot 4 Q + K among the rows g (of the block) and w (of W).
-template <int Q, int K>
-__device__ __forceinline__ void f16_pivot(double (&g)[4], double (&w)[4], double (&d)[4], double (&rr)[4], int& fail) {
-    d[K] = f16_bcast<4 * Q + K>(g[K]);
-    double r = __builtin_amdgcn_rcp(d[K]);
-    double e = fma(-d[K], r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-d[K], r, 1.0);
-    r = fma(r, e, r);
-    rr[K] = r;
-    if (!(d[K] > 0.0) && fail < 0) fail = 4 * Q + K;
-    if constexpr (K < 1) {
-        const double f = f16_bcast<4 * Q + 1>(g[K]) * r;
-        g[1] = fma(-f, g[K], g[1]);
-        w[1] = fma(-f, w[K], w[1]);
-    }
-    if constexpr (K < 2) {
-        const double f = f16_bcast<4 * Q + 2>(g[K]) * r;
-        g[2] = fma(-f, g[K], g[2]);
-        w[2] = fma(-f, w[K], w[2]);
-    }
-    if constexpr (K < 3) {
-        const double f = f16_bcast<4 * Q + 3>(g[K]) * r;
-        g[3] = fma(-f, g[K], g[3]);
-        w[3] = fma(-f, w[K], w[3]);
-    }
-}
-
-// Rows 4 Q .. 4 Q + 3: t = U^T rows times their pivots, h = W's rows, dv the
-// pivots (each this lane's row 4 Q + lk), and the rank-4 update of the rest.
+// Group Q of the block S (both triangles of the part not yet factored): t =
+// L(li, 4 Q + lk) (meaningless above the diagonal), y4 as above, S updated.
+// fail: the first of the block's columns whose pivot is not
+// positive, if none was found before (-1).
+// pt, py4, py: those of the group before, whose products into W run here, behind
+// the reads of S (in front of them they would hold up the wavefront).
 template <int Q>
-__device__ __forceinline__ void f16_group(dbl4& S, dbl4& W, double (&t)[4], double (&h)[4], double (&dv)[4], int& fail,
-                                          int lk) {
-    double g[4], w[4], d[4], rr[4];
-    f16_rows(S[Q], g);
-    f16_rows(W[Q], w);
-    f16_pivot<Q, 0>(g, w, d, rr, fail);
-    f16_pivot<Q, 1>(g, w, d, rr, fail);
-    f16_pivot<Q, 2>(g, w, d, rr, fail);
-    f16_pivot<Q, 3>(g, w, d, rr, fail);
-    t[Q] = f16_own(g, lk);
-    dv[Q] = f16_own(d, lk);
-    h[Q] = f16_own(w, lk);
-    if constexpr (Q < 3) {
-        const double a = -(t[Q] * f16_own(rr, lk));
-        S = __builtin_amdgcn_mfma_f64_16x16x4f64(a, t[Q], S, 0, 0, 0);
-        W = __builtin_amdgcn_mfma_f64_16x16x4f64(a, h[Q], W, 0, 0, 0);
+__device__ __forceinline__ void f16_group(dbl4& S, dbl4& W, double& t, double& y4, double pt, double py4, double& py,
+                                          int& fail) {
+    // the lane opaque: what depends on it is formed here, not kept in
+    // registers (or scratch memory) across the caller's loop
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int li = lane & 15, lk = lane >> 4;
+    const double a00 = f16_lane(S[Q], 4 * Q), a10 = f16_lane(S[Q], 4 * Q + 1);
+    const double a20 = f16_lane(S[Q], 4 * Q + 2), a30 = f16_lane(S[Q], 4 * Q + 3);
+    double a11 = f16_lane(S[Q], 16 + 4 * Q + 1), a21 = f16_lane(S[Q], 16 + 4 * Q + 2);
+    double a31 = f16_lane(S[Q], 16 + 4 * Q + 3), a22 = f16_lane(S[Q], 32 + 4 * Q + 2);
+    double a32 = f16_lane(S[Q], 32 + 4 * Q + 3), a33 = f16_lane(S[Q], 48 + 4 * Q + 3);
+    if constexpr (Q > 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        py = __builtin_amdgcn_mfma_f64_4x4x4f64(py4, W[Q - 1], 0.0, 0, 0, 0);
+        W = __builtin_amdgcn_mfma_f64_16x16x4f64(-pt, py, W, 0, 0, 0);
     }
+    // column lk of Y4 in this lane: L4 y = e_lk
+    const double r0 = f16_rsqrt(a00);
+    const double l10 = a10 * r0, l20 = a20 * r0, l30 = a30 * r0;
+    a11 = fma(-l10, l10, a11);
+    const double r1 = f16_rsqrt(a11);
+    a21 = fma(-l20, l10, a21);
+    a31 = fma(-l30, l10, a31);
+    a22 = fma(-l20, l20, a22);
+    a32 = fma(-l30, l20, a32);
+    a33 = fma(-l30, l30, a33);
+    const double l21 = a21 * r1, l31 = a31 * r1;
+    a22 = fma(-l21, l21, a22);
+    const double r2 = f16_rsqrt(a22);
+    a32 = fma(-l31, l21, a32);
+    a33 = fma(-l31, l31, a33);
+    const double l32 = a32 * r2;
+    a33 = fma(-l32, l32, a33);
+    const double r3 = f16_rsqrt(a33);
+    double y0 = lk == 0 ? r0 : 0.0;
+    double y1 = fma(-l10, y0, lk == 1 ? 1.0 : 0.0) * r1;
+    double y2 = fma(-l21, y1, fma(-l20, y0, lk == 2 ? 1.0 : 0.0)) * r2;
+    double y3 = fma(-l32, y2, fma(-l31, y1, fma(-l30, y0, lk == 3 ? 1.0 : 0.0))) * r3;
+    asm volatile("" : "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3));   // selected, not branched around
+    y4 = li & 2 ? (li & 1 ? y3 : y2) : (li & 1 ? y1 : y0);
+    t = __builtin_amdgcn_mfma_f64_4x4x4f64(y4, S[Q], 0.0, 0, 0, 0);
+    if constexpr (Q < 3) S = __builtin_amdgcn_mfma_f64_16x16x4f64(-t, t, S, 0, 0, 0);
+    // the pivots are the same in every lane
+    int k = -1;
+    if (__ballot(!(a33 > 0.0))) k = 4 * Q + 3;
+    if (__ballot(!(a22 > 0.0))) k = 4 * Q + 2;
+    if (__ballot(!(a11 > 0.0))) k = 4 * Q + 1;
+    if (__ballot(!(a00 > 0.0))) k = 4 * Q;
+    fail = fail < 0 ? k : fail;
 }
 
-// S: the block, both triangles.  l[q] = L(li, 4 q + lk) (zero above the
-// diagonal), y[q] = Y(4 q + lk, li) with Y = L^{-1}.  fail (-1 on entry) gets
-// the first column whose pivot is not positive.
-__device__ __forceinline__ void f16_factor(dbl4 S, double (&l)[4], double (&y)[4], int& fail) {
-    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+// S: the block, both triangles.  l[q] = L(li, 4 q + lk) (meaningless above the
+// diagonal), y[q] = Y(4 q + lk, li) with Y = L^{-1}.  The first column whose
+// pivot is not positive, or -1.
+__device__ __forceinline__ int f16_factor(dbl4 S, double (&l)[4], double (&y)[4]) {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
     dbl4 W;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) W[r] = li == 4 * r + lk ? 1.0 : 0.0;
-    double t[4], h[4], dv[4];
-    f16_group<0>(S, W, t, h, dv, fail, lk);
-    f16_group<1>(S, W, t, h, dv, fail, lk);
-    f16_group<2>(S, W, t, h, dv, fail, lk);
-    f16_group<3>(S, W, t, h, dv, fail, lk);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        double s, r;
-        f16_sqrt_rsqrt(dv[q], s, r);
-        const int k = 4 * q + lk;
-        l[q] = li > k ? t[q] * r : (li == k ? s : 0.0);
-        y[q] = h[q] * r;
-    }
+    for (int r = 0; r < 4; ++r) W[r] = (lane & 15) == 4 * r + (lane >> 4) ? 1.0 : 0.0;
+    int fail = -1;
+    double g[4], none = 0.0;
+    f16_group<0>(S, W, l[0], g[0], 0.0, 0.0, none, fail);
+    f16_group<1>(S, W, l[1], g[1], l[0], g[0], y[0], fail);
+    f16_group<2>(S, W, l[2], g[2], l[1], g[1], y[1], fail);
+    f16_group<3>(S, W, l[3], g[3], l[2], g[2], y[2], fail);
+    y[3] = __builtin_amdgcn_mfma_f64_4x4x4f64(g[3], W[3], 0.0, 0, 0, 0);
+    return fail;
 }

@@ -1543,18 +1543,35 @@ static int64_t spin_limit_ticks(const DevInfo& di) {
 }
 
 // Chunks (64 columns) per batched factor launch.  STILES_KB_COLS (1 .. 16)
-// sets it in tile columns of the batch's largest tile.
-static int kb_chunks_per_launch(int maxb) {
+// sets it in tile columns of the batch's largest tile.  A launch's fixed cost
+// asks for long ones, the wait for its slowest matrix for short ones when
+// there are many: 64 matrices took 22.7 / 24.4 / 25.7 ms with 8 / 16 / 32
+// chunks, 8 matrices 16.1 / 11.2 / 10.6 ms with 4 / 16 / 32.
+static int kb_chunks_per_launch(int maxb, int count) {
     if (const char* e = getenv("STILES_KB_COLS")) {
         const int v = atoi(e);
         if (v >= 1 && v <= 16) return std::min(v * (maxb / FC), KB_COL_MAX);
     }
-    return 32;
+    return std::max(8, std::min(32, 512 / std::max(count, 1)));
 }
 
 static int debug_withhold() {
     if (const char* e = getenv("STILES_DEBUG_WITHHOLD")) return atoi(e);
     return -1;
+}
+
+// Workgroups of one matrix's factor: the chain and the tasks of FAC_AHEAD
+// chunks.  A workgroup that holds a ticket further ahead than its task can
+// start only polls, and the polls share the memory channels of the flags that
+// the chain itself waits for.  Measured with 24 and without a limit: 5.46 and
+// 5.55 ms at nb 30,011, w 501, tile 192; the same at w 1,024 and above, where
+// 24 chunks' tasks fill the chip anyway.  Below 16 some widths lose (w 2,001,
+// nb 100,000: 21.1 ms with 24, 24.6 with 8).
+#define FAC_AHEAD 24
+static int fac_grid(const FacCtx& x, int most) {
+    int g = 0;
+    for (int c = 0; c < std::min(4, x.nc); ++c) g = std::max(g, fac_group(x, c));
+    return std::min(most, 2 + FAC_AHEAD * g);
 }
 
 static int grid_for(int64_t work) {
@@ -1795,8 +1812,8 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
         tm_end(tm, STILES_TK_OTHER, st);
     }
     LAUNCH(STILES_TK_OTHER, k_factor_setup, dim3(grid_for(fac_ints(L))), dim3(NT), 0, st, L, f);
-    LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(1 + ntask, 2 * (int64_t)di.cus)), dim3(FAC_NT),
-           0, st, x, (int)ntask, sc, f.winfo);
+    LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(1 + ntask, fac_grid(x, 2 * di.cus))),
+           dim3(FAC_NT), 0, st, x, (int)ntask, sc, f.winfo);
     LAUNCH(STILES_TK_OTHER, k_factor_tail, dim3((unsigned)(8 * L.nt)), dim3(NT), 0, st, Lm, L, f.ldp);
     rc = enqueue_corner(Lm, L, f, st);
     if (rc) return rc;
@@ -2177,7 +2194,7 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     LAUNCH(STILES_TK_OTHER, kb_factor_setup, dim3((unsigned)(8 * count)), dim3(NT), 0, st, dbi);
     int maxb = 0;
     for (int k = 0; k < count; ++k) maxb = std::max(maxb, bi[k].L.b);
-    const int cols = kb_chunks_per_launch(maxb);
+    const int cols = kb_chunks_per_launch(maxb, count);
     int launch = 0;
     for (int64_t c0 = 0; c0 < pl.maxC; c0 += cols) {
         for (int m0 = 0; m0 < act[c0]; m0 += KB_SLICE) {
