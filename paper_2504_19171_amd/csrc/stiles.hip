@@ -20,6 +20,7 @@
 #include "persist.hpp"
 #include "wave_gemm.hpp"
 #include "factor.hpp"
+#include "phase2.hpp"
 
 #define NT 256
 #define WS_HEAD 256  // bytes reserved at the start of every workspace (info and scheduler words)
@@ -49,26 +50,12 @@ static int make_layout(int64_t n, int64_t bandwidth, int64_t arrow, int32_t tile
     return 0;
 }
 
-// Parts of the Phase 2 sums: two (measured: as fast as three at tile 256,
-// faster at 128 and, by a fifth in the batched form, at 64, where the extra
-// tasks of the three-part form cost more than the shorter chain saves).
-// STILES_P2_SPLIT=3 selects the three-part form (measurement and tests).
-static int p2_split_for(int tile) {
-    (void)tile;
-    if (const char* e = getenv("STILES_P2_SPLIT")) {
-        const int v = atoi(e);
-        if (v == 2 || v == 3) return v;
-    }
-    return 2;
-}
-
 static Lay to_dev(const stiles_layout& s) {
     Lay l;
     l.nb = s.nb; l.w = s.w; l.nt = s.nt;
     l.off_band = s.off_band; l.off_arrow = s.off_arrow; l.off_corner = s.off_corner;
     l.total = s.total_doubles;
     l.b = s.tile; l.bt = s.bt; l.ap = s.arrow_ld; l.a = (int)s.arrow;
-    l.p2s = p2_split_for(s.tile);
     return l;
 }
 
@@ -555,409 +542,13 @@ __global__ __launch_bounds__(NT) void k_lauum_all(const double* W, double* S, La
     lauum_body(W, S, L, xcd_block((int)blockIdx.x, (int)gridDim.x) + j0 * lauum_per(L), smem);
 }
 
-#define ARW (-1)   // "the arrow" in place of a band tile offset
-
-// ---------------------------------------------------------------------------
-// Phase 2 as one persistent kernel
-// ---------------------------------------------------------------------------
-// Tile column J needs the off-diagonal tiles S(J) x S(J) of Sigma, where
-// S(J) = band tiles J+1..J+s and the arrow.  Each output block is summed over
-// k in three parts, by how late its operands become final:
-//   k over the far tiles J+3..J+s and the arrow: final once the off-diagonal
-//     tiles of column J+2 are (two and a half columns ahead);
-//   k = J+2: final once column J+2 is done;
-//   k = J+1: final once column J+1's off-diagonal tiles (rows i far) or its
-//     diagonal tile (row J+1) are.
-// With two parts (Lay::p2s == 2) the k = J+2 term stays in the far parts:
-// EA and E1A sum over k = J+2.., EB and E1B have no tasks, EA(J) waits for
-// done(J+2) and E1A(J) for L1(J+1) and far(J+1), L and L1 read the partial of
-// EA and E1A, and the group order is [EA(G-1), L(G), L1(G), E1A(G-1), DA(G),
-// DB(G)].
-// Every task is a 32 x 32 block whose reduction is spread over the 4
-// wavefronts of a workgroup, so that the tasks on the dependency chain stay
-// short ("far rows" = tiles J+2..J+s and the arrow):
-//   EA : Sigma_{i,J}   = -sum_{k = J+3.., arrow} Sigma_{i,k} Lhat_{k,J}   i far
-//   EB : Sigma_{i,J}  -= Sigma_{i,J+2} Lhat_{J+2,J}                      i far
-//   L  : Sigma_{i,J}  -= Sigma_{i,J+1} Lhat_{J+1,J}                      i far
-//   E1A: Sigma_{J+1,J} = -sum_{k = J+3.., arrow} Sigma_{J+1,k} Lhat_{k,J}
-//   E1B: Sigma_{J+1,J} -= Sigma_{J+1,J+2} Lhat_{J+2,J}
-//   L1 : Sigma_{J+1,J} -= Sigma_{J+1,J+1} Lhat_{J+1,J}
-//   DA : Sigma_JJ = X_J^T X_J - sum_{i far} Lhat_{i,J}^T Sigma_{i,J}       (lower blocks)
-//   DB : Sigma_JJ -= Lhat_{J+1,J}^T Sigma_{J+1,J}, then mirrored           (lower blocks)
-// Dependencies (counters per kind and tile column; "offdiag(J)": L(J), L1(J)
-// done, or EA(J) for the last column; "far(J)": L(J) done, or EA(J) for the
-// last column; "done(J)": DB(J), or DA(J) for the last column):
-//   EA(J): offdiag(J+2);          EB(J): done(J+2), EA(J);
-//   E1A(J): far(J+1);             E1B(J): L1(J+1), E1A(J);
-//   L(J): offdiag(J+1), EB(J) (EA(J) when s < 2);
-//   L1(J): done(J+1), E1B(J) (E1A(J) when s < 2);
-//   DA(J): far(J);                DB(J): DA(J), L1(J).
-// Ticket order: groups G = N-1 .. 0, group G = [EA(G-1), L(G), E1B(G),
-// E1A(G-1), EB(G-1), L1(G), DA(G), DB(G)] (group N-1 also starts with
-// EA(N-1)); every task depends only on tasks of earlier groups or earlier in
-// its own group.  The order puts each task's ticket close to the time it
-// becomes ready, so few workgroups sit on a ticket that is still waiting (it
-// was the fastest of the orders timed).
-enum { P2_EA = 0, P2_EB, P2_E1A, P2_E1B, P2_L, P2_L1, P2_DA, P2_DB, P2_KINDS };
-
-struct P2 {
-    double* S;
-    const double* W;
-    Lay L;
-    int* cnt;        // [P2_KINDS * N] finished tasks per kind and tile column
-    int ntasks;
-    // groups are taken in the order G = N-1-q, q = 0, 1, ...; from q = q0 on,
-    // every group but the last (G = 0) holds g_tasks tasks, and group q0
-    // starts at ticket off_q0, so a ticket's group is found in closed form
-    int q0, off_q0, g_tasks;
-};
-
-struct P2Counts {
-    int n[P2_KINDS];
-};
-
-// Task counts of tile column J.  EA and E1A exist (possibly with an empty
-// reduction, writing zeros) wherever their rows do.
-__host__ __device__ inline P2Counts p2_counts(const Lay& L, int64_t J) {
-    P2Counts c;
-    const int s = L.s(J);
-    const int C32 = L.b / 32;
-    const int far = s > 1 ? s - 1 : 0;
-    const int nf32 = far * C32 + (L.ap + 31) / 32;
-    const bool three = L.p2s == 3;
-    c.n[P2_EA] = nf32 * C32;
-    c.n[P2_EB] = three && s >= 2 ? nf32 * C32 : 0;
-    c.n[P2_E1A] = s >= 1 ? C32 * C32 : 0;
-    c.n[P2_E1B] = three && s >= 2 ? C32 * C32 : 0;
-    c.n[P2_L] = s >= 1 ? nf32 * C32 : 0;
-    c.n[P2_L1] = s >= 1 ? C32 * C32 : 0;
-    c.n[P2_DA] = C32 * (C32 + 1) / 2;
-    c.n[P2_DB] = s >= 1 ? C32 * (C32 + 1) / 2 : 0;
-    return c;
+__global__ void k_selinv_setup(Lay L, int* cnt, int* ticket, int* err, int* info) {
+    p2_setup_body(L, cnt, ticket, err, info);
 }
-
-// Task count of one kind (a switch rather than indexing P2Counts::n with a
-// run-time kind, which would put the array in scratch memory).
-__host__ __device__ inline int p2_count(const Lay& L, int64_t J, int kind) {
-    const P2Counts c = p2_counts(L, J);
-    switch (kind) {
-        case P2_EA: return c.n[P2_EA];
-        case P2_EB: return c.n[P2_EB];
-        case P2_E1A: return c.n[P2_E1A];
-        case P2_E1B: return c.n[P2_E1B];
-        case P2_L: return c.n[P2_L];
-        case P2_L1: return c.n[P2_L1];
-        case P2_DA: return c.n[P2_DA];
-        default: return c.n[P2_DB];
-    }
-}
-
-// Slot i of group G: the kind and the tile column offset (0 or -1) of its
-// tasks (with two parts, EB and E1B come last and have no tasks).
-#define P2_SLOTS 8
-// (a switch, not tables: a table indexed at run time would live in scratch
-// memory)
-__host__ __device__ inline void p2_slot(const Lay& L, int i, int& kind, int& dj) {
-    if (L.p2s == 3) {
-        switch (i) {
-            case 0: kind = P2_EA; dj = -1; break;
-            case 1: kind = P2_L; dj = 0; break;
-            case 2: kind = P2_E1B; dj = 0; break;
-            case 3: kind = P2_E1A; dj = -1; break;
-            case 4: kind = P2_EB; dj = -1; break;
-            case 5: kind = P2_L1; dj = 0; break;
-            case 6: kind = P2_DA; dj = 0; break;
-            default: kind = P2_DB; dj = 0;
-        }
-    } else {
-        switch (i) {
-            case 0: kind = P2_EA; dj = -1; break;
-            case 1: kind = P2_L; dj = 0; break;
-            case 2: kind = P2_L1; dj = 0; break;
-            case 3: kind = P2_E1A; dj = -1; break;
-            case 4: kind = P2_DA; dj = 0; break;
-            case 5: kind = P2_DB; dj = 0; break;
-            case 6: kind = P2_EB; dj = -1; break;
-            default: kind = P2_E1B; dj = 0;
-        }
-    }
-}
-
-// Tasks in group G (see the ticket order above).
-__host__ __device__ inline int p2_group_tasks(const Lay& L, int64_t G) {
-    const P2Counts c = p2_counts(L, G);
-    int t = (G == L.nt - 1) ? c.n[P2_EA] : 0;
-    if (G >= 1) {
-        const P2Counts c1 = p2_counts(L, G - 1);
-        t += c1.n[P2_EA] + c1.n[P2_E1A] + c1.n[P2_EB];
-    }
-    return t + c.n[P2_E1B] + c.n[P2_L] + c.n[P2_L1] + c.n[P2_DA] + c.n[P2_DB];
-}
-
-__device__ inline void p2_setup_body(const P2& p, int* ticket, int* err) {
-    const Lay& L = p.L;
-    for (int64_t i = threadIdx.x; i < P2_KINDS * L.nt; i += blockDim.x) p.cnt[i] = 0;
-    if (threadIdx.x == 0) {
-        *ticket = 0;
-        *err = 0;
-    }
-}
-__global__ void k_p2_setup(P2 p, int* ticket, int* err) { p2_setup_body(p, ticket, err); }
-
-// Operand A = Sigma restricted to a block of rows and a tile of k:
-// rows = block rbl (of rb rows) of tile J+d (d >= 1) or of the arrow (ARW);
-// k = tile J+e (e >= 1) or the arrow.
-__device__ inline void p2_sigma_rows(const Lay& L, const double* S, int64_t J, int d, int rbl, int rb, int e,
-                                     const double*& a, int64_t& lda, int& ta, int& av) {
-    av = rb;
-    if (d != ARW && e != ARW) {
-        if (d > e) { a = S + L.band(J + e, d - e) + rbl * rb; lda = L.b; ta = 0; }
-        else if (d == e) { a = S + L.band(J + d, 0) + rbl * rb; lda = L.b; ta = 0; }
-        else { a = S + L.band(J + d, e - d) + (int64_t)rbl * rb * L.b; lda = L.b; ta = 1; }
-    } else if (d != ARW) {
-        a = S + L.arrow(J + d) + (int64_t)rbl * rb * L.ap; lda = L.ap; ta = 1;
-    } else {
-        av = imin_(rb, L.ap - rbl * rb);
-        lda = L.ap; ta = 0;
-        a = (e != ARW) ? S + L.arrow(J + e) + rbl * rb : S + L.corner() + rbl * rb;
-    }
-}
-
-// Row block rbg (of rb rows) among the far rows of S(J): tiles J+2..J+s, arrow.
-__device__ inline void p2_far_row(const Lay& L, int s, int rbg, int rb, int& d, int& rbl) {
-    const int per = L.b / rb;
-    const int far = s > 1 ? s - 1 : 0;
-    if (rbg < far * per) { d = 2 + rbg / per; rbl = rbg % per; }
-    else { d = ARW; rbl = rbg - far * per; }
-}
-
-// Every task of the given kind and tile column finished (nothing to wait for
-// past the last column).
-__device__ inline void p2_dep_all(const P2& p, SchedDeps& d, int kind, int64_t J) {
-    if (J < p.L.nt) deps_add(d, &p.cnt[kind * p.L.nt + J], p2_count(p.L, J, kind));
-}
-// done(J): all of column J final.
-__device__ inline void p2_dep_done(const P2& p, SchedDeps& d, int64_t J) {
-    if (J < p.L.nt) p2_dep_all(p, d, p.L.s(J) >= 1 ? P2_DB : P2_DA, J);
-}
-// far(J): the far rows of column J final.
-__device__ inline void p2_dep_far(const P2& p, SchedDeps& d, int64_t J) {
-    if (J < p.L.nt) p2_dep_all(p, d, p.L.s(J) >= 1 ? P2_L : P2_EA, J);
-}
-// offdiag(J): every off-diagonal tile of column J final.
-__device__ inline void p2_dep_offdiag(const P2& p, SchedDeps& d, int64_t J) {
-    if (J >= p.L.nt) return;
-    if (p.L.s(J) >= 1) {
-        p2_dep_all(p, d, P2_L, J);
-        p2_dep_all(p, d, P2_L1, J);
-    } else {
-        p2_dep_all(p, d, P2_EA, J);
-    }
-}
-
-// LDS of a Phase 2 workgroup: the wavefronts' staging areas, which
-// wave_reduce reuses for the partial blocks (the larger of the two), then the
-// reduced block.  Both kernels run two workgroups per CU.  The single-matrix
-// kernel stages 16-deep chunks; the batched one 8-deep chunks, which halve its
-// LDS (41 against 72 KB), so that the kernels of other serving lanes still
-// find room on a CU beside it.  (Three batched workgroups per CU, which the
-// 8-deep chunks allow, made a batched pass faster alone, 125 against 141 ms,
-// but filled every CU: concurrent serving lanes then lost capacity, and in the
-// 2,000-job served stream one batch's selected inverse hit the wait limit.)
-template <int KC>
-struct P2Cfg {
-    static constexpr int STAGE = WS<KC>::SMEM > WR_SMEM_DOUBLES ? WS<KC>::SMEM : WR_SMEM_DOUBLES;
-    static constexpr int SMEM = STAGE + 32 * WR_LD;
-    static constexpr int WG_PER_CU = 2;
-};
-#define P2_KC_SINGLE 16
-#define P2_KC_BATCHED 8
-
-// One Phase 2 task: a 32 x 32 output block, its reduction spread over the 4
-// wavefronts.
-template <int KC>
-__device__ __forceinline__ void p2_task_small(const P2& p, int kind, int64_t J, int u, bool mirror_da, double* smem,
-                                           double* red, int t) {
-    const Lay& L = p.L;
-    const int C32 = L.b / 32;
-    const int s = L.s(J);
-    const int far = s > 1 ? s - 1 : 0;
-    // the reduction: band tiles J+e0 .. J+e0+nband-1, then the arrow if karw
-    int e0, nband;
-    bool karw;
-    const int ef = L.p2s == 3 ? 3 : 2;   // first band tile of the far parts
-    switch (kind) {
-        case P2_EA: case P2_E1A: e0 = ef; nband = s >= ef ? s - ef + 1 : 0; karw = L.ap > 0; break;
-        case P2_EB: case P2_E1B: e0 = 2; nband = 1; karw = false; break;
-        case P2_DA: e0 = 2; nband = far; karw = L.ap > 0; break;
-        default: e0 = 1; nband = 1; karw = false;   // L, L1, DB
-    }
-    const int nseg = nband + (karw ? 1 : 0);
-    const int ktot = nband * L.b + (karw ? L.ap : 0);
-    // the output block
-    int d = 0, rbl = 0, rb = 0, cb = 0;
-    const bool rowtask = kind < P2_DA;
-    if (rowtask) {
-        if (kind == P2_EA || kind == P2_EB || kind == P2_L) p2_far_row(L, s, u / C32, 32, d, rbl);
-        else { d = 1; rbl = u / C32; }
-        cb = u % C32;
-    } else {
-        tri_decode(u, rb, cb);
-    }
-    const bool zero_base = kind == P2_EA || kind == P2_E1A;
-    double* O;
-    int64_t ldo;
-    int mv = 32;
-    if (rowtask) {
-        if (d != ARW) { O = p.S + L.band(J, d) + rbl * 32 + (int64_t)cb * 32 * L.b; ldo = L.b; }
-        else { O = p.S + L.arrow(J) + rbl * 32 + (int64_t)cb * 32 * L.ap; ldo = L.ap; mv = imin_(32, L.ap - rbl * 32); }
-    } else {
-        O = p.S + L.band(J, 0) + rb * 32 + (int64_t)cb * 32 * L.b;
-        ldo = L.b;
-    }
-    const bool diag = (kind >= P2_DA) && rb == cb;
-    // the partial already stored (EB, E1B, L, L1, DB) is final once the task
-    // runs: read it now so its round trip overlaps the products
-    // (unconditional loads from inside the block, the unused ones dropped
-    // when the partial is applied: a load under a branch would make the
-    // compiler wait for it before the products)
-    double ov[4] = {0.0, 0.0, 0.0, 0.0};
-    if (!zero_base) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = threadIdx.x + 256 * q, i = imin_(e & 31, mv - 1), j = e >> 5;
-            ov[q] = ld_coh(O + i + (int64_t)j * ldo);
-        }
-    }
-    dbl4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
-    wave_segs<KC>(acc, nseg, ktot, smem, [&](int q) {
-        const int e = (q < nband) ? e0 + q : ARW;
-        if (rowtask) {
-            const double* a; int64_t lda; int ta, av;
-            p2_sigma_rows(L, p.S, J, d, rbl, 32, e, a, lda, ta, av);
-            if (e != ARW)
-                return mkseg(a, lda, ta, p.W + L.band(J, e) + (int64_t)cb * 32 * L.b, L.b, 0, L.b, av, 1, 0);
-            return mkseg(a, lda, ta, p.W + L.arrow(J) + (int64_t)cb * 32 * L.ap, L.ap, 0, L.ap, av, 1, 0);
-        }
-        if (e != ARW)
-            return mkseg(p.W + L.band(J, e) + (int64_t)rb * 32 * L.b, L.b, 1,
-                         p.S + L.band(J, e) + (int64_t)cb * 32 * L.b, L.b, 0, L.b, 32, 0, 1);
-        return mkseg(p.W + L.arrow(J) + (int64_t)rb * 32 * L.ap, L.ap, 1,
-                     p.S + L.arrow(J) + (int64_t)cb * 32 * L.ap, L.ap, 0, L.ap, 32, 0, 1);
-    });
-    TRACE(t, 4, wall_clock64());
-    wave_reduce(acc, smem, red);
-    TRACE(t, 5, wall_clock64());
-    // out = base - red, base = the partial already stored (EB, E1B, L, L1,
-    // DB), Sigma_JJ's initial value X^T X (DA), or 0 (EA, E1A)
-    const bool mirror = (kind == P2_DB) || (kind == P2_DA && mirror_da);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = threadIdx.x + 256 * q, i = e & 31, j = e >> 5;
-        if (i >= mv || (diag && i < j)) continue;
-        red[j * WR_LD + i] = (zero_base ? 0.0 : ov[q]) - red[j * WR_LD + i];
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 1024; e += 256) {
-        const int i = e & 31, j = e >> 5;
-        if (i >= mv) continue;
-        if (diag && i < j) {
-            if (mirror) st_coh(O + i + (int64_t)j * ldo, red[i * WR_LD + j]);
-            continue;
-        }
-        const double v = red[j * WR_LD + i];
-        st_coh(O + i + (int64_t)j * ldo, v);
-        if (mirror && !diag) st_coh(p.S + L.band(J, 0) + (cb * 32 + j) + (int64_t)(rb * 32 + i) * L.b, v);
-    }
-    TRACE(t, 6, wall_clock64());
-}
-
-template <int KC>
-__device__ inline void p2_run(const P2& p, const Sched& sc, double* smem, int* sh) {
-    double* red = smem + P2Cfg<KC>::STAGE;
-    const Lay& L = p.L;
-    const int64_t N = L.nt;
-    for (;;) {
-        const int t = sched_next(sc, p.ntasks, &sh[0]);
-        if (t < 0) break;
-        TRACE(t, 0, wall_clock64());
-        // the group of ticket t: in closed form past group q0, else by
-        // walking the first q0 groups (arithmetic only, no memory reads)
-        int64_t q;
-        int base;
-        if (t >= p.off_q0) {
-            q = p.q0 + (t - p.off_q0) / p.g_tasks;
-            if (q > N - 1) q = N - 1;
-            base = p.off_q0 + (int)(q - p.q0) * p.g_tasks;
-        } else {
-            q = 0;
-            base = 0;
-            for (;;) {
-                const int n = p2_group_tasks(L, N - 1 - q);
-                if (t < base + n) break;
-                base += n;
-                ++q;
-            }
-        }
-        const int64_t G = N - 1 - q;       // group
-        int u = t - base;
-        // decode (kind, J, index) inside group G
-        int kind = -1;
-        int64_t J = G;
-        if (G == N - 1) {
-            const int n = p2_counts(L, G).n[P2_EA];
-            if (u < n) kind = P2_EA;
-            else u -= n;
-        }
-        for (int i = 0; kind < 0 && i < P2_SLOTS; ++i) {
-            int k, dj;
-            p2_slot(L, i, k, dj);
-            if (G + dj < 0) continue;
-            const int n = p2_count(L, G + dj, k);
-            if (u < n) { kind = k; J = G + dj; }
-            else u -= n;
-        }
-        int* my = &p.cnt[kind * N + J];
-
-        // dependencies, all polled together
-        SchedDeps dp;
-        dp.n = 0;
-        const bool three = L.p2s == 3;
-        const bool two = three && L.s(J) >= 2;   // EB / E1B hold the partial
-        switch (kind) {
-            case P2_EA:
-                if (three) p2_dep_offdiag(p, dp, J + 2);
-                else p2_dep_done(p, dp, J + 2);
-                break;
-            case P2_EB: p2_dep_done(p, dp, J + 2); p2_dep_all(p, dp, P2_EA, J); break;
-            case P2_E1A:
-                if (!three) p2_dep_all(p, dp, P2_L1, J + 1);
-                p2_dep_far(p, dp, J + 1);
-                break;
-            case P2_E1B: p2_dep_all(p, dp, P2_L1, J + 1); p2_dep_all(p, dp, P2_E1A, J); break;
-            case P2_L: p2_dep_offdiag(p, dp, J + 1); p2_dep_all(p, dp, two ? P2_EB : P2_EA, J); break;
-            case P2_L1: p2_dep_done(p, dp, J + 1); p2_dep_all(p, dp, two ? P2_E1B : P2_E1A, J); break;
-            case P2_DA: p2_dep_far(p, dp, J); break;
-            default: p2_dep_all(p, dp, P2_DA, J); p2_dep_all(p, dp, P2_L1, J);
-        }
-        if (!sched_wait_deps(sc, dp, &sh[1])) break;
-        TRACE(t, 1, wall_clock64());
-
-        p2_task_small<KC>(p, kind, J, u, L.s(J) == 0, smem, red, t);
-        sched_signal(sc, my, t);
-        TRACE(t, 2, wall_clock64());
-        TRACE(t, 3, (unsigned long long)kind | ((unsigned long long)J << 8) | ((unsigned long long)blockIdx.x << 40));
-        TRACE(t, 7, (unsigned long long)__smid());
-    }
-}
-__global__ __launch_bounds__(NT) void k_phase2(P2 p, Sched sc) {
-    __shared__ double smem[P2Cfg<P2_KC_SINGLE>::SMEM];
+__global__ __launch_bounds__(P2Cfg<8>::NTH, 2) void k_phase2(P2 p, Sched sc) {
+    __shared__ __attribute__((aligned(128))) double smem[P2Cfg<8>::SMEM];
     __shared__ int sh[2];
-    p2_run<P2_KC_SINGLE>(p, sc, smem, sh);
+    p2_run<8>(p, sc, smem, sh);
 }
 
 __global__ void k_selinv_final(const int* info_ws, const int* err, int* info) {
@@ -1028,7 +619,7 @@ __host__ __device__ inline SelinvWs selinv_ws(const Lay& L, char* ws) {
     return v;
 }
 
-__host__ __device__ inline P2 make_p2(double* S, const SelinvWs& v, const Lay& L, int ntasks) {
+__host__ __device__ inline P2 make_p2(double* S, const SelinvWs& v, const Lay& L, int ntasks, int64_t jf) {
     P2 p;
     p.S = S;
     p.W = v.W;
@@ -1036,11 +627,13 @@ __host__ __device__ inline P2 make_p2(double* S, const SelinvWs& v, const Lay& L
     p.cnt = v.flags;
     p.ntasks = ntasks;
     const int64_t N = L.nt;
-    const int64_t qr = L.bt > 1 ? L.bt : 1;
-    p.q0 = (int)(N - 1 < qr ? N - 1 : qr);
+    p.klast = imin_(L.b, (int)((L.b + L.w - L.bt * (int64_t)L.b + 31) / 32 * 32));
+    p.jf = (int)jf;
+    const int64_t qr = L.bt > 1 ? L.bt : 1, ql = imax64(N - 1 - jf, 0);
+    p.q0 = (int)(ql < qr ? ql : qr);
     p.off_q0 = 0;
-    for (int q = 0; q < p.q0; ++q) p.off_q0 += p2_group_tasks(L, N - 1 - q);
-    p.g_tasks = p.q0 < N - 1 ? p2_group_tasks(L, N - 1 - p.q0) : 1;
+    for (int q = 0; q < p.q0; ++q) p.off_q0 += p2_group_tasks(L, N - 1 - q, jf);
+    p.g_tasks = p2_group_tasks(L, N - 1 - p.q0, jf);
     return p;
 }
 
@@ -1180,12 +773,11 @@ __global__ __launch_bounds__(64) void kb_factor_final(const BInst* bi, const int
 }
 
 // Selinv set-up of every matrix (one workgroup per matrix): info word and the
-// Phase 2 ticket, error word, group offsets and counters.
+// Phase 2 ticket, error word and counters.
 __global__ __launch_bounds__(NT) void kb_selinv_setup(const BInst* bi) {
     const BInst& I = bi[blockIdx.x];
     const SelinvWs v = selinv_ws(I.L, I.ws);
-    if (threadIdx.x == 0) *v.winfo = 0;
-    p2_setup_body(make_p2(I.S, v, I.L, I.p2_tasks), v.ticket, v.err);
+    p2_setup_body(I.L, v.flags, v.ticket, v.err, v.winfo);
 }
 
 __global__ __launch_bounds__(NT) void kb_zero_unused(BArgs a) {
@@ -1214,8 +806,8 @@ __global__ __launch_bounds__(NT) void kb_lauum(BArgs a) {
 
 // Phase 2 of every matrix in one persistent launch: each matrix runs on its
 // own share of the workgroups, with its own tickets.
-__global__ __launch_bounds__(NT) void kb_phase2(BArgs a) {
-    __shared__ double smem[P2Cfg<P2_KC_BATCHED>::SMEM];
+__global__ __launch_bounds__(P2Cfg<4>::NTH, 2) void kb_phase2(BArgs a) {
+    __shared__ __attribute__((aligned(128))) double smem[P2Cfg<4>::SMEM];
     __shared__ int sh[2];
     BATCH_DECODE(a, I, bid, nblk);
     const SelinvWs v = selinv_ws(I.L, I.ws);
@@ -1224,7 +816,7 @@ __global__ __launch_bounds__(NT) void kb_phase2(BArgs a) {
     sc.err = v.err;
     sc.spin_limit = a.spin_limit;
     sc.withhold = -1;
-    p2_run<P2_KC_BATCHED>(make_p2(I.S, v, I.L, I.p2_tasks), sc, smem, sh);
+    p2_run<4>(make_p2(I.S, v, I.L, I.p2_tasks, 0), sc, smem, sh);
 }
 
 __global__ void kb_selinv_final(const BInst* bi) {
@@ -1613,7 +1205,7 @@ static int enqueue_corner(double* Lm, const Lay& L, const FactorWs& f, hipStream
 
 static int64_t p2_total_tasks(const Lay& L) {
     int64_t t = 0;
-    for (int64_t J = 0; J < L.nt; ++J) t += p2_group_tasks(L, J);
+    for (int64_t J = 0; J < L.nt; ++J) t += p2_group_tasks(L, J, 0);
     return t;
 }
 
@@ -1639,9 +1231,9 @@ static size_t fws_bytes(const stiles_layout& l) {
 }
 // selinv workspace (SelinvWs): head (info, ticket, error words), the Phase 1
 // tiles (inverted diagonal tiles, Lhat, corner inverse) in the tile layout,
-// then the Phase 2 ready counters (P2_KINDS N).
+// then the Phase 2 counters.
 static size_t sws_bytes(const stiles_layout& l) {
-    return WS_HEAD + sizeof(double) * (size_t)l.total_doubles + sizeof(int) * (size_t)(P2_KINDS * l.nt);
+    return WS_HEAD + sizeof(double) * (size_t)l.total_doubles + sizeof(int) * (size_t)((l.bt + 2) * l.nt);
 }
 static int batch_plan(const stiles_batch_item* items, int count, bool need_sigma, BPlan& pl) {
     pl.lay.resize(count);
@@ -1832,11 +1424,11 @@ static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, in
     const SelinvWs v = selinv_ws(L, (char*)workspace);
     const int nb64 = L.b / 64, nab = arrow_blocks(L.ap);
     int64_t ntasks = 0;
-    for (int64_t J = jf; J < L.nt; ++J) ntasks += p2_group_tasks(L, J);
+    for (int64_t J = jf; J < L.nt; ++J) ntasks += p2_group_tasks(L, J, jf);
     if (ntasks > 0x7fffffff) return -3;
-    const int64_t j1 = std::max<int64_t>(0, jf - 1);
+    const int64_t j1 = std::min<int64_t>(jf, L.nt - 1);
 
-    LAUNCH(STILES_TK_OTHER, k_set_int, dim3(1), dim3(64), 0, st, v.winfo, 0);
+    LAUNCH(STILES_TK_OTHER, k_selinv_setup, dim3(1), dim3(NT), 0, st, L, v.flags, v.ticket, v.err, v.winfo);
     if (L.bt > 0) {
         const int64_t tail = (int64_t)L.bt * (L.bt + 1) / 2 * L.b * L.b;
         LAUNCH(STILES_TK_OTHER, k_zero_unused, dim3(grid_for(tail)), dim3(NT), 0, st, S, L);
@@ -1857,16 +1449,15 @@ static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, in
     // Phase 2, bottom-right to top-left, one persistent launch
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
-    const P2 p = make_p2(S, v, L, (int)ntasks);
+    const P2 p = make_p2(S, v, L, (int)ntasks, jf);
     Sched sc;
     sc.ticket = v.ticket;
     sc.err = v.err;
     sc.spin_limit = spin_limit_ticks(di);
     sc.withhold = debug_withhold();
-    LAUNCH(STILES_TK_OTHER, k_p2_setup, dim3(1), dim3(NT), 0, st, p, sc.ticket, sc.err);
     if (ntasks > 0) {
-        const int grid = (int)std::min<int64_t>(ntasks, P2Cfg<P2_KC_SINGLE>::WG_PER_CU * (int64_t)di.cus);
-        LAUNCH(STILES_TK_PHASE2, k_phase2, dim3(grid), dim3(NT), 0, st, p, sc);
+        const int grid = (int)std::min<int64_t>(ntasks, P2Cfg<8>::WG_PER_CU * (int64_t)di.cus);
+        LAUNCH(STILES_TK_PHASE2, k_phase2, dim3(grid), dim3(P2Cfg<8>::NTH), 0, st, p, sc);
     }
     LAUNCH(STILES_TK_OTHER, k_selinv_final, dim3(1), dim3(64), 0, st, (const int*)v.winfo, (const int*)v.err,
            (int*)info);
@@ -2297,7 +1888,7 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     // counts, at least one per matrix
     t.start(segs.size());
     {
-        const int64_t total = std::min<int64_t>(sum_tasks, P2Cfg<P2_KC_BATCHED>::WG_PER_CU * (int64_t)di.cus);
+        const int64_t total = std::min<int64_t>(sum_tasks, P2Cfg<4>::WG_PER_CU * (int64_t)di.cus);
         for (int k = 0; k < count; ++k) {
             const int64_t want = total * bi[k].p2_tasks / std::max<int64_t>(1, sum_tasks);
             t.add(segs, k, (int)std::max<int64_t>(1, std::min<int64_t>(bi[k].p2_tasks, want)));
@@ -2319,7 +1910,7 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     LAUNCH(STILES_TK_PHASE1, kb_trtri, dim3((unsigned)tr.grid), dim3(NT), 0, st, args(tr));
     if (tm.grid > 0) LAUNCH(STILES_TK_PHASE1, kb_trmm, dim3((unsigned)tm.grid), dim3(NT), 0, st, args(tm));
     LAUNCH(STILES_TK_PHASE1, kb_lauum, dim3((unsigned)la.grid), dim3(NT), 0, st, args(la));
-    LAUNCH(STILES_TK_PHASE2, kb_phase2, dim3((unsigned)p2.grid), dim3(NT), 0, st, args(p2));
+    LAUNCH(STILES_TK_PHASE2, kb_phase2, dim3((unsigned)p2.grid), dim3(P2Cfg<4>::NTH), 0, st, args(p2));
     LAUNCH(STILES_TK_OTHER, kb_selinv_final, dim3(count), dim3(64), 0, st, dbi);
     return 0;
 }
