@@ -54,6 +54,7 @@ struct FacCtx {
     int wc;     // block half-bandwidth
     int w1;     // max(wc, 1): row length of fl
     int na;     // arrow row blocks
+    int col0;   // first column's number in the matrix
     double* Yd; // Y_p of every chunk, 4 x 256 doubles in operand order
     int* po;    // [nc * 4]   row tile t of chunk c's diagonal block and Y_t are in memory
     int* fl;    // [nc * w1]  block (i, k) final at fl[i * w1 + i - k - 1]: 4
@@ -83,6 +84,7 @@ __host__ __device__ inline FacCtx fac_ctx(const Lay& L, double* Lm, double* Yd, 
     x.wc = fac_wc(L);
     x.w1 = x.wc > 1 ? x.wc : 1;
     x.na = arrow_blocks(L.ap);
+    x.col0 = 0;
     x.Yd = Yd;
     x.po = flags;
     x.fl = x.po + x.nc * (int64_t)4;
@@ -897,7 +899,7 @@ __device__ inline bool fac_chain_wave(const FacCtx& x, const Sched& sc, FacSmem&
             }
             ch_store(D, b, S, S, dbl4{l[0], l[1], l[2], l[3]}, li, lk);
             if (fail >= 0 && lane == 0)
-                __hip_atomic_fetch_min((GLOBAL_AS int*)info, c * FC + 16 * S + fail + 1, __ATOMIC_RELAXED,
+                __hip_atomic_fetch_min((GLOBAL_AS int*)info, x.col0 + c * FC + 16 * S + fail + 1, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
             double* Yg = (double*)uniform_ptr(x.Yd + (int64_t)c * 1024 + S * 256);
 #pragma unroll

@@ -71,7 +71,7 @@ __global__ void k_set_int(int* p, int v) {
 
 // Pack the canonical band form into the tile layout (every double written).
 // Workgroup g < N (B+1) writes band tile g = J (B+1) + d, i.e. tile (J+d, J);
-// the next N write the arrow tiles J; the last one the corner.
+// the next N write the arrow tiles J; the rest the corner's 64 x 64 blocks.
 //
 // A band tile is written 32 columns at a time through LDS.  Column c of tile
 // (J+d, J) holds A[(J+d) b + r, J b + c]; in the band form that is
@@ -217,11 +217,20 @@ __global__ __launch_bounds__(NT) void k_pack(const double* __restrict__ ab, cons
             }
         }
     } else {
+        // the corner in 64 x 64 blocks through LDS (C by rows, the tile by
+        // columns); by one workgroup it took a corner of 413 rows 300 us
         double* O = T + L.corner();
-        const int ap = L.ap;
-        for (int e = tid; e < ap * ap; e += NT) {
-            const int r = e % ap, c = e / ap;
-            O[e] = (r < L.a && c < L.a) ? C[r * L.a + c] : (r == c ? 1.0 : 0.0);
+        const int ap = L.ap, nab = arrow_blocks(ap), q = (int)(g - nband - L.nt);
+        const int r0 = 64 * (q % nab), c0 = 64 * (q / nab);
+        for (int e = tid; e < 64 * 64; e += NT) {
+            const int r = e >> 6, c = e & 63;
+            blk[r * 65 + c] = r0 + r < L.a && c0 + c < L.a ? C[(int64_t)(r0 + r) * L.a + c0 + c]
+                                                           : (r0 + r == c0 + c ? 1.0 : 0.0);
+        }
+        __syncthreads();
+        for (int e = tid; e < 64 * 64; e += NT) {
+            const int r = e & 63, c = e >> 6;
+            if (r0 + r < ap && c0 + c < ap) O[r0 + r + (int64_t)(c0 + c) * ap] = blk[r * 65 + c];
         }
     }
 }
@@ -245,58 +254,6 @@ __global__ __launch_bounds__(NT) void k_zero_unused(double* T, Lay L) { zero_unu
 
 // ---------------------------------------------------------------------------
 // Factor kernels
-// ---------------------------------------------------------------------------
-
-// POTRF of one m x m diagonal block (m <= 256), optional TRTRI of the result
-// into X, log det partial into ldp[0..1], first failing column into *info
-// (atomicMin of the 1-based global column col_base + c + 1).
-__device__ __forceinline__ void potrf_body(double* M, int64_t ld, int m, double* X, int64_t ldx, double* ldp, int* info,
-                                  int64_t col_base, double* smem) {
-    // device memory (a batched caller reads these pointers from its table)
-    M = (double*)(GLOBAL_AS double*)M;
-    if (X) X = (double*)(GLOBAL_AS double*)X;
-    int fail;
-    double s, c;
-    potrf_tile(M, ld, m, smem, &fail, &s, &c);
-    if (threadIdx.x == 0) {
-        ldp[0] = s;
-        ldp[1] = c;
-        if (fail >= 0) atomicMin(info, (int)(col_base + fail + 1));
-    }
-    if (X) {
-        __syncthreads();
-        int bad;
-        trtri_tile(M, ld, X, ldx, m, smem, &bad);
-    }
-}
-__global__ __launch_bounds__(NT) void k_potrf(double* M, int64_t ld, int m, double* X, int64_t ldx,
-                                             double* ldp, int* info, int64_t col_base) {
-    extern __shared__ double smem[];
-    potrf_body(M, ld, m, X, ldx, ldp, info, col_base, smem);
-}
-
-// In place: columns are produced last block first, so every column block
-// read later is still unmodified (X^T is upper triangular).
-__device__ inline void trsm_rows(double* C, int64_t ld, int valid, const double* X, int64_t ldx,
-                                 int ncols, double* smem) {
-    for (int cb = ncols / 64 - 1; cb >= 0; --cb) {
-        GAcc g;
-        gacc_zero(g);
-        gemm_acc(g, opnd(C, ld, 0, valid), opnd(X + cb * 64, ldx, 1, 64), (cb + 1) * 64, smem);
-        gemm_store(g, smem, 1.0, 0.0, nullptr, 0, C + (int64_t)cb * 64 * ld, ld, valid, 64);
-    }
-}
-
-// Generic TRSM on a contiguous row panel (used for the blocked corner).
-__global__ __launch_bounds__(NT) void k_trsm_generic(double* C, int64_t ld, int rows, const double* X,
-                                                    int64_t ldx, int ncols) {
-    __shared__ double smem[GB_SMEM_DOUBLES];
-    const int rb = blockIdx.x;
-    trsm_rows(C + rb * 64, ld, imin_(64, rows - rb * 64), X, ldx, ncols, smem);
-}
-
-// ---------------------------------------------------------------------------
-// Factor kernels of the band tile columns
 // ---------------------------------------------------------------------------
 
 // Compensated sum over a wavefront of the pairs (s, c) of its lanes, joined
@@ -337,8 +294,79 @@ __device__ inline void factor_tail_body(double* Lm, const Lay& L, int bid, doubl
         }
     }
 }
-__global__ __launch_bounds__(NT) void k_factor_tail(double* Lm, Lay L, double* ldp) {
-    factor_tail_body(Lm, L, blockIdx.x, ldp);
+
+// The corner is factored by the same persistent kernel, as a dense matrix of 64
+// x 64 tiles in the workspace (its own layout: a_p rows rounded up to 64, the
+// rest the identity).  a_p <= 512, so the copies there and back are 2 MB at
+// most.  (One workgroup on the corner in place took 49 / 220 / 640 us at a_p =
+// 64 / 208 / 416.)
+__host__ __device__ inline Lay corner_lay(const Lay& L) {
+    Lay c;
+    const int nab = arrow_blocks(L.ap);
+    c.nb = 64 * nab;
+    c.w = nab > 0 ? c.nb - 1 : 0;
+    c.nt = nab;
+    c.b = 64;
+    c.bt = nab > 0 ? nab - 1 : 0;
+    c.ap = c.a = 0;
+    c.off_band = 0;
+    c.off_arrow = c.off_corner = c.total = (int64_t)nab * nab * 64 * 64;
+    return c;
+}
+// Workgroups that copy the corner there (its lower 64 x 64 blocks) and back
+// (all blocks, and one for the log det).
+__host__ __device__ inline int corner_in_blocks(const Lay& L) {
+    const int nab = arrow_blocks(L.ap);
+    return nab * (nab + 1) / 2;
+}
+__host__ __device__ inline int corner_out_blocks(const Lay& L) {
+    const int nab = arrow_blocks(L.ap);
+    return nab > 0 ? nab * nab + 1 : 0;
+}
+__device__ inline void corner_in_body(const double* Lm, const Lay& L, int bid, double* T) {
+    const Lay K = corner_lay(L);
+    int r, c;
+    tri_decode(bid, r, c);
+    const double* A = (const double*)(GLOBAL_AS const double*)(Lm + L.corner());
+    double* O = (double*)(GLOBAL_AS double*)(T + K.band(c, r - c));
+    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
+        const int i = 64 * r + (e & 63), j = 64 * c + (e >> 6);
+        O[e] = i < L.ap && j < L.ap ? A[i + (int64_t)j * L.ap] : (i == j ? 1.0 : 0.0);
+    }
+}
+__device__ inline void corner_out_body(double* Lm, const Lay& L, int bid, const double* T, double* ldp) {
+    const Lay K = corner_lay(L);
+    const int nab = arrow_blocks(L.ap);
+    T = (const double*)(GLOBAL_AS const double*)T;
+    if (bid == nab * nab) {
+        if (threadIdx.x >= 64) return;
+        double s = 0.0, c = 0.0;
+        for (int j = threadIdx.x; j < 64 * nab; j += 64) neumaier(s, c, 2.0 * log(T[K.band(j >> 6, 0) + (j & 63) * 65]));
+        neumaier_join(s, c);
+        if (threadIdx.x == 0) {
+            ldp[2 * L.nt] = s;
+            ldp[2 * L.nt + 1] = c;
+        }
+        return;
+    }
+    const int r = bid % nab, c = bid / nab;
+    double* A = (double*)(GLOBAL_AS double*)(Lm + L.corner());
+    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
+        const int i = 64 * r + (e & 63), j = 64 * c + (e >> 6);
+        if (i < L.ap && j < L.ap) A[i + (int64_t)j * L.ap] = i >= j ? T[K.band(c, r - c) + e] : 0.0;
+    }
+}
+// Workgroups 8 N .. of the tail: the corner's copy.
+__host__ __device__ inline int factor_tail_blocks(const Lay& L) { return (int)(8 * L.nt) + corner_in_blocks(L); }
+__device__ inline void factor_tail(double* Lm, const Lay& L, int bid, double* ldp, double* T) {
+    if (bid < 8 * L.nt) factor_tail_body(Lm, L, bid, ldp);
+    else corner_in_body(Lm, L, (int)(bid - 8 * L.nt), T);
+}
+__global__ __launch_bounds__(NT) void k_factor_tail(double* Lm, Lay L, double* ldp, double* T) {
+    factor_tail(Lm, L, blockIdx.x, ldp, T);
+}
+__global__ __launch_bounds__(NT) void k_corner_out(double* Lm, Lay L, const double* T, double* ldp) {
+    corner_out_body(Lm, L, blockIdx.x, T, ldp);
 }
 
 // Group and index inside it of task t of one matrix.
@@ -365,8 +393,7 @@ __device__ inline void fac_ticket(const FacCtx& x, int t, int& c, int& u) {
 
 // The band factor of one matrix in one persistent launch (factor.hpp): ticket
 // 0 is the chain, ticket 1 + t task t.
-__global__ __launch_bounds__(FAC_NT, 2) void k_factor_all(FacCtx x, int ntask, Sched sc, int* info) {
-    __shared__ FacSmem sm;
+__device__ inline void fac_run(const FacCtx& x, int ntask, const Sched& sc, FacSmem& sm, int* info) {
     if (threadIdx.x == 0) sm.dead = 0;
     for (;;) {
         const int g = sched_next(sc, 1 + ntask, &sm.sh);
@@ -380,24 +407,9 @@ __global__ __launch_bounds__(FAC_NT, 2) void k_factor_all(FacCtx x, int ntask, S
         if (!fac_task(x, sc, sm, c, u, g)) return;
     }
 }
-
-// C (rows x rows, lower blocks) -= P P^T, P rows x K (generic, corner blocking).
-__global__ __launch_bounds__(NT) void k_syrk_generic(double* C, int64_t ldc, const double* P,
-                                                    int64_t ldp, int rows, int K) {
-    __shared__ double smem[GB_SMEM_DOUBLES];
-    int rb, cb;
-    tri_decode(blockIdx.x, rb, cb);
-    const int va = imin_(64, rows - rb * 64), vb = imin_(64, rows - cb * 64);
-    GAcc g;
-    gacc_zero(g);
-    gemm_acc(g, opnd(P + rb * 64, ldp, 0, va), opnd(P + cb * 64, ldp, 1, vb), K, smem);
-    double* O = C + rb * 64 + (int64_t)cb * 64 * ldc;
-    gemm_store(g, smem, -1.0, 1.0, O, ldc, O, ldc, va, vb);
-}
-
-__global__ void k_zero_block(double* C, int64_t ld, int rows, int cols) {
-    for (int idx = threadIdx.x + blockIdx.x * blockDim.x; idx < rows * cols; idx += blockDim.x * gridDim.x)
-        C[(idx % rows) + (int64_t)(idx / rows) * ld] = 0.0;
+__global__ __launch_bounds__(FAC_NT, 2) void k_factor_all(FacCtx x, int ntask, Sched sc, int* info) {
+    __shared__ FacSmem sm;
+    fac_run(x, ntask, sc, sm, info);
 }
 
 // Final log det (compensated sum of the partial pairs in a fixed order: each
@@ -425,19 +437,21 @@ __global__ __launch_bounds__(64) void k_factor_final(const double* ldp, int npar
 // ---------------------------------------------------------------------------
 
 // Phase 1, diagonal tiles: X_J = L_JJ^{-1} ("TRSM(L_ii^T, I)"), stored in the
-// diagonal slots of the workspace; the corner inverse likewise.
+// diagonal slots of the workspace; the corner inverse likewise, one workgroup
+// per 64 columns.
+__host__ __device__ inline int trtri_blocks(const Lay& L) { return (int)L.nt + arrow_blocks(L.ap); }
 __device__ inline void trtri_body(const double* Lm, double* W, const Lay& L, int* info, int bid, double* smem) {
     const int64_t J = bid;
     int bad;
     if (J < L.nt) {
         trtri_tile(Lm + L.band(J, 0), L.b, W + L.band(J, 0), L.b, L.b, smem, &bad);
     } else {
-        trtri_tile(Lm + L.corner(), L.ap, W + L.corner(), L.ap, L.ap, smem, &bad);
+        trtri_columns(Lm + L.corner(), L.ap, W + L.corner(), L.ap, L.ap, (int)(J - L.nt), smem, &bad);
     }
     if (threadIdx.x == 0 && bad) atomicExch(info, STILES_EBADL);
 }
 // (j0: first tile column; the launches of a selection start there)
-__global__ __launch_bounds__(NT) void k_trtri_all(const double* Lm, double* W, Lay L, int* info, int64_t j0) {
+__global__ __launch_bounds__(NT, 2) void k_trtri_all(const double* Lm, double* W, Lay L, int* info, int64_t j0) {
     __shared__ double smem[TRTRI_SMEM_DOUBLES];
     trtri_body(Lm, W, L, info, (int)(blockIdx.x + j0), smem);
 }
@@ -571,18 +585,23 @@ struct FactorWs {
     int* err;       // scheduler error word
     int* ticket;
     double* ldp;    // log det partial pairs, N + 2 of them
-    double* Xc;     // 256 x 256 inverse of the blocked corner
+    int* cticket;   // the corner's
+    double* Tc;     // the corner's tiles (corner_lay)
+    double* Ycd;    // its 16 x 16 diagonal-block inverses
     double* Yd;     // 16 x 16 diagonal-block inverses of every L_JJ
-    int* flags;     // fac_ints(L) flags
+    int* flags;     // fac_ints(L) flags, then the corner's
 };
 __host__ __device__ inline FactorWs factor_ws(const Lay& L, char* ws) {
     FactorWs f;
     f.winfo = (int*)ws;
     f.err = f.winfo + 16;
     f.ticket = f.winfo + 32;
+    f.cticket = f.winfo + 48;
     f.ldp = (double*)(ws + WS_HEAD);
-    f.Xc = f.ldp + 2 * (L.nt + 2);
-    f.Yd = f.Xc + 256 * 256;
+    f.Tc = f.ldp + 2 * (L.nt + 2);
+    const int64_t nab = arrow_blocks(L.ap);
+    f.Ycd = f.Tc + nab * nab * 64 * 64;
+    f.Yd = f.Ycd + nab * 64 * 16;
     f.flags = (int*)(f.Yd + L.nt * (int64_t)L.b * 16);
     return f;
 }
@@ -593,9 +612,16 @@ __device__ inline void factor_setup_body(const Lay& L, const FactorWs& f, int64_
         *f.winfo = 0x7fffffff;
         *f.err = 0;
         *f.ticket = 0;
+        *f.cticket = 0;
     }
-    const int64_t n = fac_ints(L);
+    const int64_t n = fac_ints(L) + fac_ints(corner_lay(L));
     for (int64_t i = at; i < n; i += step) f.flags[i] = 0;
+}
+// The corner's factor.
+__host__ __device__ inline FacCtx corner_ctx(const Lay& L, const FactorWs& f) {
+    FacCtx x = fac_ctx(corner_lay(L), f.Tc, f.Ycd, f.flags ? f.flags + fac_ints(L) : nullptr);
+    x.col0 = (int)L.nb;
+    return x;
 }
 __global__ __launch_bounds__(NT) void k_factor_setup(Lay L, FactorWs f) {
     factor_setup_body(L, f, threadIdx.x + (int64_t)blockIdx.x * NT, (int64_t)NT * gridDim.x);
@@ -755,15 +781,29 @@ __global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BFacArgs a) {
 
 __global__ __launch_bounds__(NT) void kb_factor_tail(BArgs a) {
     BATCH_DECODE(a, I, bid, nblk);
-    factor_tail_body(I.Lm, I.L, bid, factor_ws(I.L, I.ws).ldp);
+    const FactorWs f = factor_ws(I.L, I.ws);
+    factor_tail(I.Lm, I.L, bid, f.ldp, f.Tc);
 }
 
-// Corner POTRF (a_p <= 256) of the matrices listed in idx, one workgroup each.
-__global__ __launch_bounds__(NT) void kb_corner(const BInst* bi, const int* idx) {
-    extern __shared__ double smem[];
-    const BInst& I = bi[idx[blockIdx.x]];
+// The corners, each on its own workgroups with its own tickets.  (A matrix's
+// workgroups follow one another in the launch, so whichever of them are
+// resident, those of the first unfinished one are.)
+__global__ __launch_bounds__(FAC_NT, 2) void kb_corner(BArgs a, int* err) {
+    __shared__ FacSmem sm;
+    BATCH_DECODE(a, I, bid, nblk);
     const FactorWs f = factor_ws(I.L, I.ws);
-    potrf_body(I.Lm + I.L.corner(), (int64_t)I.L.ap, I.L.ap, nullptr, 0, f.ldp + 2 * I.L.nt, f.winfo, I.L.nb, smem);
+    Sched sc;
+    sc.ticket = f.cticket;
+    sc.err = err;
+    sc.spin_limit = a.spin_limit;
+    sc.withhold = -1;
+    const FacCtx x = corner_ctx(I.L, f);
+    fac_run(x, (int)fac_tasks(x), sc, sm, f.winfo);
+}
+__global__ __launch_bounds__(NT) void kb_corner_out(BArgs a) {
+    BATCH_DECODE(a, I, bid, nblk);
+    const FactorWs f = factor_ws(I.L, I.ws);
+    corner_out_body(I.Lm, I.L, bid, f.Tc, f.ldp);
 }
 
 __global__ __launch_bounds__(64) void kb_factor_final(const BInst* bi, const int* err) {
@@ -785,7 +825,7 @@ __global__ __launch_bounds__(NT) void kb_zero_unused(BArgs a) {
     zero_unused_body(I.S, I.L, bid, nblk);
 }
 
-__global__ __launch_bounds__(NT) void kb_trtri(BArgs a) {
+__global__ __launch_bounds__(NT, 2) void kb_trtri(BArgs a) {
     __shared__ double smem[TRTRI_SMEM_DOUBLES];
     BATCH_DECODE(a, I, bid, nblk);
     const SelinvWs v = selinv_ws(I.L, I.ws);
@@ -1174,33 +1214,14 @@ static int grid_for(int64_t work) {
 }
 
 // log det partial pairs: one per band tile column, one or two for the corner
-static int factor_nparts(const Lay& L) {
-    return (int)L.nt + (L.ap > 0 ? (L.ap <= 256 ? 1 : 2) : 0);
-}
+static int factor_nparts(const Lay& L) { return (int)L.nt + (L.ap > 0 ? 1 : 0); }
 
-// The corner's Cholesky: one POTRF when a_p <= 256, else POTRF + TRTRI of
-// its first 256 columns, TRSM and SYRK of the rest, POTRF of the remainder.
-static int enqueue_corner(double* Lm, const Lay& L, const FactorWs& f, hipStream_t st) {
+// Workgroups of a corner's factor: the chain and up to 31 for its tasks (at
+// most eight block rows).
+static int corner_grid(const Lay& L) {
     if (L.ap == 0) return 0;
-    double* Cc = Lm + L.corner();
-    if (L.ap <= 256) {
-        LAUNCH(STILES_TK_POTRF, k_potrf, dim3(1), dim3(NT), sizeof(double) * potrf_smem_doubles(L.ap), st, Cc,
-               (int64_t)L.ap, L.ap, (double*)nullptr, (int64_t)0, f.ldp + 2 * L.nt, f.winfo, L.nb);
-        return 0;
-    }
-    const int c2 = L.ap - 256;
-    LAUNCH(STILES_TK_POTRF, k_potrf, dim3(1), dim3(NT), sizeof(double) * potrf_smem_doubles(256), st, Cc,
-           (int64_t)L.ap, 256, f.Xc, (int64_t)256, f.ldp + 2 * L.nt, f.winfo, L.nb);
-    LAUNCH(STILES_TK_OTHER, k_trsm_generic, dim3((c2 + 63) / 64), dim3(NT), 0, st, Cc + 256, (int64_t)L.ap, c2,
-           (const double*)f.Xc, (int64_t)256, 256);
-    const int nab2 = (c2 + 63) / 64;
-    LAUNCH(STILES_TK_OTHER, k_syrk_generic, dim3(nab2 * (nab2 + 1) / 2), dim3(NT), 0, st,
-           Cc + 256 + (int64_t)256 * L.ap, (int64_t)L.ap, (const double*)(Cc + 256), (int64_t)L.ap, c2, 256);
-    LAUNCH(STILES_TK_POTRF, k_potrf, dim3(1), dim3(NT), sizeof(double) * potrf_smem_doubles(c2), st,
-           Cc + 256 + (int64_t)256 * L.ap, (int64_t)L.ap, c2, (double*)nullptr, (int64_t)0, f.ldp + 2 * (L.nt + 1),
-           f.winfo, L.nb + 256);
-    LAUNCH(STILES_TK_OTHER, k_zero_block, dim3(64), dim3(NT), 0, st, Cc + (int64_t)256 * L.ap, (int64_t)L.ap, 256, c2);
-    return 0;
+    const int64_t n = fac_tasks(fac_ctx(corner_lay(L), nullptr, nullptr, nullptr));
+    return (int)std::min<int64_t>(1 + n, 32);
 }
 
 static int64_t p2_total_tasks(const Lay& L) {
@@ -1221,13 +1242,13 @@ struct BPlan {
     int64_t maxC = 0;          // most chunks of a matrix
 };
 // factor workspace (FactorWs): head (info, error words) + log det partials
-// (N + 2 pairs) + the 256 x 256 inverse of the blocked corner + the 16 x 16
-// diagonal-block inverses of every L_JJ + the flags of the persistent launch.
+// (N + 2 pairs) + the corner's tiles and diagonal-block inverses + the 16 x 16
+// diagonal-block inverses of every L_JJ + the flags of the persistent launches.
 static size_t fws_bytes(const stiles_layout& l) {
     const Lay L = to_dev(l);
     return WS_HEAD + sizeof(double) * (size_t)(2 * (l.nt + 2)) +
-           sizeof(double) * (size_t)(256 * 256 + l.nt * (int64_t)l.tile * 16) +
-           sizeof(int) * (size_t)fac_ints(L);
+           sizeof(double) * (size_t)(corner_lay(L).total + arrow_blocks(L.ap) * 64 * 16 + l.nt * (int64_t)l.tile * 16) +
+           sizeof(int) * (size_t)(fac_ints(L) + fac_ints(corner_lay(L)));
 }
 // selinv workspace (SelinvWs): head (info, ticket, error words), the Phase 1
 // tiles (inverted diagonal tiles, Lhat, corner inverse) in the tile layout,
@@ -1249,13 +1270,13 @@ static int batch_plan(const stiles_batch_item* items, int count, bool need_sigma
         sumC += nc;
         pl.maxC = std::max(pl.maxC, nc);
     }
-    // segment tables of at most six per-matrix launches; ints: the corner
-    // list, the error word, a ticket per factor launch (at most one per chunk
+    // segment tables of at most six per-matrix launches; ints: the error
+    // word, a ticket per factor launch (at most one per chunk
     // and slice), and the queue tables (the order, then per chunk the prefix
     // sums over the matrices that have it)
     const size_t nseg = 6 * ((size_t)count + 1);
     const size_t slices = ((size_t)count + KB_SLICE - 1) / KB_SLICE;
-    const size_t nint = (size_t)count + 1 + (size_t)pl.maxC * slices + (size_t)count + (size_t)sumC + (size_t)pl.maxC;
+    const size_t nint = 1 + (size_t)pl.maxC * slices + (size_t)count + (size_t)sumC + (size_t)pl.maxC;
     pl.table_f = align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg) + align256(sizeof(int) * nint);
     pl.table = pl.table_f + align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg);
     size_t o = pl.table;
@@ -1369,7 +1390,8 @@ int stiles_pack(const double* ab, const double* arrow_rows, const double* corner
     if (arrow > 0 && !corner) return -3;
     if (!tiles) return -4;
     Lay L = to_dev(lay);
-    LAUNCH(STILES_TK_OTHER, k_pack, dim3((unsigned)(L.nt * (int64_t)(L.bt + 1) + L.nt + 1)), dim3(NT), 0, S_(stream),
+    const int nab = arrow_blocks(L.ap);
+    LAUNCH(STILES_TK_OTHER, k_pack, dim3((unsigned)(L.nt * (int64_t)(L.bt + 1) + L.nt + nab * nab)), dim3(NT), 0, S_(stream),
            ab, arrow_rows, corner, tiles, L);
     return 0;
 }
@@ -1403,21 +1425,26 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
         HIPCHK(hipMemcpyAsync(Lm, A, sizeof(double) * (size_t)L.total, hipMemcpyDeviceToDevice, st));
         tm_end(tm, STILES_TK_OTHER, st);
     }
-    LAUNCH(STILES_TK_OTHER, k_factor_setup, dim3(grid_for(fac_ints(L))), dim3(NT), 0, st, L, f);
+    LAUNCH(STILES_TK_OTHER, k_factor_setup, dim3(grid_for(fac_ints(L) + fac_ints(corner_lay(L)))), dim3(NT), 0, st, L, f);
     LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(1 + ntask, fac_grid(x, 2 * di.cus))),
            dim3(FAC_NT), 0, st, x, (int)ntask, sc, f.winfo);
-    LAUNCH(STILES_TK_OTHER, k_factor_tail, dim3((unsigned)(8 * L.nt)), dim3(NT), 0, st, Lm, L, f.ldp);
-    rc = enqueue_corner(Lm, L, f, st);
-    if (rc) return rc;
+    LAUNCH(STILES_TK_OTHER, k_factor_tail, dim3((unsigned)factor_tail_blocks(L)), dim3(NT), 0, st, Lm, L, f.ldp, f.Tc);
+    if (L.ap > 0) {
+        const FacCtx xc = corner_ctx(L, f);
+        sc.ticket = f.cticket;
+        sc.withhold = -1;
+        LAUNCH(STILES_TK_POTRF, k_factor_all, dim3((unsigned)corner_grid(L)), dim3(FAC_NT), 0, st, xc, (int)fac_tasks(xc), sc,
+               f.winfo);
+        LAUNCH(STILES_TK_OTHER, k_corner_out, dim3((unsigned)corner_out_blocks(L)), dim3(NT), 0, st, Lm, L,
+               (const double*)f.Tc, f.ldp);
+    }
     LAUNCH(STILES_TK_OTHER, k_factor_final, dim3(1), dim3(64), 0, st, (const double*)f.ldp, factor_nparts(L),
            (const int*)f.winfo, (const int*)f.err, logdet, (int*)info);
     return 0;
 }
 
 // Selected inverse on the tile columns J >= jf (and the corner): Phase 1 of
-// the columns from jf - 1 on (the first Phase 2 group also holds the EA, E1A
-// and EB tasks of column jf - 1), Phase 2 groups N-1 .. jf.  jf = 0 is the
-// whole pattern.
+// these columns, Phase 2 groups N-1 .. jf.  jf = 0 is the whole pattern.
 static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, int64_t jf, int32_t* info,
                        void* workspace, hipStream_t st) {
     Lay L = to_dev(lay);
@@ -1434,7 +1461,7 @@ static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, in
         LAUNCH(STILES_TK_OTHER, k_zero_unused, dim3(grid_for(tail)), dim3(NT), 0, st, S, L);
     }
     // Phase 1
-    LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)(L.nt - j1 + (L.ap > 0))), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
+    LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)(trtri_blocks(L) - j1)), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
            j1);
     {
         const int64_t g = (L.nt - j1) * (int64_t)(L.bt * nb64 + nab) * nb64;
@@ -1575,7 +1602,7 @@ int stiles_inverse(const double* Lm, double* Ainv, int64_t n, int64_t bandwidth,
     LAUNCH(STILES_TK_OTHER, k_set_int, dim3(1), dim3(64), 0, st, v.err, 0);
     LAUNCH(STILES_TK_OTHER, k_zero_ints, dim3(grid_for(np * np * 2)), dim3(NT), 0, st, (int*)D, np * np * 2);
     // Phase 1: X_J, Lhat (as for stiles_selinv)
-    LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)(L.nt + (L.ap > 0))), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
+    LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)trtri_blocks(L)), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
            (int64_t)0);
     {
         const int64_t g = L.nt * (int64_t)(L.bt * nb64 + nab) * nb64;
@@ -1723,21 +1750,25 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     std::vector<BSeg> segs;
     SegTab t;
     t.start(segs.size());
-    for (int k = 0; k < count; ++k) t.add(segs, k, (int)(8 * bi[k].L.nt));
-    const size_t zu_at = t.begin;
-    const int zu_grid = t.grid, zu_n = t.finish(segs);
-    // ints: [0, count) corner list, [count] error word, then one ticket per
-    // factor launch (zero as uploaded), then the queue tables
+    for (int k = 0; k < count; ++k) t.add(segs, k, factor_tail_blocks(bi[k].L));
+    struct Launch { size_t at; int n, grid; };
+    auto close = [&](Launch& l) { l.at = t.begin; l.grid = t.grid; l.n = t.finish(segs); };
+    Launch tail, corner, corner_back;
+    close(tail);
+    t.start(segs.size());
+    for (int k = 0; k < count; ++k)
+        if (bi[k].L.ap > 0) t.add(segs, k, corner_grid(bi[k].L));
+    close(corner);
+    t.start(segs.size());
+    for (int k = 0; k < count; ++k)
+        if (bi[k].L.ap > 0) t.add(segs, k, corner_out_blocks(bi[k].L));
+    close(corner_back);
+    // ints: the error word, then one ticket per factor launch (zero as
+    // uploaded), then the queue tables
     const int slices = (count + KB_SLICE - 1) / KB_SLICE;
     const size_t nticket = (size_t)pl.maxC * slices;
-    std::vector<int> ints((size_t)count + 1 + nticket, 0);
-    int ncorner = 0, corner_smem = 0;
-    for (int k = 0; k < count; ++k)
-        if (bi[k].L.ap > 0 && bi[k].L.ap <= 256) {
-            ints[ncorner++] = k;
-            corner_smem = std::max(corner_smem, (int)sizeof(double) * potrf_smem_doubles(bi[k].L.ap));
-        }
-    const size_t err_at = (size_t)count, tick_at = (size_t)count + 1;
+    std::vector<int> ints(1 + nticket, 0);
+    const size_t err_at = 0, tick_at = 1;
     std::vector<FacCtx> fx(count);
     for (int k = 0; k < count; ++k) fx[k] = fac_ctx(bi[k].L, nullptr, nullptr, nullptr);
     const size_t order_at = ints.size();
@@ -1814,17 +1845,11 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
                    st, a);
         }
     }
-    {
-        const BArgs a{dbi, dseg + zu_at, zu_n, spin};
-        LAUNCH(STILES_TK_OTHER, kb_factor_tail, dim3((unsigned)zu_grid), dim3(NT), 0, st, a);
-    }
-    if (ncorner > 0) {
-        LAUNCH(STILES_TK_POTRF, kb_corner, dim3((unsigned)ncorner), dim3(NT), corner_smem, st, dbi, (const int*)dint);
-    }
-    for (int k = 0; k < count; ++k) {
-        if (bi[k].L.ap <= 256) continue;
-        rc = enqueue_corner(bi[k].Lm, bi[k].L, factor_ws(bi[k].L, bi[k].ws), st);
-        if (rc) return rc;
+    auto args = [&](const Launch& l) { return BArgs{dbi, dseg + l.at, l.n, spin}; };
+    LAUNCH(STILES_TK_OTHER, kb_factor_tail, dim3((unsigned)tail.grid), dim3(NT), 0, st, args(tail));
+    if (corner.grid > 0) {
+        LAUNCH(STILES_TK_POTRF, kb_corner, dim3((unsigned)corner.grid), dim3(FAC_NT), 0, st, args(corner), dint + err_at);
+        LAUNCH(STILES_TK_OTHER, kb_corner_out, dim3((unsigned)corner_back.grid), dim3(NT), 0, st, args(corner_back));
     }
     LAUNCH(STILES_TK_OTHER, kb_factor_final, dim3(count), dim3(64), 0, st, dbi, (const int*)(dint + err_at));
     return 0;
@@ -1872,7 +1897,7 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     }
     close(zu);
     t.start(segs.size());
-    for (int k = 0; k < count; ++k) t.add(segs, k, (int)(bi[k].L.nt + (bi[k].L.ap > 0)));
+    for (int k = 0; k < count; ++k) t.add(segs, k, trtri_blocks(bi[k].L));
     close(tr);
     t.start(segs.size());
     for (int k = 0; k < count; ++k) {
