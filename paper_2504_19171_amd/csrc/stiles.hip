@@ -1244,11 +1244,13 @@ struct BPlan {
 // factor workspace (FactorWs): head (info, error words) + log det partials
 // (N + 2 pairs) + the corner's tiles and diagonal-block inverses + the 16 x 16
 // diagonal-block inverses of every L_JJ + the flags of the persistent launches.
+// Never less than one tile, which callers may count on.
 static size_t fws_bytes(const stiles_layout& l) {
     const Lay L = to_dev(l);
-    return WS_HEAD + sizeof(double) * (size_t)(2 * (l.nt + 2)) +
-           sizeof(double) * (size_t)(corner_lay(L).total + arrow_blocks(L.ap) * 64 * 16 + l.nt * (int64_t)l.tile * 16) +
-           sizeof(int) * (size_t)(fac_ints(L) + fac_ints(corner_lay(L)));
+    const size_t n = WS_HEAD + sizeof(double) * (size_t)(2 * (l.nt + 2)) +
+                     sizeof(double) * (size_t)(corner_lay(L).total + arrow_blocks(L.ap) * 64 * 16 + l.nt * (int64_t)l.tile * 16) +
+                     sizeof(int) * (size_t)(fac_ints(L) + fac_ints(corner_lay(L)));
+    return std::max(n, sizeof(double) * (size_t)l.tile * (size_t)l.tile);
 }
 // selinv workspace (SelinvWs): head (info, ticket, error words), the Phase 1
 // tiles (inverted diagonal tiles, Lhat, corner inverse) in the tile layout,
