@@ -42,7 +42,12 @@ enum { P2_FAR = 0, P2_ROW, P2_DIAG };
 struct P2 {
     double* S;
     const double* W;
-    Lay L;
+    Lay L;      // of Sigma
+    // of W: its tile half-bandwidth and arrow offset.  The same as Sigma's for
+    // the selected inverse; for the whole inverse Sigma has every tile below
+    // the diagonal, and the sums still run over W's band and arrow only.
+    int btw;
+    int64_t warrow;
     int* cnt;
     int ntasks;
     // rows of the last band tile (J + bt) that Lhat's band reaches, to 32
@@ -52,6 +57,10 @@ struct P2 {
     // every group but the last holds g_tasks tasks, and group q0 starts at
     // ticket off_q0, so a ticket's group is found in closed form
     int q0, off_q0, g_tasks;
+
+    __host__ __device__ int sw(int64_t J) const { return (int)(L.nt - 1 - J < btw ? L.nt - 1 - J : btw); }
+    __host__ __device__ int64_t wband(int64_t J, int e) const { return (J * (int64_t)(btw + 1) + e) * L.b * L.b; }
+    __host__ __device__ int64_t war(int64_t J) const { return warrow + J * (int64_t)L.ap * L.b; }
 };
 
 __host__ __device__ inline int p2_ctr(const Lay& L) { return L.bt + 2; }   // counters per tile column
@@ -72,6 +81,13 @@ __host__ __device__ inline int p2_far2_tasks(const Lay& L, int64_t J) {
 __host__ __device__ inline int p2_group_tasks(const Lay& L, int64_t J, int64_t jf) {
     return (J == L.nt - 1 ? p2_far_tasks(L, J) : 0) + (J > jf ? p2_far_tasks(L, J - 1) : 0) + p2_row_tasks(L, J) +
            p2_diag_tasks(L);
+}
+// Tasks before group q <= max(bt, 1), none of these the last: one more row tile
+// in each than in the one before.
+__host__ __device__ inline int64_t p2_base(const Lay& L, int64_t q) {
+    if (q == 0) return 0;
+    const int64_t nb64 = L.b / 64, nab = arrow_blocks(L.ap);
+    return nb64 * nb64 * (q * (q - 1) / 2) + q * (nab * nb64 + p2_diag_tasks(L)) + (q - 1) * 4 * nb64 * nb64 + nab * nb64;
 }
 // Tasks that make tile offset d (or ARW) of a column final.
 __device__ inline int p2_target(const Lay& L, int d) {
@@ -335,7 +351,7 @@ __device__ inline void p2_far_row(const Lay& L, int64_t J, int rb, int& d, int& 
 template <int NW>
 __device__ __forceinline__ bool p2_far(const P2& p, const Sched& sc, int64_t J, int u, double* smem, int* sh, int t) {
     const Lay& L = p.L;
-    const int nb64 = L.b / 64, s = L.s(J);
+    const int nb64 = L.b / 64, s = p.sw(J);
     const int rb = u / nb64, cb = u % nb64;
     int d, rbl;
     p2_far_row(L, J, rb, d, rbl);
@@ -357,8 +373,8 @@ __device__ __forceinline__ bool p2_far(const P2& p, const Sched& sc, int64_t J, 
             int64_t lda;
             p2_sigma_rows(L, p.S, J, d, rbl, 64, e, g.a, lda, g.ta, g.av);
             g.lda = (int)lda;
-            if (e != ARW) { g.b = p.W + L.band(J, e) + (int64_t)cb * 64 * L.b; g.ldb = L.b; g.K = e == L.bt ? p.klast : L.b; }
-            else { g.b = p.W + L.arrow(J) + (int64_t)cb * 64 * L.ap; g.ldb = L.ap; g.K = L.ap; }
+            if (e != ARW) { g.b = p.W + p.wband(J, e) + (int64_t)cb * 64 * L.b; g.ldb = L.b; g.K = e == p.btw ? p.klast : L.b; }
+            else { g.b = p.W + p.war(J) + (int64_t)cb * 64 * L.ap; g.ldb = L.ap; g.K = L.ap; }
             return g;
         });
         q += m;
@@ -392,7 +408,7 @@ __device__ __forceinline__ bool p2_far(const P2& p, const Sched& sc, int64_t J, 
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    put(half, j, r, -((half ? acc[1][j][r] : acc[0][j][r]) + take[(4 * j + r) * 64 + l]));
+                    put(half, j, r, 0.0 - ((half ? acc[1][j][r] : acc[0][j][r]) + take[(4 * j + r) * 64 + l]));
     } else {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -400,7 +416,7 @@ __device__ __forceinline__ bool p2_far(const P2& p, const Sched& sc, int64_t J, 
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) put(i, j, r, -(acc[i][j][r] + acc1[i][j][r]));
+                    for (int r = 0; r < 4; ++r) put(i, j, r, 0.0 - (acc[i][j][r] + acc1[i][j][r]));
     }
     return true;
 }
@@ -413,7 +429,7 @@ template <int NW>
 __device__ __forceinline__ bool p2_near(const P2& p, const Sched& sc, int kind, int64_t J, int u, double* smem, double* red,
                                         int* sh, int t) {
     const Lay& L = p.L;
-    const int C32 = L.b / 32, s = L.s(J), karw = L.ap > 0 ? 1 : 0;
+    const int C32 = L.b / 32, s = p.sw(J), karw = L.ap > 0 ? 1 : 0;
     const bool row = kind == P2_ROW;
     int rb, cb;
     if (row) { rb = u / C32; cb = u % C32; }
@@ -443,9 +459,9 @@ __device__ __forceinline__ bool p2_near(const P2& p, const Sched& sc, int kind, 
         const int ld = e == ARW ? L.ap : L.b;
         Seg g;
         g.a = p.S + (e == ARW ? L.arrow(row ? J + 1 : J) : L.band(row ? J + 1 : J, row ? e - 1 : e)) + (int64_t)rb * 32 * ld;
-        g.b = p.W + (e == ARW ? L.arrow(J) : L.band(J, e)) + (int64_t)cb * 32 * ld;
+        g.b = p.W + (e == ARW ? p.war(J) : p.wband(J, e)) + (int64_t)cb * 32 * ld;
         g.lda = g.ldb = ld;
-        g.K = e == ARW ? L.ap : e == L.bt ? p.klast : L.b;
+        g.K = e == ARW ? L.ap : e == p.btw ? p.klast : L.b;
         return g;
     };
     // the counter of its Sigma operand
@@ -459,7 +475,7 @@ __device__ __forceinline__ bool p2_near(const P2& p, const Sched& sc, int kind, 
     // arrow and the tiles from J+3 on, then J+2 and J+1
     const int n1 = s - e2 + karw;
     auto off1 = [&](int q) { return q < karw ? ARW : s - (q - karw); };
-    auto len = [&](int e) { return e == L.bt ? p.klast : L.b; };
+    auto len = [&](int e) { return e == p.btw ? p.klast : L.b; };
     if (n1 > 0) {
         if (!p2_all_ready(sc, n1, sh, [&](int q, const int*& f, int& t) { dep(off1(q), f, t); })) return false;
         TRACE(t, 1, wall_clock64());
@@ -514,14 +530,15 @@ __device__ inline void p2_run(const P2& p, const Sched& sc, double* smem, int* s
             if (q > N - 1 - p.jf) q = N - 1 - p.jf;
             base = p.off_q0 + (int)(q - p.q0) * p.g_tasks;
         } else {
-            q = 0;
-            base = 0;
-            for (;;) {
-                const int n = p2_group_tasks(L, N - 1 - q, p.jf);
-                if (t < base + n) break;
-                base += n;
-                ++q;
-            }
+            // p2_base is a q^2 + b q + c from q = 1 on: its root, set right
+            // for the rounding
+            const double nb64 = L.b / 64, nn = 0.5 * nb64 * nb64, bb = (double)p2_base(L, 2) - (double)p2_base(L, 1) - 3.0 * nn;
+            const double cc = (double)p2_base(L, 1) - nn - bb;
+            q = (int64_t)((sqrt(fmax(bb * bb + 4.0 * nn * (t - cc), 0.0)) - bb) / (2.0 * nn));
+            q = q < 0 ? 0 : q > p.q0 - 1 ? p.q0 - 1 : q;
+            while (q > 0 && p2_base(L, q) > t) --q;
+            while (q < p.q0 - 1 && p2_base(L, q + 1) <= t) ++q;
+            base = (int)p2_base(L, q);
         }
         const int64_t G = N - 1 - q;
         int u = t - base;

@@ -65,10 +65,6 @@ static Lay to_dev(const stiles_layout& s) {
 __global__ void k_zero_ints(int* p, int64_t n) {
     for (int64_t i = threadIdx.x + (int64_t)blockIdx.x * blockDim.x; i < n; i += (int64_t)blockDim.x * gridDim.x) p[i] = 0;
 }
-__global__ void k_set_int(int* p, int v) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
-}
-
 // Pack the canonical band form into the tile layout (every double written).
 // Workgroup g < N (B+1) writes band tile g = J (B+1) + d, i.e. tile (J+d, J);
 // the next N write the arrow tiles J; the rest the corner's 64 x 64 blocks.
@@ -523,7 +519,8 @@ __host__ __device__ inline int lauum_corner(const Lay& L) {
 __host__ __device__ inline int64_t lauum_blocks(const Lay& L, int64_t j0) {
     return (L.nt - j0) * (int64_t)lauum_per(L) + lauum_corner(L);
 }
-__device__ inline void lauum_body(const double* W, double* S, const Lay& L, int64_t bid, double* smem) {
+// (W in layout K, Sigma in layout L: the same tiles, no more of them in K)
+__device__ inline void lauum_body(const double* W, const Lay& K, double* S, const Lay& L, int64_t bid, double* smem) {
     const int per = lauum_per(L);
     const int64_t nband = L.nt * (int64_t)per;
     const double* X;
@@ -534,11 +531,11 @@ __device__ inline void lauum_body(const double* W, double* S, const Lay& L, int6
     if (bid < nband) {
         const int64_t J = bid / per;
         t = (int)(bid % per);
-        X = W + L.band(J, 0); O = S + L.band(J, 0); m = L.b; ld = L.b;
+        X = W + K.band(J, 0); O = S + L.band(J, 0); m = L.b; ld = L.b;
     } else {
         t = (int)(bid - nband);
         if (t >= lauum_corner(L)) return;
-        X = W + L.corner(); O = S + L.corner(); m = L.ap; ld = L.ap;
+        X = W + K.corner(); O = S + L.corner(); m = L.ap; ld = L.ap;
     }
     int rb, cb;
     tri_decode(t, rb, cb);
@@ -553,7 +550,7 @@ __device__ inline void lauum_body(const double* W, double* S, const Lay& L, int6
 }
 __global__ __launch_bounds__(NT) void k_lauum_all(const double* W, double* S, Lay L, int64_t j0) {
     __shared__ double smem[GB_SMEM_DOUBLES];
-    lauum_body(W, S, L, xcd_block((int)blockIdx.x, (int)gridDim.x) + j0 * lauum_per(L), smem);
+    lauum_body(W, L, S, L, xcd_block((int)blockIdx.x, (int)gridDim.x) + j0 * lauum_per(L), smem);
 }
 
 __global__ void k_selinv_setup(Lay L, int* cnt, int* ticket, int* err, int* info) {
@@ -645,20 +642,23 @@ __host__ __device__ inline SelinvWs selinv_ws(const Lay& L, char* ws) {
     return v;
 }
 
-__host__ __device__ inline P2 make_p2(double* S, const SelinvWs& v, const Lay& L, int ntasks, int64_t jf) {
+// Phase 2 on tile columns J >= jf of Sigma in layout L, W in layout K (the same
+// tiles, no more of them).
+__host__ __device__ inline P2 make_p2(double* S, const Lay& L, const double* W, const Lay& K, int* cnt, int ntasks, int64_t jf) {
     P2 p;
     p.S = S;
-    p.W = v.W;
+    p.W = W;
     p.L = L;
-    p.cnt = v.flags;
+    p.btw = K.bt;
+    p.warrow = K.off_arrow;
+    p.cnt = cnt;
     p.ntasks = ntasks;
     const int64_t N = L.nt;
-    p.klast = imin_(L.b, (int)((L.b + L.w - L.bt * (int64_t)L.b + 31) / 32 * 32));
+    p.klast = imin_(L.b, (int)((L.b + K.w - K.bt * (int64_t)L.b + 31) / 32 * 32));
     p.jf = (int)jf;
     const int64_t qr = L.bt > 1 ? L.bt : 1, ql = imax64(N - 1 - jf, 0);
     p.q0 = (int)(ql < qr ? ql : qr);
-    p.off_q0 = 0;
-    for (int q = 0; q < p.q0; ++q) p.off_q0 += p2_group_tasks(L, N - 1 - q, jf);
+    p.off_q0 = (int)p2_base(L, p.q0);
     p.g_tasks = p2_group_tasks(L, N - 1 - p.q0, jf);
     return p;
 }
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(NT) void kb_trmm(BArgs a) {
 __global__ __launch_bounds__(NT) void kb_lauum(BArgs a) {
     __shared__ double smem[GB_SMEM_DOUBLES];
     BATCH_DECODE(a, I, bid, nblk);
-    lauum_body(selinv_ws(I.L, I.ws).W, I.S, I.L, bid, smem);
+    lauum_body(selinv_ws(I.L, I.ws).W, I.L, I.S, I.L, bid, smem);
 }
 
 // Phase 2 of every matrix in one persistent launch: each matrix runs on its
@@ -856,7 +856,7 @@ __global__ __launch_bounds__(P2Cfg<4>::NTH, 2) void kb_phase2(BArgs a) {
     sc.err = v.err;
     sc.spin_limit = a.spin_limit;
     sc.withhold = -1;
-    p2_run<4>(make_p2(I.S, v, I.L, I.p2_tasks, 0), sc, smem, sh);
+    p2_run<4>(make_p2(I.S, I.L, v.W, I.L, v.flags, I.p2_tasks, 0), sc, smem, sh);
 }
 
 __global__ void kb_selinv_final(const BInst* bi) {
@@ -948,108 +948,58 @@ __global__ __launch_bounds__(NT) void k_gather(const double* S, Lay L, const int
 // ---------------------------------------------------------------------------
 // Full inversion (every entry of A^{-1})
 // ---------------------------------------------------------------------------
-// The recurrence of Phase 2 taken over every tile row instead of the rows of
-// S(J): in the padded index space (band rows 0 .. N b - 1, then the a_p arrow
-// rows), with D the dense symmetric inverse (leading dimension np),
-//   D[R, J] = -sum_{k in S(J)} D[R, k] Lhat_{k,J}   for all rows R below block J,
-//   D[J, J] = X_J^T X_J - sum_{k in S(J)} Lhat_{k,J}^T D[k, J],
-// for J = N-1 .. 0 after the corner D[A, A] = X_A^T X_A (Sec. III-D; the
-// full-inversion case of Sec. III-B).  Only Lhat_{k,J} with k in S(J) is
-// non-zero, so each block column is one product over the s band tiles and the
-// arrow.  Every value goes to both triangles, so a later column reads D[i, k]
-// for any i directly.
-
-// Diagonal blocks X_J^T X_J (and the corner's) into D.
-__global__ __launch_bounds__(NT) void k_inv_lauum(const double* W, double* D, int64_t ldd, Lay L) {
+// The recurrence of Phase 2 over every tile row instead of the rows of S(J):
+//   Sigma_{i,J} = -sum_{k in S(J)} Sigma_{i,k} Lhat_{k,J}   for all i below J,
+// (Sec. III-D; the full-inversion case of Sec. III-B).  So it is Phase 2 with
+// Sigma in the layout of a dense band (every tile below the diagonal) and W in
+// L's own; the sums run over W's tiles only.  (A launch per column and for its
+// diagonal tile took 46 us a column at w 256, a 37, tile 128; this takes 15.)
+__host__ __device__ inline Lay full_lay(const Lay& L) {
+    Lay F = L;
+    F.bt = (int)(L.nt - 1);
+    F.w = L.nb - 1;
+    F.off_band = 0;
+    F.off_arrow = L.nt * L.nt * (int64_t)L.b * L.b;
+    F.off_corner = F.off_arrow + L.nt * (int64_t)L.ap * L.b;
+    F.total = F.off_corner + (int64_t)L.ap * L.ap;
+    return F;
+}
+__global__ __launch_bounds__(NT) void k_inv_lauum(const double* W, Lay L, double* S, Lay F) {
     __shared__ double smem[GB_SMEM_DOUBLES];
-    const int per = lauum_per(L);
-    const int64_t nband = L.nt * (int64_t)per;
-    const double* X;
-    double* O;
-    int m;
-    int64_t ld;
-    int t;
-    if ((int64_t)blockIdx.x < nband) {
-        const int64_t J = blockIdx.x / per;
-        t = (int)(blockIdx.x % per);
-        X = W + L.band(J, 0); m = L.b; ld = L.b;
-        O = D + J * L.b + J * L.b * ldd;
-    } else {
-        t = (int)(blockIdx.x - nband);
-        if (t >= lauum_corner(L)) return;
-        X = W + L.corner(); m = L.ap; ld = L.ap;
-        const int64_t o = L.nt * (int64_t)L.b;
-        O = D + o + o * ldd;
-    }
+    lauum_body(W, L, S, F, xcd_block((int)blockIdx.x, (int)gridDim.x), smem);
+}
+
+// The n x n output from Sigma's tiles (layout F), a pair of mirrored 64 x 64
+// blocks per workgroup, the upper one through LDS.  Block rows and columns of
+// the band lie in one tile each; a block may end in arrow rows.
+__global__ __launch_bounds__(NT) void k_inv_compact(const double* __restrict__ S, Lay F, double* __restrict__ O) {
+    __shared__ double blk[64 * 65];
+    const int64_t n = F.nb + F.a;
     int rb, cb;
-    tri_decode(t, rb, cb);
-    const int k0 = rb * 64;
-    const int va = imin_(64, m - rb * 64), vb = imin_(64, m - cb * 64);
-    GAcc g;
-    gacc_zero(g);
-    gemm_acc(g, opnd(X + k0 + (int64_t)rb * 64 * ld, ld, 1, va), opnd(X + k0 + (int64_t)cb * 64 * ld, ld, 0, vb),
-             m - k0, smem);
-    gemm_store_sym(g, smem, 1.0, 0.0, nullptr, 0, O + rb * 64 + (int64_t)cb * 64 * ldd,
-                   O + cb * 64 + (int64_t)rb * 64 * ldd, ldd, rb == cb, va, vb);
-}
-
-// D[R, J] for the rows R = (J+1) b .. np-1; block (row block, column block)
-// of 64 x 64, mirrored into D[J, R].
-__global__ __launch_bounds__(NT) void k_inv_column(const double* W, double* D, int64_t ldd, Lay L, int64_t J) {
-    __shared__ double smem[GB_SMEM_DOUBLES];
-    const int nb64 = L.b / 64;
-    const int64_t r0 = (J + 1) * L.b;
-    const int rbk = blockIdx.x / nb64, cb = blockIdx.x % nb64;
-    const int64_t i0 = r0 + (int64_t)rbk * 64;
-    const int mv = (int)std::min<int64_t>(64, ldd - i0);
-    const int s = L.s(J);
-    const int64_t ca = L.nt * (int64_t)L.b;   // first arrow column
-    const int64_t c0 = J * L.b + cb * 64;
-    GAcc g;
-    gacc_zero(g);
-    for (int d = 1; d <= s; ++d)
-        gemm_acc(g, opnd(D + i0 + (J + d) * L.b * ldd, ldd, 0, mv), opnd(W + L.band(J, d) + (int64_t)cb * 64 * L.b, L.b, 0),
-                 L.b, smem);
-    if (L.ap > 0)
-        gemm_acc(g, opnd(D + i0 + ca * ldd, ldd, 0, mv), opnd(W + L.arrow(J) + (int64_t)cb * 64 * L.ap, L.ap, 0),
-                 L.ap, smem);
-    gemm_store_sym(g, smem, -1.0, 0.0, nullptr, 0, D + i0 + c0 * ldd, D + c0 + i0 * ldd, ldd, 0, mv, 64);
-}
-
-// D[J, J] -= Lhat_{S,J}^T D[S, J], lower 64 x 64 blocks, mirrored.
-__global__ __launch_bounds__(NT) void k_inv_diag(const double* W, double* D, int64_t ldd, Lay L, int64_t J) {
-    __shared__ double smem[GB_SMEM_DOUBLES];
-    int rb, cb;
-    tri_decode(blockIdx.x, rb, cb);
-    const int s = L.s(J);
-    const int64_t ca = L.nt * (int64_t)L.b;
-    const int64_t j0 = J * L.b;
-    GAcc g;
-    gacc_zero(g);
-    for (int d = 1; d <= s; ++d) {
-        const double* Lh = W + L.band(J, d);
-        gemm_acc(g, opnd(Lh + (int64_t)rb * 64 * L.b, L.b, 1), opnd(D + (J + d) * L.b + (j0 + cb * 64) * ldd, ldd, 0),
-                 L.b, smem);
+    tri_decode((int)blockIdx.x, rb, cb);
+    const int64_t i0 = 64 * (int64_t)rb, j0 = 64 * (int64_t)cb;
+    const int64_t It = i0 / F.b, Jt = j0 / F.b;
+    const bool low = i0 < F.nb && j0 < F.nb;   // some of the block is of the band
+    const double* T = S + (low ? F.band(Jt, (int)(It - Jt)) + (i0 - It * F.b) + (j0 - Jt * F.b) * F.b : 0);
+    const double* R = S + (j0 < F.nb ? F.arrow(Jt) + (j0 - Jt * F.b) * F.ap : 0);
+    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
+        const int r = e & 63, c = e >> 6;
+        int64_t i = i0 + r, j = j0 + c;
+        if (i >= n || j >= n) continue;
+        double v;
+        if (i < F.nb && j < F.nb) v = T[r + c * F.b];
+        else if (j < F.nb) v = R[(i - F.nb) + c * (int64_t)F.ap];
+        else if (i >= F.nb) v = S[F.corner() + (i - F.nb) + (j - F.nb) * F.ap];
+        else v = S[F.arrow(Jt) + (j - F.nb) + (i - Jt * F.b) * F.ap];   // above the diagonal of a diagonal block
+        O[i + j * n] = v;
+        blk[r * 65 + c] = v;
     }
-    if (L.ap > 0) {
-        const double* Lh = W + L.arrow(J);
-        gemm_acc(g, opnd(Lh + (int64_t)rb * 64 * L.ap, L.ap, 1), opnd(D + ca + (j0 + cb * 64) * ldd, ldd, 0), L.ap,
-                 smem);
-    }
-    double* O = D + j0 + j0 * ldd;
-    gemm_store_sym(g, smem, -1.0, 1.0, O + rb * 64 + (int64_t)cb * 64 * ldd, ldd, O + rb * 64 + (int64_t)cb * 64 * ldd,
-                   O + cb * 64 + (int64_t)rb * 64 * ldd, ldd, rb == cb, 64, 64);
-}
-
-// The real rows and columns of D into the n x n output (band index i -> i,
-// arrow index nb + r -> N b + r).
-__global__ __launch_bounds__(NT) void k_inv_compact(const double* D, int64_t ldd, Lay L, double* O) {
-    const int64_t n = L.nb + L.a;
-    const int64_t shift = L.nt * (int64_t)L.b - L.nb;
-    for (int64_t idx = blockIdx.x * (int64_t)NT + threadIdx.x; idx < n * n; idx += (int64_t)gridDim.x * NT) {
-        const int64_t i = idx % n, j = idx / n;
-        const int64_t si = i < L.nb ? i : i + shift, sj = j < L.nb ? j : j + shift;
-        O[idx] = D[si + sj * ldd];
+    if (rb == cb) return;
+    __syncthreads();
+    for (int e = threadIdx.x; e < 64 * 64; e += NT) {
+        const int c = e & 63, r = e >> 6;
+        const int64_t i = i0 + r, j = j0 + c;
+        if (i < n && j < n) O[j + i * n] = blk[r * 65 + c];
     }
 }
 
@@ -1478,7 +1428,7 @@ static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, in
     // Phase 2, bottom-right to top-left, one persistent launch
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
-    const P2 p = make_p2(S, v, L, (int)ntasks, jf);
+    const P2 p = make_p2(S, L, v.W, L, v.flags, (int)ntasks, jf);
     Sched sc;
     sc.ticket = v.ticket;
     sc.err = v.err;
@@ -1576,12 +1526,15 @@ int stiles_mfma_peak(double* sink, int64_t sink_doubles, int32_t iters, double* 
 size_t stiles_trace_workspace_bytes(void) { return sizeof(double) * TP_BLOCKS; }
 
 // padded order of the dense inverse: N b band rows and a_p arrow rows
-static int64_t inv_order(const stiles_layout& l) { return l.nt * (int64_t)l.tile + l.arrow_ld; }
-
+// inverse workspace: the selected inverse's, Sigma in the dense layout, its
+// Phase 2 counters; never less than a dense matrix beside the first, which
+// callers may count on
 size_t stiles_inverse_workspace_bytes(const stiles_layout* lay) {
     if (!lay) return 0;
-    const int64_t np = inv_order(*lay);
-    return sws_bytes(*lay) + sizeof(double) * (size_t)(np * np);
+    const Lay F = full_lay(to_dev(*lay));
+    const size_t np = (size_t)(lay->nt * lay->tile + lay->arrow_ld);
+    return align256(sws_bytes(*lay)) +
+           std::max(sizeof(double) * np * np, sizeof(double) * (size_t)F.total + sizeof(int) * (size_t)((F.bt + 2) * F.nt));
 }
 
 int stiles_inverse(const double* Lm, double* Ainv, int64_t n, int64_t bandwidth, int64_t arrow, int32_t tile,
@@ -1594,15 +1547,17 @@ int stiles_inverse(const double* Lm, double* Ainv, int64_t n, int64_t bandwidth,
     if (!info) return -7;
     if (!workspace || workspace_bytes < stiles_inverse_workspace_bytes(&lay)) return -8;
     hipStream_t st = S_(stream);
-    const Lay L = to_dev(lay);
+    const Lay L = to_dev(lay), F = full_lay(L);
     const SelinvWs v = selinv_ws(L, (char*)workspace);
-    double* D = (double*)((char*)workspace + sws_bytes(lay));
-    const int64_t np = inv_order(lay);
+    double* D = (double*)((char*)workspace + align256(sws_bytes(lay)));
+    int* cnt = (int*)(D + F.total);
     const int nb64 = L.b / 64, nab = arrow_blocks(L.ap);
+    const int64_t ntasks = p2_total_tasks(F), n64 = (lay.n + 63) / 64;
+    if (ntasks > 0x7fffffff || n64 * (n64 + 1) / 2 > 0x7fffffff) return -3;
+    DevInfo di;
+    if (dev_info(&di)) return STILES_EHIP;
 
-    LAUNCH(STILES_TK_OTHER, k_set_int, dim3(1), dim3(64), 0, st, v.winfo, 0);
-    LAUNCH(STILES_TK_OTHER, k_set_int, dim3(1), dim3(64), 0, st, v.err, 0);
-    LAUNCH(STILES_TK_OTHER, k_zero_ints, dim3(grid_for(np * np * 2)), dim3(NT), 0, st, (int*)D, np * np * 2);
+    LAUNCH(STILES_TK_OTHER, k_selinv_setup, dim3(1), dim3(NT), 0, st, F, cnt, v.ticket, v.err, v.winfo);
     // Phase 1: X_J, Lhat (as for stiles_selinv)
     LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)trtri_blocks(L)), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
            (int64_t)0);
@@ -1610,18 +1565,15 @@ int stiles_inverse(const double* Lm, double* Ainv, int64_t n, int64_t bandwidth,
         const int64_t g = L.nt * (int64_t)(L.bt * nb64 + nab) * nb64;
         if (g > 0) LAUNCH(STILES_TK_PHASE1, k_trmm_all, dim3((unsigned)g), dim3(NT), 0, st, Lm, v.W, L, (int64_t)0);
     }
-    LAUNCH(STILES_TK_PHASE1, k_inv_lauum, dim3((unsigned)lauum_blocks(L, 0)), dim3(NT), 0,
-           st, (const double*)v.W, D, np, L);
-    for (int64_t J = L.nt - 1; J >= 0; --J) {
-        const int64_t rows = np - (J + 1) * L.b;
-        if (rows > 0) {
-            const int64_t g = (rows + 63) / 64 * nb64;
-            LAUNCH(STILES_TK_PHASE2, k_inv_column, dim3((unsigned)g), dim3(NT), 0, st, (const double*)v.W, D, np, L, J);
-            LAUNCH(STILES_TK_PHASE2, k_inv_diag, dim3((unsigned)(nb64 * (nb64 + 1) / 2)), dim3(NT), 0, st,
-                   (const double*)v.W, D, np, L, J);
-        }
-    }
-    LAUNCH(STILES_TK_OTHER, k_inv_compact, dim3(grid_for(lay.n * lay.n)), dim3(NT), 0, st, (const double*)D, np, L,
+    LAUNCH(STILES_TK_PHASE1, k_inv_lauum, dim3((unsigned)lauum_blocks(L, 0)), dim3(NT), 0, st, (const double*)v.W, L, D, F);
+    Sched sc;
+    sc.ticket = v.ticket;
+    sc.err = v.err;
+    sc.spin_limit = spin_limit_ticks(di);
+    sc.withhold = -1;
+    const int grid = (int)std::min<int64_t>(ntasks, P2Cfg<8>::WG_PER_CU * (int64_t)di.cus);
+    LAUNCH(STILES_TK_PHASE2, k_phase2, dim3(grid), dim3(P2Cfg<8>::NTH), 0, st, make_p2(D, F, v.W, L, cnt, (int)ntasks, 0), sc);
+    LAUNCH(STILES_TK_OTHER, k_inv_compact, dim3((unsigned)(n64 * (n64 + 1) / 2)), dim3(NT), 0, st, (const double*)D, F,
            Ainv);
     LAUNCH(STILES_TK_OTHER, k_selinv_final, dim3(1), dim3(64), 0, st, (const int*)v.winfo, (const int*)v.err, (int*)info);
     return 0;

@@ -35,6 +35,7 @@ SHAPES = [
 
 
 def _factor(nb, w, a, b, seed):
+    import torch  # noqa: F401  (its HIP runtime is loaded first)
     from gpu_util import to_device
     from paper_2504_19171_amd import stiles as st
     M = inputs.arrowhead_spd(nb, w, a, seed=seed)
@@ -111,3 +112,22 @@ def test_batched_and_partial_forms_match_bit_for_bit():
             assert int(info.item()) == 0
             assert torch.equal(P.ravel()[jf * band:lay.nt * band], S.ravel()[jf * band:lay.nt * band]), (s, jf)
             assert torch.equal(P.ravel()[lay.off_arrow + jf * arrow:], S.ravel()[lay.off_arrow + jf * arrow:]), (s, jf)
+
+
+@pytest.mark.parametrize("nb,w,a,b", SHAPES + [(130, 0, 0, 64), (200, 0, 5, 64)])
+def test_every_entry_of_the_inverse(nb, w, a, b):
+    """The full inverse: Phase 2 over every tile below the diagonal (with w = 0
+    and no arrow, sums without a term), written out in 64 x 64 blocks that end
+    anywhere in the band, the arrow or both."""
+    from paper_2504_19171_amd import stiles as st
+    M, lay, L = _factor(nb, w, a, b, 177 + nb)
+    print(f"inverse nb {nb} w {w} a {a} tile {b}", flush=True)
+    X, info = st.inverse(L, lay)
+    assert int(info.item()) == 0
+    A = _dense(M, nb, a)
+    R = np.linalg.inv(A)
+    g, d = np.sqrt(np.diag(R)), 1.0 / np.sqrt(np.diag(A))
+    tol = 4.0 * (w + a + 64) * np.finfo(float).eps * np.linalg.cond(A * d[:, None] * d[None, :])
+    got = X.cpu().numpy().reshape(nb + a, nb + a)
+    assert (np.abs(got - R) / (g[:, None] * g[None, :])).max() <= tol
+    assert np.array_equal(got, got.T)
