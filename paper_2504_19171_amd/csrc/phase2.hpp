@@ -514,14 +514,15 @@ __device__ __forceinline__ bool p2_near(const P2& p, const Sched& sc, int kind, 
     return true;
 }
 
+// Takes tickets until there are none (true) or the kernel must stop.
 template <int NW>
-__device__ inline void p2_run(const P2& p, const Sched& sc, double* smem, int* sh) {
+__device__ inline bool p2_run(const P2& p, const Sched& sc, double* smem, int* sh) {
     double* red = smem + P2Cfg<NW>::STAGE;
     const Lay& L = p.L;
     const int64_t N = L.nt;
     for (;;) {
         const int t = sched_next(sc, p.ntasks, &sh[0]);
-        if (t < 0) break;
+        if (t < 0) return true;   // (or an error, which every later wait meets)
         TRACE(t, 0, wall_clock64());
         int64_t q;
         int base;
@@ -572,7 +573,7 @@ __device__ inline void p2_run(const P2& p, const Sched& sc, double* smem, int* s
         } else {
             ok = p2_near<NW>(p, sc, kind, J, u, smem, red, &sh[1], t);
         }
-        if (!ok) break;
+        if (!ok) return false;
         sched_signal(sc, p.cnt + J * p2_ctr(L) + d, t);
         TRACE(t, 2, wall_clock64());
         TRACE(t, 3, (unsigned long long)kind | ((unsigned long long)J << 8) | ((unsigned long long)blockIdx.x << 40));

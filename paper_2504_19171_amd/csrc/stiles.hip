@@ -844,19 +844,49 @@ __global__ __launch_bounds__(NT) void kb_lauum(BArgs a) {
     lauum_body(selinv_ws(I.L, I.ws).W, I.L, I.S, I.L, bid, smem);
 }
 
-// Phase 2 of every matrix in one persistent launch: each matrix runs on its
-// own share of the workgroups, with its own tickets.
-__global__ __launch_bounds__(P2Cfg<4>::NTH, 2) void kb_phase2(BArgs a) {
-    __shared__ __attribute__((aligned(128))) double smem[P2Cfg<4>::SMEM];
+#define P2_WIDE_TASKS 512.0
+// Phase 2 of every matrix in one persistent launch: each matrix starts on its
+// own share of the workgroups, with its own tickets, and a workgroup whose
+// matrix has no tickets left joins the one with the most work left (tasks, times
+// the length of their sums).
+__device__ inline int p2_busiest(const BInst* bi, int count, int* sh) {
+    if (threadIdx.x < 64) {
+        float best = 0.0f;
+        int at = -1;
+        for (int k = threadIdx.x; k < count; k += 64) {
+            const BInst& I = bi[k];
+            const SelinvWs v = selinv_ws(I.L, I.ws);
+            const int left = ld_coh_i(v.err) == 0 ? I.p2_tasks - ld_coh_i(v.ticket) : 0;
+            const float work = (float)left * (float)(I.L.bt * I.L.b + I.L.ap + I.L.b);
+            if (left > 0 && work > best) { best = work; at = k; }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float ob = __shfl_xor(best, o);
+            const int oa = __shfl_xor(at, o);
+            if (ob > best || (ob == best && oa > at)) { best = ob; at = oa; }
+        }
+        if (threadIdx.x == 0) *sh = at;
+    }
+    __syncthreads();
+    const int k = __builtin_amdgcn_readfirstlane(*sh);
+    __syncthreads();   // read by all before it is written again
+    return k;
+}
+template <int NW>
+__global__ __launch_bounds__(P2Cfg<NW>::NTH, 2) void kb_phase2(BArgs a, int count) {
+    __shared__ __attribute__((aligned(128))) double smem[P2Cfg<NW>::SMEM];
     __shared__ int sh[2];
-    BATCH_DECODE(a, I, bid, nblk);
-    const SelinvWs v = selinv_ws(I.L, I.ws);
-    Sched sc;
-    sc.ticket = v.ticket;
-    sc.err = v.err;
-    sc.spin_limit = a.spin_limit;
-    sc.withhold = -1;
-    p2_run<4>(make_p2(I.S, I.L, v.W, I.L, v.flags, I.p2_tasks, 0), sc, smem, sh);
+    for (int k = a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst; k >= 0; k = p2_busiest(a.bi, count, &sh[1])) {
+        const BInst& I = a.bi[k];
+        const SelinvWs v = selinv_ws(I.L, I.ws);
+        Sched sc;
+        sc.ticket = v.ticket;
+        sc.err = v.err;
+        sc.spin_limit = a.spin_limit;
+        sc.withhold = -1;
+        if (!p2_run<NW>(make_p2(I.S, I.L, v.W, I.L, v.flags, I.p2_tasks, 0), sc, smem, sh)) return;
+    }
 }
 
 __global__ void kb_selinv_final(const BInst* bi) {
@@ -1863,11 +1893,19 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     t.start(segs.size());
     for (int k = 0; k < count; ++k) t.add(segs, k, (int)lauum_blocks(bi[k].L, 0));
     close(la);
+    // Eight wavefronts per workgroup (one per CU) when the matrices' tile
+    // columns together hold few tasks, so that their length counts, else four
+    // (two per CU).  Measured, eight against four: 170 to 360 tasks 0.36 / 0.42
+    // and 1.60 / 2.12 ms, 8 served matrices 8.5 / 9.0, 860 tasks the same, 830
+    // with longer sums 23.2 / 17.9, 1,730 1.76 / 1.39.
+    double column = 0.0;
+    for (int k = 0; k < count; ++k) column += (double)bi[k].p2_tasks / (double)bi[k].L.nt;
+    const bool wide = column <= P2_WIDE_TASKS;
     // Phase 2: the resident workgroups shared in proportion to the task
     // counts, at least one per matrix
     t.start(segs.size());
     {
-        const int64_t total = std::min<int64_t>(sum_tasks, P2Cfg<4>::WG_PER_CU * (int64_t)di.cus);
+        const int64_t total = std::min<int64_t>(sum_tasks, (wide ? P2Cfg<8>::WG_PER_CU : P2Cfg<4>::WG_PER_CU) * (int64_t)di.cus);
         for (int k = 0; k < count; ++k) {
             const int64_t want = total * bi[k].p2_tasks / std::max<int64_t>(1, sum_tasks);
             t.add(segs, k, (int)std::max<int64_t>(1, std::min<int64_t>(bi[k].p2_tasks, want)));
@@ -1889,7 +1927,8 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     LAUNCH(STILES_TK_PHASE1, kb_trtri, dim3((unsigned)tr.grid), dim3(NT), 0, st, args(tr));
     if (tm.grid > 0) LAUNCH(STILES_TK_PHASE1, kb_trmm, dim3((unsigned)tm.grid), dim3(NT), 0, st, args(tm));
     LAUNCH(STILES_TK_PHASE1, kb_lauum, dim3((unsigned)la.grid), dim3(NT), 0, st, args(la));
-    LAUNCH(STILES_TK_PHASE2, kb_phase2, dim3((unsigned)p2.grid), dim3(P2Cfg<4>::NTH), 0, st, args(p2));
+    if (wide) LAUNCH(STILES_TK_PHASE2, kb_phase2<8>, dim3((unsigned)p2.grid), dim3(P2Cfg<8>::NTH), 0, st, args(p2), (int)count);
+    else LAUNCH(STILES_TK_PHASE2, kb_phase2<4>, dim3((unsigned)p2.grid), dim3(P2Cfg<4>::NTH), 0, st, args(p2), (int)count);
     LAUNCH(STILES_TK_OTHER, kb_selinv_final, dim3(count), dim3(64), 0, st, dbi);
     return 0;
 }
