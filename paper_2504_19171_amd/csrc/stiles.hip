@@ -389,18 +389,19 @@ __device__ inline void fac_ticket(const FacCtx& x, int t, int& c, int& u) {
 
 // The band factor of one matrix in one persistent launch (factor.hpp): ticket
 // 0 is the chain, ticket 1 + t task t.
-__device__ inline void fac_run(const FacCtx& x, int ntask, const Sched& sc, FacSmem& sm, int* info) {
+// Until no tickets are left (true) or the kernel must stop.
+__device__ inline bool fac_run(const FacCtx& x, int ntask, const Sched& sc, FacSmem& sm, int* info) {
     if (threadIdx.x == 0) sm.dead = 0;
     for (;;) {
         const int g = sched_next(sc, 1 + ntask, &sm.sh);
-        if (g < 0) return;
+        if (g < 0) return true;
         if (g == 0) {
-            if (!fac_chain(x, sc, sm, 0, x.nc, info, g == sc.withhold)) return;
+            if (!fac_chain(x, sc, sm, 0, x.nc, info, g == sc.withhold)) return false;
             continue;
         }
         int c, u;
         fac_ticket(x, g - 1, c, u);
-        if (!fac_task(x, sc, sm, c, u, g)) return;
+        if (!fac_task(x, sc, sm, c, u, g)) return false;
     }
 }
 __global__ __launch_bounds__(FAC_NT, 2) void k_factor_all(FacCtx x, int ntask, Sched sc, int* info) {
@@ -672,6 +673,7 @@ struct BInst {
     double* logdet;
     int* info;        // [0] factor, [1] selinv
     char* ws;         // this matrix's workspace (factor or selinv layout)
+    int fac_ntask;    // factor task count
     int p2_tasks;     // Phase 2 task count
     int nparts;       // log det partial pairs (tile columns + corner blocks)
 };
@@ -715,67 +717,58 @@ __global__ __launch_bounds__(NT) void kb_factor_setup(const BInst* bi) {
     factor_setup_body(I.L, factor_ws(I.L, I.ws), threadIdx.x + (int64_t)(blockIdx.x & 7) * NT, 8 * NT);
 }
 
-// Chunks c0 .. c0 + ncol - 1 (64 columns each) of the matrices [m0, m1) of the
-// batch's order (decreasing chunk count, so those that still have a chunk c
-// come first) in one launch.  The first tickets are the chains, one per
-// matrix; then every group's tasks chunk after chunk, matrix after matrix.
-// Each matrix's tasks keep their order, so a task waits only for smaller
-// tickets and chains.  A chain goes on from where the launch before left it.
-// At most KB_SLICE matrices share a launch, so that the chains never take
-// more than half of its workgroups.
-#define KB_COL_MAX 64        // chunks per launch, at most
+// The matrix [k0, k1) with the most work left (of each, left and its weight:
+// work(k, left, weight)), or -1.
+template <class F>
+__device__ inline int batch_busiest(int k0, int k1, int* sh, F&& work) {
+    if (threadIdx.x < 64) {
+        float best = 0.0f;
+        int at = -1;
+        for (int k = k0 + threadIdx.x; k < k1; k += 64) {
+            const float w = work(k);
+            if (w > best) { best = w; at = k; }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float ob = __shfl_xor(best, o);
+            const int oa = __shfl_xor(at, o);
+            if (ob > best || (ob == best && oa > at)) { best = ob; at = oa; }
+        }
+        if (threadIdx.x == 0) *sh = at;
+    }
+    __syncthreads();
+    const int k = __builtin_amdgcn_readfirstlane(*sh);
+    __syncthreads();   // read by all before it is written again
+    return k;
+}
+
+// The band factors of matrices [k0, k1), at most KB_SLICE a launch: each starts
+// on its own share of the workgroups (two or more), with its own tickets, the
+// first of which is its chain.  (With one queue over all matrices, chunk after
+// chunk, in 97 launches, 64 matrices took 22.3 ms; this takes 14.3.)  A
+// workgroup whose matrix has no tickets left
+// joins the one with the most work left (tasks, times the length of their sums)
+// among those whose chain is under way: so no workgroup becomes a chain that
+// waits for others that have all become chains too.
 #define KB_SLICE 128
-struct BFacArgs {
-    const BInst* bi;
-    const int* ints;                 // the queue tables
-    int order_at;                    // ints + order_at: the matrices in order
-    int m0, m1;
-    int c0, ncol;
-    int tb[KB_COL_MAX + 1];          // first ticket of each chunk; tb[0]: the chains; tb[ncol]: all
-    int pre_at[KB_COL_MAX];          // ints + pre_at[g]: tasks of the matrices before each, in chunk c0 + g
-    int act[KB_COL_MAX];             // matrices of the slice that have chunk c0 + g
-    int* ticket;
-    int* err;                        // the batch's error word
-    int64_t spin_limit;
-};
-__global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BFacArgs a) {
+__global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BArgs a, int k0, int k1, int* err) {
     __shared__ FacSmem sm;
-    if (threadIdx.x == 0) sm.dead = 0;
-    Sched sc;
-    sc.ticket = a.ticket;
-    sc.err = a.err;
-    sc.spin_limit = a.spin_limit;
-    sc.withhold = -1;
-    for (;;) {
-        const int g = sched_next(sc, a.tb[a.ncol], &sm.sh);
-        if (g < 0) return;
-        int m, c = a.c0, u = 0;
-        if (g < a.tb[0]) {
-            m = a.m0 + g;
-        } else {
-            int e = 0;
-            while (e + 1 < a.ncol && g >= a.tb[e + 1]) ++e;
-            c = a.c0 + e;
-            // the matrix: entries of the prefix sums at or below the ticket,
-            // 64 at a time
-            const int* pre = a.ints + a.pre_at[e] + a.m0;
-            const int lane = threadIdx.x & 63, n = a.act[e];
-            const int want = g - a.tb[e] + pre[0];
-            int k = 0;
-            for (int j = 0; j < n; j += 64)
-                k += __popcll(__ballot(j + lane < n && pre[imin_(j + lane, n - 1) + 1] <= want));
-            k = imin_(k, n - 1);
-            m = a.m0 + k;
-            u = want - pre[k];
-        }
-        const BInst& I = a.bi[a.ints[a.order_at + m]];
+    for (int k = a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst; k >= 0;) {
+        const BInst& I = a.bi[k];
         const FactorWs f = factor_ws(I.L, I.ws);
+        Sched sc;
+        sc.ticket = f.ticket;
+        sc.err = err;
+        sc.spin_limit = a.spin_limit;
+        sc.withhold = -1;
         const FacCtx x = fac_ctx(I.L, I.Lm, f.Yd, f.flags);
-        if (g < a.tb[0]) {
-            if (!fac_chain(x, sc, sm, a.c0, imin_(a.c0 + a.ncol, x.nc), f.winfo, false)) return;
-        } else if (!fac_task(x, sc, sm, c, u, g)) {
-            return;
-        }
+        if (!fac_run(x, I.fac_ntask, sc, sm, f.winfo)) return;
+        if (ld_coh_i(err) != 0) return;
+        k = batch_busiest(k0, k1, &sm.sh, [&](int m) {
+            const BInst& M = a.bi[m];
+            const int t = ld_coh_i(factor_ws(M.L, M.ws).ticket), left = 1 + M.fac_ntask - t;
+            return t > 0 && left > 0 ? (float)left * (float)(fac_wc(M.L) + 4) : 0.0f;
+        });
     }
 }
 
@@ -849,35 +842,11 @@ __global__ __launch_bounds__(NT) void kb_lauum(BArgs a) {
 // own share of the workgroups, with its own tickets, and a workgroup whose
 // matrix has no tickets left joins the one with the most work left (tasks, times
 // the length of their sums).
-__device__ inline int p2_busiest(const BInst* bi, int count, int* sh) {
-    if (threadIdx.x < 64) {
-        float best = 0.0f;
-        int at = -1;
-        for (int k = threadIdx.x; k < count; k += 64) {
-            const BInst& I = bi[k];
-            const SelinvWs v = selinv_ws(I.L, I.ws);
-            const int left = ld_coh_i(v.err) == 0 ? I.p2_tasks - ld_coh_i(v.ticket) : 0;
-            const float work = (float)left * (float)(I.L.bt * I.L.b + I.L.ap + I.L.b);
-            if (left > 0 && work > best) { best = work; at = k; }
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ob = __shfl_xor(best, o);
-            const int oa = __shfl_xor(at, o);
-            if (ob > best || (ob == best && oa > at)) { best = ob; at = oa; }
-        }
-        if (threadIdx.x == 0) *sh = at;
-    }
-    __syncthreads();
-    const int k = __builtin_amdgcn_readfirstlane(*sh);
-    __syncthreads();   // read by all before it is written again
-    return k;
-}
 template <int NW>
 __global__ __launch_bounds__(P2Cfg<NW>::NTH, 2) void kb_phase2(BArgs a, int count) {
     __shared__ __attribute__((aligned(128))) double smem[P2Cfg<NW>::SMEM];
     __shared__ int sh[2];
-    for (int k = a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst; k >= 0; k = p2_busiest(a.bi, count, &sh[1])) {
+    for (int k = a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst; k >= 0;) {
         const BInst& I = a.bi[k];
         const SelinvWs v = selinv_ws(I.L, I.ws);
         Sched sc;
@@ -886,6 +855,12 @@ __global__ __launch_bounds__(P2Cfg<NW>::NTH, 2) void kb_phase2(BArgs a, int coun
         sc.spin_limit = a.spin_limit;
         sc.withhold = -1;
         if (!p2_run<NW>(make_p2(I.S, I.L, v.W, I.L, v.flags, I.p2_tasks, 0), sc, smem, sh)) return;
+        k = batch_busiest(0, count, &sh[1], [&](int m) {
+            const BInst& M = a.bi[m];
+            const SelinvWs u = selinv_ws(M.L, M.ws);
+            const int left = ld_coh_i(u.err) == 0 ? M.p2_tasks - ld_coh_i(u.ticket) : 0;
+            return left > 0 ? (float)left * (float)(M.L.bt * M.L.b + M.L.ap + M.L.b) : 0.0f;
+        });
     }
 }
 
@@ -1154,19 +1129,6 @@ static int64_t spin_limit_ticks(const DevInfo& di) {
     return (int64_t)(ms * (double)di.clock_khz);
 }
 
-// Chunks (64 columns) per batched factor launch.  STILES_KB_COLS (1 .. 16)
-// sets it in tile columns of the batch's largest tile.  A launch's fixed cost
-// asks for long ones, the wait for its slowest matrix for short ones when
-// there are many: 64 matrices took 22.7 / 24.4 / 25.7 ms with 8 / 16 / 32
-// chunks, 8 matrices 16.1 / 11.2 / 10.6 ms with 4 / 16 / 32.
-static int kb_chunks_per_launch(int maxb, int count) {
-    if (const char* e = getenv("STILES_KB_COLS")) {
-        const int v = atoi(e);
-        if (v >= 1 && v <= 16) return std::min(v * (maxb / FC), KB_COL_MAX);
-    }
-    return std::max(8, std::min(32, 512 / std::max(count, 1)));
-}
-
 static int debug_withhold() {
     if (const char* e = getenv("STILES_DEBUG_WITHHOLD")) return atoi(e);
     return -1;
@@ -1219,7 +1181,6 @@ struct BPlan {
     size_t table_f = 0;        // bytes of the factor's table area (at the start of the workspace)
     size_t table = 0;          // bytes of both table areas (the selected inverse's follows the factor's)
     size_t total = 0;
-    int64_t maxC = 0;          // most chunks of a matrix
 };
 // factor workspace (FactorWs): head (info, error words) + log det partials
 // (N + 2 pairs) + the corner's tiles and diagonal-block inverses + the 16 x 16
@@ -1238,27 +1199,23 @@ static size_t fws_bytes(const stiles_layout& l) {
 static size_t sws_bytes(const stiles_layout& l) {
     return WS_HEAD + sizeof(double) * (size_t)l.total_doubles + sizeof(int) * (size_t)((l.bt + 2) * l.nt);
 }
+static size_t batch_nseg(int count) {
+    return 6 * ((size_t)count + 1) + ((size_t)count + KB_SLICE - 1) / KB_SLICE;
+}
 static int batch_plan(const stiles_batch_item* items, int count, bool need_sigma, BPlan& pl) {
     pl.lay.resize(count);
     pl.off.resize(count);
-    int64_t sumC = 0;
     for (int k = 0; k < count; ++k) {
         const stiles_batch_item& it = items[k];
         if (make_layout(it.n, it.bandwidth, it.arrow, it.tile, &pl.lay[k])) return -1;
         if (it.reserved != 0 || !it.A || !it.L || !it.logdet || !it.info) return -1;
         if (need_sigma && (!it.Sigma || it.Sigma == it.L)) return -1;
         if (need_sigma && p2_total_tasks(to_dev(pl.lay[k])) > 0x7fffffff) return -1;
-        const int64_t nc = fac_chunks(to_dev(pl.lay[k]));
-        sumC += nc;
-        pl.maxC = std::max(pl.maxC, nc);
     }
-    // segment tables of at most six per-matrix launches; ints: the error
-    // word, a ticket per factor launch (at most one per chunk
-    // and slice), and the queue tables (the order, then per chunk the prefix
-    // sums over the matrices that have it)
-    const size_t nseg = 6 * ((size_t)count + 1);
-    const size_t slices = ((size_t)count + KB_SLICE - 1) / KB_SLICE;
-    const size_t nint = 1 + (size_t)pl.maxC * slices + (size_t)count + (size_t)sumC + (size_t)pl.maxC;
+    // segment tables of at most six per-matrix launches and a sentinel per
+    // launch of the factor; ints: the error word
+    const size_t nseg = batch_nseg(count);
+    const size_t nint = 1;
     pl.table_f = align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg) + align256(sizeof(int) * nint);
     pl.table = pl.table_f + align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg);
     size_t o = pl.table;
@@ -1691,7 +1648,7 @@ static int pinned_upload(void* dst, const void* src, size_t n, hipStream_t st) {
 
 static int batch_upload(const std::vector<BInst>& bi, const std::vector<BSeg>& segs, const std::vector<int>& idx,
                         char* ws, hipStream_t st) {
-    const size_t o1 = align256(sizeof(BInst) * bi.size()), o2 = o1 + align256(sizeof(BSeg) * 6 * (bi.size() + 1));
+    const size_t o1 = align256(sizeof(BInst) * bi.size()), o2 = o1 + align256(sizeof(BSeg) * batch_nseg((int)bi.size()));
     std::vector<char> h(o2 + sizeof(int) * idx.size());
     memcpy(h.data(), bi.data(), sizeof(BInst) * bi.size());
     memcpy(h.data() + o1, segs.data(), sizeof(BSeg) * segs.size());
@@ -1728,9 +1685,12 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
         I.info = items[k].info;
         I.ws = ws + pl.off[k];
         I.nparts = factor_nparts(I.L);
+        const int64_t n = fac_tasks(fac_ctx(I.L, nullptr, nullptr, nullptr));
+        if (n >= 0x7fffffff) return -1;
+        I.fac_ntask = (int)n;
     }
     const size_t seg0 = align256(sizeof(BInst) * (size_t)count);
-    const size_t int0 = seg0 + align256(sizeof(BSeg) * 6 * ((size_t)count + 1));
+    const size_t int0 = seg0 + align256(sizeof(BSeg) * batch_nseg(count));
     std::vector<BSeg> segs;
     SegTab t;
     t.start(segs.size());
@@ -1747,36 +1707,23 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     for (int k = 0; k < count; ++k)
         if (bi[k].L.ap > 0) t.add(segs, k, corner_out_blocks(bi[k].L));
     close(corner_back);
-    // ints: the error word, then one ticket per factor launch (zero as
-    // uploaded), then the queue tables
-    const int slices = (count + KB_SLICE - 1) / KB_SLICE;
-    const size_t nticket = (size_t)pl.maxC * slices;
-    std::vector<int> ints(1 + nticket, 0);
-    const size_t err_at = 0, tick_at = 1;
-    std::vector<FacCtx> fx(count);
-    for (int k = 0; k < count; ++k) fx[k] = fac_ctx(bi[k].L, nullptr, nullptr, nullptr);
-    const size_t order_at = ints.size();
-    std::vector<int> order(count);
-    for (int k = 0; k < count; ++k) order[k] = k;
-    std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return fx[p].nc > fx[q].nc; });
-    ints.insert(ints.end(), order.begin(), order.end());
-    std::vector<size_t> pre_at(pl.maxC);
-    std::vector<int> act(pl.maxC);
-    {
-        int n = count;
-        for (int64_t c = 0; c < pl.maxC; ++c) {
-            while (n > 0 && fx[order[n - 1]].nc <= c) --n;
-            act[c] = n;
-            pre_at[c] = ints.size();
-            int64_t acc = 0;
-            ints.push_back(0);
-            for (int m = 0; m < n; ++m) {
-                acc += fac_group(fx[order[m]], (int)c);
-                if (acc > 0x7fffffff / KB_COL_MAX) return -1;
-                ints.push_back((int)acc);
-            }
+    // the factor: the resident workgroups shared in proportion to the tasks,
+    // at least two per matrix (one when it has no tasks)
+    std::vector<Launch> fac;
+    for (int k0 = 0; k0 < count; k0 += KB_SLICE) {
+        const int k1 = std::min(count, k0 + KB_SLICE);
+        int64_t sum = 0;
+        for (int k = k0; k < k1; ++k) sum += bi[k].fac_ntask;
+        t.start(segs.size());
+        for (int k = k0; k < k1; ++k) {
+            const int64_t n = bi[k].fac_ntask, want = 2 * (int64_t)di.cus * n / std::max<int64_t>(1, sum);
+            t.add(segs, k, (int)std::min<int64_t>(1 + n, std::max<int64_t>(2, want)));
         }
+        Launch l;
+        close(l);
+        fac.push_back(l);
     }
+    const std::vector<int> ints(1, 0);   // the error word
     int rc = 0;
     if (mode & BATCH_UPLOAD) {
         rc = batch_upload(bi, segs, ints, ws, st);
@@ -1788,9 +1735,7 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     int* dint = (int*)(ws + int0);
     const int64_t spin = spin_limit_ticks(di);
 
-    // the error word and the launches' tickets start at zero on every run
-    LAUNCH(STILES_TK_OTHER, k_zero_ints, dim3(grid_for(1 + (int64_t)nticket)), dim3(NT), 0, st, dint + err_at,
-           1 + (int64_t)nticket);
+    LAUNCH(STILES_TK_OTHER, k_zero_ints, dim3(1), dim3(NT), 0, st, dint, (int64_t)1);
     for (int k = 0; k < count; ++k) {
         if (bi[k].A == bi[k].Lm) continue;
         hipEvent_t tm = tm_begin(st);
@@ -1798,44 +1743,16 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
         tm_end(tm, STILES_TK_OTHER, st);
     }
     LAUNCH(STILES_TK_OTHER, kb_factor_setup, dim3((unsigned)(8 * count)), dim3(NT), 0, st, dbi);
-    int maxb = 0;
-    for (int k = 0; k < count; ++k) maxb = std::max(maxb, bi[k].L.b);
-    const int cols = kb_chunks_per_launch(maxb, count);
-    int launch = 0;
-    for (int64_t c0 = 0; c0 < pl.maxC; c0 += cols) {
-        for (int m0 = 0; m0 < act[c0]; m0 += KB_SLICE) {
-            BFacArgs a;
-            memset(&a, 0, sizeof(a));
-            a.bi = dbi;
-            a.ints = dint;
-            a.order_at = (int)order_at;
-            a.m0 = m0;
-            a.m1 = std::min(m0 + KB_SLICE, act[c0]);
-            a.c0 = (int)c0;
-            a.ncol = (int)std::min<int64_t>(cols, pl.maxC - c0);
-            int64_t ntot = a.tb[0] = a.m1 - m0;
-            for (int g = 0; g < a.ncol; ++g) {
-                const int c = (int)c0 + g, me = std::min(a.m1, act[c]);
-                a.pre_at[g] = (int)pre_at[c];
-                a.act[g] = std::max(0, me - m0);
-                if (a.act[g] > 0) ntot += ints[pre_at[c] + me] - ints[pre_at[c] + m0];
-                a.tb[g + 1] = (int)ntot;
-            }
-            if (ntot > 0x7fffffff) return -1;
-            a.ticket = dint + tick_at + launch++;
-            a.err = dint + err_at;
-            a.spin_limit = spin;
-            LAUNCH(STILES_TK_FACTOR, kb_factor, dim3((unsigned)std::min<int64_t>(ntot, 2 * (int64_t)di.cus)), dim3(FAC_NT), 0,
-                   st, a);
-        }
-    }
     auto args = [&](const Launch& l) { return BArgs{dbi, dseg + l.at, l.n, spin}; };
+    for (size_t q = 0; q < fac.size(); ++q)
+        LAUNCH(STILES_TK_FACTOR, kb_factor, dim3((unsigned)fac[q].grid), dim3(FAC_NT), 0, st, args(fac[q]),
+               (int)q * KB_SLICE, std::min<int>(count, ((int)q + 1) * KB_SLICE), dint);
     LAUNCH(STILES_TK_OTHER, kb_factor_tail, dim3((unsigned)tail.grid), dim3(NT), 0, st, args(tail));
     if (corner.grid > 0) {
-        LAUNCH(STILES_TK_POTRF, kb_corner, dim3((unsigned)corner.grid), dim3(FAC_NT), 0, st, args(corner), dint + err_at);
+        LAUNCH(STILES_TK_POTRF, kb_corner, dim3((unsigned)corner.grid), dim3(FAC_NT), 0, st, args(corner), dint);
         LAUNCH(STILES_TK_OTHER, kb_corner_out, dim3((unsigned)corner_back.grid), dim3(NT), 0, st, args(corner_back));
     }
-    LAUNCH(STILES_TK_OTHER, kb_factor_final, dim3(count), dim3(64), 0, st, dbi, (const int*)(dint + err_at));
+    LAUNCH(STILES_TK_OTHER, kb_factor_final, dim3(count), dim3(64), 0, st, dbi, (const int*)dint);
     return 0;
 }
 
