@@ -244,8 +244,8 @@ __device__ __forceinline__ void far_landed(int later) {
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// The products of one stage; issue() in their midst (its address arithmetic
-// runs beside the matrix cores).
+// The products of one stage; issue() in their midst (its arithmetic runs beside
+// the matrix cores).
 struct FarAddr {
     uint32_t x0, x1, k0, k1, b0, b1;   // operands in stage 0: Sigma along x, along k; Lhat (along k)
 };
@@ -470,9 +470,12 @@ __device__ __forceinline__ bool p2_near(const P2& p, const Sched& sc, int kind, 
         f = p2_counter(p, J, e);
         t = p2_target(L, e);
     };
-    const int e2 = row ? imin_(s, 1) : imin_(s, 2);   // part two: tile offsets e2 .. 1
     // two parts: ROW the tiles from J+2 on and the arrow, then J+1; DIAG the
-    // arrow and the tiles from J+3 on, then J+2 and J+1
+    // arrow and the tiles from J+3 on, then J+2 and J+1, as FAR(J) ends on row
+    // tile J+2 - but with fewer than three band tiles below, FAR(J) is early and
+    // J+2 belongs to part one (nb 6,000, w 256, tile 128: 564 against 601 us;
+    // w 553 1.92 against 1.98 ms the other way)
+    const int e2 = imin_(s, !row && s >= 3 ? 2 : 1);   // part two: tile offsets e2 .. 1
     const int n1 = s - e2 + karw;
     auto off1 = [&](int q) { return q < karw ? ARW : s - (q - karw); };
     auto len = [&](int e) { return e == p.btw ? p.klast : L.b; };

@@ -107,17 +107,18 @@ __device__ __forceinline__ void wave_sum(dbl4 (&acc0)[2][2], dbl4 (&acc1)[2][2],
     const uint32_t s0 = lds_addr(sw);
     const uint32_t r0 = wg_at(li), r1 = wg_at(li + 16);
     // the next chunk to issue: piece, its k up to ke, the term and where it starts
-    int pc = w - NW, k = 0, ke = 0, q = -1, t0 = 0, t1 = 0;
+    int pc = w, k = imin_(per * w, ktot), ke = imin_(per * (w + 1), ktot), q = -1, t0 = 0, t1 = 0;
     const double *pa = nullptr, *pb = nullptr;
     uint32_t oa[4], ob[4];
     int left = 0, wr = 0, rd = 0;
     unsigned second = 0;   // bit i: the i-th chunk in flight is of the second piece
     auto issue = [&]() {
-        while (k >= ke) {
+        if (k >= ke) {
+            if (pc + NW >= WG_PIECES) return;
             pc += NW;
-            if (pc >= WG_PIECES) return;
             k = imin_(per * pc, ktot);
             ke = imin_(per * (pc + 1), ktot);
+            if (k >= ke) return;
         }
         if (k >= t1) {
             int K = 0;
