@@ -34,6 +34,7 @@
 #include "common.hpp"
 #include "persist.hpp"
 #include "wave_gemm.hpp"
+#include "factor.hpp"
 
 #define ARW (-1)   // "the arrow" in place of a band tile offset
 
@@ -143,9 +144,10 @@ __device__ inline void p2_sigma_dep(const P2& p, int64_t J, int d, int e, const 
 
 // How many of the n operands q = 0 .. n-1 (dep(q, counter, target)) are ready,
 // from the first on; waits for `need` of them.  At most 64 are looked at.
-// 0: the kernel must stop.
-template <class F>
-__device__ inline int p2_ready(const Sched& sc, int n, int need, int* sh, F&& dep) {
+// 0: the kernel must stop.  meanwhile() is called once by every wavefront, by
+// the one that looks after its first look; its loads may be in flight on return.
+template <class F, class G>
+__device__ inline int p2_ready(const Sched& sc, int n, int need, int* sh, F&& dep, G&& meanwhile) {
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
         const int lane = threadIdx.x & 63, m = imin_(n, 64);
         const int* f;
@@ -156,6 +158,7 @@ __device__ inline int p2_ready(const Sched& sc, int n, int need, int* sh, F&& de
         for (unsigned polls = 0;; ++polls) {
             const uint64_t b = __ballot(ld_coh_i(f) >= target);
             k = ~b == 0 ? m : imin_(m, (int)__builtin_ctzll(~b));
+            if (polls == 0) meanwhile();
             if (k >= need) break;
             if (t0 < 0) t0 = wall_clock64();
             if ((polls & 15) == 15) {
@@ -168,18 +171,23 @@ __device__ inline int p2_ready(const Sched& sc, int n, int need, int* sh, F&& de
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        if (lane == 0) *sh = k;
+        if (lane == 0) fac_lds_set(sh, k);
+    } else {
+        meanwhile();
     }
-    __syncthreads();
-    return __builtin_amdgcn_readfirstlane(*sh);
+    // (not __syncthreads, which would wait for meanwhile()'s loads)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    return __builtin_amdgcn_readfirstlane(fac_lds_get(sh));
 }
 // All n of them, any number.
-template <class F>
-__device__ inline bool p2_all_ready(const Sched& sc, int n, int* sh, F&& dep) {
+template <class F, class G>
+__device__ inline bool p2_all_ready(const Sched& sc, int n, int* sh, F&& dep, G&& meanwhile) {
     for (int q = 0; q < n; q += 64) {
         const int m = imin_(n - q, 64);
-        if (p2_ready(sc, m, m, sh, [&](int e, const int*& f, int& t) { dep(q + e, f, t); }) == 0) return false;
-        __syncthreads();   // *sh has been read by all
+        const int k = p2_ready(sc, m, m, sh, [&](int e, const int*& f, int& t) { dep(q + e, f, t); },
+                               [&]() { if (q == 0) meanwhile(); });
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // *sh has been read by all
+        if (k == 0) return false;
     }
     return true;
 }
@@ -363,7 +371,7 @@ __device__ __forceinline__ bool p2_far(const P2& p, const Sched& sc, int64_t J, 
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = acc1[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
     for (int q = 0; q < n;) {
-        const int m = p2_ready(sc, n - q, 1, sh, [&](int e, const int*& f, int& t) { p2_sigma_dep(p, J, d, term(q + e), f, t); });
+        const int m = p2_ready(sc, n - q, 1, sh, [&](int e, const int*& f, int& t) { p2_sigma_dep(p, J, d, term(q + e), f, t); }, []() {});
         if (m == 0) return false;
         if (q == 0) TRACE(t, 1, wall_clock64());
         if (q + m == n) TRACE(t, 5, wall_clock64());
@@ -480,16 +488,17 @@ __device__ __forceinline__ bool p2_near(const P2& p, const Sched& sc, int kind, 
     auto off1 = [&](int q) { return q < karw ? ARW : s - (q - karw); };
     auto len = [&](int e) { return e == p.btw ? p.klast : L.b; };
     if (n1 > 0) {
-        if (!p2_all_ready(sc, n1, sh, [&](int q, const int*& f, int& t) { dep(off1(q), f, t); })) return false;
-        TRACE(t, 1, wall_clock64());
         const int klen = L.ap + (s > e2 ? (s - e2 - 1) * L.b + len(s) : 0);
-        wave_sum<NW>(acc, acc1, n1, klen, sw, [&](int q) { return term(off1(q)); });
+        if (!wave_sum<NW>(acc, acc1, n1, klen, sw, [&](int q) { return term(off1(q)); }, [&](auto&& pre) {
+                return p2_all_ready(sc, n1, sh, [&](int q, const int*& f, int& t) { dep(off1(q), f, t); }, pre);
+            }))
+            return false;
     }
-    TRACE(t, 4, wall_clock64());
     if (e2 > 0) {
-        if (!p2_all_ready(sc, e2, sh, [&](int q, const int*& f, int& t) { dep(e2 - q, f, t); })) return false;
-        TRACE(t, 5, wall_clock64());
-        wave_sum<NW>(acc, acc1, e2, len(1) + (e2 > 1 ? len(2) : 0), sw, [&](int q) { return term(e2 - q); });
+        if (!wave_sum<NW>(acc, acc1, e2, len(1) + (e2 > 1 ? len(2) : 0), sw, [&](int q) { return term(e2 - q); }, [&](auto&& pre) {
+                return p2_all_ready(sc, e2, sh, [&](int q, const int*& f, int& t) { dep(e2 - q, f, t); }, pre);
+            }))
+            return false;
     }
     if (NW != 8)
 #pragma unroll

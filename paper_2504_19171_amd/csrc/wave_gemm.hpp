@@ -91,6 +91,7 @@ struct Seg {
 // s_waitcnt immediates, gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt in
 // 6:4, lgkmcnt in 11:8; a counter at its maximum is not waited for.
 #define WG_VMCNT8 0x0F78
+#define WG_VMCNT4 0x0F74
 #define WG_VMCNT0 0x0F70
 
 // acc0 (and acc1, with four wavefronts) += this wavefront's piece(s) w (and w +
@@ -99,8 +100,13 @@ struct Seg {
 // pieces are one stream, two in flight; the vmcnt waits assume no other memory
 // access of this wavefront in between (loads issued before are older and
 // complete first).
-template <int NW, class F>
-__device__ __forceinline__ void wave_sum(dbl4 (&acc0)[2][2], dbl4 (&acc1)[2][2], int nseg, int ktot, double* sw, F&& seg) {
+// gate(pre) waits until A may be read, false if it never may; pre() issues the
+// first loads of B meanwhile (B lies farther away than A, which has just been
+// written).
+template <int NW, class F, class G>
+__device__ __forceinline__ bool wave_sum(dbl4 (&acc0)[2][2], dbl4 (&acc1)[2][2], int nseg, int ktot, double* sw, F&& seg,
+                                         G&& gate) {
+    if (NW < 8 && !gate([]() {})) return false;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = threadIdx.x & 15;
     const int per = 16 * (((ktot >> 4) + WG_PIECES - 1) / WG_PIECES);
@@ -112,13 +118,13 @@ __device__ __forceinline__ void wave_sum(dbl4 (&acc0)[2][2], dbl4 (&acc1)[2][2],
     uint32_t oa[4], ob[4];
     int left = 0, wr = 0, rd = 0;
     unsigned second = 0;   // bit i: the i-th chunk in flight is of the second piece
-    auto issue = [&]() {
+    auto there = [&]() {   // is there a chunk at k (of the next piece, if this one is done)
         if (k >= ke) {
-            if (pc + NW >= WG_PIECES) return;
+            if (pc + NW >= WG_PIECES) return false;
             pc += NW;
             k = imin_(per * pc, ktot);
             ke = imin_(per * (pc + 1), ktot);
-            if (k >= ke) return;
+            if (k >= ke) return false;
         }
         if (k >= t1) {
             int K = 0;
@@ -137,25 +143,66 @@ __device__ __forceinline__ void wave_sum(dbl4 (&acc0)[2][2], dbl4 (&acc1)[2][2],
                 ob[i] = wg_lane(g.ldb, i) << 3;
             }
         }
-        double* st = sw + wr * WG_CHUNK;
+        return true;
+    };
+    auto load_a = [&](int at, int buf) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            __builtin_amdgcn_global_load_lds((const void*)((const char*)(pa + (k - t0)) + oa[i]), (lds_void_t*)(st + 128 * i), 16,
-                                             0, 16);
+            __builtin_amdgcn_global_load_lds((const void*)((const char*)(pa + (at - t0)) + oa[i]),
+                                             (lds_void_t*)(sw + buf * WG_CHUNK + 128 * i), 16, 0, 16);
+    };
+    auto load_b = [&](int at, int buf) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            __builtin_amdgcn_global_load_lds((const void*)((const char*)(pb + (k - t0)) + ob[i]),
-                                             (lds_void_t*)(st + 512 + 128 * i), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const void*)((const char*)(pb + (at - t0)) + ob[i]),
+                                             (lds_void_t*)(sw + buf * WG_CHUNK + 512 + 128 * i), 16, 0, 0);
+    };
+    auto issued = [&]() {
         if (NW < 8) second |= (unsigned)(pc >= NW) << left;
         ++left;
         wr ^= 1;
         k += 16;
     };
-    issue();
-    issue();
+    auto issue = [&]() {
+        if (!there()) return;
+        load_a(k, wr);
+        load_b(k, wr);
+        issued();
+    };
+    // with eight wavefronts: chunks whose B is on its way (the second only
+    // beside the first).  (With four the CU's other workgroup has work for the
+    // time: 64 matrices 17.6 ms without, 19.4 with.)
+    int early = 0;
+    if (NW == 8 && !gate([&]() {
+            if (!there()) return;
+            load_b(k, 0);
+            early = 1;
+            if (k + 16 >= imin_(ke, t1)) return;
+            load_b(k + 16, 1);
+            early = 2;
+        })) {
+        __builtin_amdgcn_s_waitcnt(WG_VMCNT0);   // no load into LDS outlives the workgroup
+        return false;
+    }
+    if (NW == 8) early = __builtin_amdgcn_readfirstlane(early);
+    if (NW == 8 && early > 0) {
+        load_a(k, 0);
+        issued();
+        if (early > 1) {
+            load_a(k, 1);
+            issued();
+        } else {
+            issue();
+        }
+    } else if (NW < 8) {
+        issue();
+        issue();
+    }
     while (left > 0) {
-        if (left > 1) __builtin_amdgcn_s_waitcnt(WG_VMCNT8);
-        else __builtin_amdgcn_s_waitcnt(WG_VMCNT0);
+        if (left == 1) __builtin_amdgcn_s_waitcnt(WG_VMCNT0);
+        else if (NW == 8 && early > 1) __builtin_amdgcn_s_waitcnt(WG_VMCNT4);   // only the second chunk's A is younger
+        else __builtin_amdgcn_s_waitcnt(WG_VMCNT8);
+        early = 0;
         __builtin_amdgcn_wave_barrier();
         wg2 a[2][2], b[2][2];
         const uint32_t st = s0 + (uint32_t)rd * (WG_CHUNK * 8u);
@@ -181,6 +228,7 @@ __device__ __forceinline__ void wave_sum(dbl4 (&acc0)[2][2], dbl4 (&acc1)[2][2],
         if (!two) mma(acc0);
         else mma(acc1);
     }
+    return true;
 }
 
 #define WR_LD 33
