@@ -879,33 +879,51 @@ __global__ void kb_selinv_final(const BInst* bi) {
 // triangles (weight 1 each), a band tile below the diagonal and an arrow tile
 // the strictly lower part (weight 2: the upper part mirrors it); padding
 // (rows or columns past nb in the band, past a in the arrow) is left out.
-// Block g of TP_BLOCKS sums a contiguous range of the buffer in a fixed order
-// into part[g]; k_trace_final adds the parts in order (Neumaier), so the
+// The buffer is one tile column after another (of b or a_p doubles), so each of
+// the TP_BLOCKS workgroups' wavefronts takes every TP_WAVES-th of them, in a
+// fixed order, and works out its place once (element by element the divisions
+// bounded the pass: 1.07 ms where reading both buffers, 1.9 GB each, takes
+// 0.72); k_trace_final adds the parts (compensated, in a fixed order), so the
 // result does not depend on timing.
 #define TP_BLOCKS 1024
+#define TP_WAVES (TP_BLOCKS * (NT / 64))
 __global__ __launch_bounds__(NT) void k_trace_part(const double* __restrict__ S, const double* __restrict__ B, Lay L,
                                                    double* part) {
     __shared__ double red[NT];
-    const int64_t per = (L.total + TP_BLOCKS - 1) / TP_BLOCKS;
-    const int64_t lo = blockIdx.x * per, hi = std::min<int64_t>(L.total, lo + per);
-    const int64_t b = L.b, b2 = b * b;
+    const int lane = threadIdx.x & 63;
+    const int64_t per = (int64_t)(L.bt + 1) * L.b;   // columns of a tile column's band tiles
+    const int64_t nband = L.nt * per, narrow = L.ap > 0 ? L.nt * (int64_t)L.b : 0, n = nband + narrow + L.ap;
     double acc = 0.0;
-    for (int64_t idx = lo + threadIdx.x; idx < hi; idx += NT) {
-        double wgt = 0.0;
-        if (idx < L.off_arrow) {
-            const int64_t t = idx / b2, e = idx % b2;
-            const int64_t J = t / (L.bt + 1), d = t % (L.bt + 1);
-            const int64_t i = (J + d) * b + e % b, j = J * b + e / b;
-            if (J + d < L.nt && i < L.nb && j < L.nb) wgt = d == 0 ? 1.0 : 2.0;
-        } else if (idx < L.off_corner) {
-            const int64_t e = idx - L.off_arrow;
-            const int64_t J = e / ((int64_t)L.ap * b), f = e % ((int64_t)L.ap * b);
-            if (f % L.ap < L.a && J * b + f / L.ap < L.nb) wgt = 2.0;
+    for (int64_t u = blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < n; u += TP_WAVES) {
+        int64_t at, rows;   // where the column starts, its rows that count
+        double wgt = 2.0;
+        if (u < nband) {
+            const int64_t J = u / per;
+            const int v = (int)(u - J * per), d = v / L.b, c = v - d * L.b;
+            at = u * L.b;
+            rows = J * L.b + c < L.nb ? L.nb - (J + d) * L.b : 0;
+            rows = rows < 0 ? 0 : rows > L.b ? L.b : rows;
+            if (d == 0) wgt = 1.0;
+        } else if (u < nband + narrow) {
+            at = L.off_arrow + (u - nband) * L.ap;
+            rows = u - nband < L.nb ? L.a : 0;
         } else {
-            const int64_t e = idx - L.off_corner;
-            if (e % L.ap < L.a && e / L.ap < L.a) wgt = 1.0;
+            at = L.off_corner + (u - nband - narrow) * L.ap;
+            rows = u - nband - narrow < L.a ? L.a : 0;
+            wgt = 1.0;
         }
-        if (wgt != 0.0) acc = fma(wgt * S[idx], B[idx], acc);
+        for (int64_t r = lane; r < rows; r += 256) {
+            double x[4], y[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {   // (each load from the column, those past its end dropped)
+                const int64_t i = at + (r + 64 * q < rows ? r + 64 * q : r);
+                x[q] = S[i];
+                y[q] = B[i];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (r + 64 * q < rows) acc = fma(wgt * x[q], y[q], acc);
+        }
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -915,11 +933,11 @@ __global__ __launch_bounds__(NT) void k_trace_part(const double* __restrict__ S,
     }
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
-__global__ void k_trace_final(const double* part, double* out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ __launch_bounds__(64) void k_trace_final(const double* part, double* out) {
     double s = 0.0, c = 0.0;
-    for (int g = 0; g < TP_BLOCKS; ++g) neumaier(s, c, part[g]);
-    *out = s + c;
+    for (int g = threadIdx.x; g < TP_BLOCKS; g += 64) neumaier(s, c, part[g]);
+    neumaier_join(s, c);
+    if (threadIdx.x == 0) *out = s + c;
 }
 
 // ---------------------------------------------------------------------------
