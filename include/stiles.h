@@ -147,12 +147,10 @@ int stiles_selinv(const double* L, double* Sigma, int64_t n, int64_t bandwidth, 
  * fills the device.  The tasks and their arithmetic are those of stiles_factor
  * and stiles_selinv on each matrix alone: results are identical bit for bit.
  *
- * The factor's launches run in step across the batch: each covers eight
- * consecutive tile columns of every matrix that has them (the environment
- * variable STILES_KB_COLS, 1 to 16, sets the count; the columns of a launch
- * are chained through per-block update counters), so the batch takes about as
- * long as its longest matrix, and a batch with one tile size runs best.  With
- * every tile at most 128 wide, the factor runs two workgroups per compute unit.
+ * The factor and Phase 2 are one launch each (the factor one per 128 matrices):
+ * a workgroup whose matrix has no tasks left joins the one with the most work
+ * left, so a batch takes about as long as its work divided over the device, or
+ * as its longest matrix alone.
  *
  * items (host array of `count` entries, read during the call only):
  *   n, bandwidth, arrow, tile   as for stiles_layout_init; reserved must be 0
@@ -300,12 +298,12 @@ int stiles_trace_product(const double* Sigma, const double* B, int64_t n, int64_
  * drops events not collected yet.  Thread-safe; costs two event records per
  * launch while enabled.
  */
-#define STILES_TK_POTRF 0      /* factor: the corner's diagonal blocks (POTRF) */
-#define STILES_TK_TRSM 1       /* factor: reserved (panel TRSM runs inside the tile-column launches) */
-#define STILES_TK_UPDATE 2     /* factor: reserved (trailing updates run inside the tile-column launches) */
+#define STILES_TK_POTRF 0      /* factor: the corner */
+#define STILES_TK_TRSM 1       /* factor: reserved (the panel TRSM runs inside the factor launch) */
+#define STILES_TK_UPDATE 2     /* factor: reserved (trailing updates run inside the factor launch) */
 #define STILES_TK_PHASE1 3     /* selinv: Phase 1 (TRTRI, TRMM, LAUUM) */
 #define STILES_TK_PHASE2 4     /* selinv: Phase 2 (persistent kernel) */
-#define STILES_TK_FACTOR 5     /* factor: one launch per band tile column (POTRF + TRSM + updates) */
+#define STILES_TK_FACTOR 5     /* factor: the band, one launch (POTRF + TRSM + updates) */
 #define STILES_TK_OTHER 6      /* pack, copies, corner, finalization */
 #define STILES_TK_COUNT 7
 int stiles_timing_enable(int on);

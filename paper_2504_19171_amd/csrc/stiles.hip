@@ -435,22 +435,30 @@ __global__ __launch_bounds__(64) void k_factor_final(const double* ldp, int npar
 
 // Phase 1, diagonal tiles: X_J = L_JJ^{-1} ("TRSM(L_ii^T, I)"), stored in the
 // diagonal slots of the workspace; the corner inverse likewise, one workgroup
-// per 64 columns.
-__host__ __device__ inline int trtri_blocks(const Lay& L) { return (int)L.nt + arrow_blocks(L.ap); }
+// per 64 columns.  A tile takes one workgroup per 64 columns too when that
+// leaves no more workgroups than fit the chip at once, or when it has 64 (79
+// tiles of 256: 131 against 188 us; 27,000 of 64: 0.87 against 1.13 ms), else
+// one, which inverts each diagonal block once (391 of 256: 303 against 442 us).
+__host__ __device__ inline int trtri_per(const Lay& L) { return L.b == 64 || L.nt * (L.b / 64) <= 512 ? L.b / 64 : 1; }
+__host__ __device__ inline int trtri_blocks(const Lay& L) { return (int)L.nt * trtri_per(L) + arrow_blocks(L.ap); }
 __device__ inline void trtri_body(const double* Lm, double* W, const Lay& L, int* info, int bid, double* smem) {
-    const int64_t J = bid;
+    const int per = trtri_per(L);
+    const int64_t J = bid / per;
     int bad;
-    if (J < L.nt) {
+    if (J < L.nt && L.b > 64 && per == 1) {
         trtri_tile(Lm + L.band(J, 0), L.b, W + L.band(J, 0), L.b, L.b, smem, &bad);
     } else {
-        trtri_columns(Lm + L.corner(), L.ap, W + L.corner(), L.ap, L.ap, (int)(J - L.nt), smem, &bad);
+        const bool band = J < L.nt;
+        const int64_t at = band ? L.band(J, 0) : L.corner();
+        const int m = band ? L.b : L.ap, s = band ? bid % per : (int)(bid - L.nt * per);
+        trtri_columns(Lm + at, m, W + at, m, m, s, smem, &bad);
     }
     if (threadIdx.x == 0 && bad) atomicExch(info, STILES_EBADL);
 }
 // (j0: first tile column; the launches of a selection start there)
 __global__ __launch_bounds__(NT, 2) void k_trtri_all(const double* Lm, double* W, Lay L, int* info, int64_t j0) {
     __shared__ double smem[TRTRI_SMEM_DOUBLES];
-    trtri_body(Lm, W, L, info, (int)(blockIdx.x + j0), smem);
+    trtri_body(Lm, W, L, info, (int)(blockIdx.x + j0 * trtri_per(L)), smem);
 }
 
 // Rows of the panel below tile J (band tiles J+1..J+s, then the arrow tile),
@@ -1418,7 +1426,7 @@ static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, in
         LAUNCH(STILES_TK_OTHER, k_zero_unused, dim3(grid_for(tail)), dim3(NT), 0, st, S, L);
     }
     // Phase 1
-    LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)(trtri_blocks(L) - j1)), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
+    LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)(trtri_blocks(L) - j1 * trtri_per(L))), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
            j1);
     {
         const int64_t g = (L.nt - j1) * (int64_t)(L.bt * nb64 + nab) * nb64;
