@@ -101,10 +101,10 @@ __device__ inline const int* p2_counter(const P2& p, int64_t J, int d) {
     return p.cnt + J * p2_ctr(p.L) + (d == ARW ? p2_arw(p.L) : d);
 }
 
-__device__ inline void p2_setup_body(const Lay& L, int* cnt, int* ticket, int* err, int* info) {
+__device__ inline void p2_setup_body(const Lay& L, int* cnt, int* ticket, int* err, int* info, int bid, int nblk) {
     const int64_t n = (int64_t)p2_ctr(L) * L.nt;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0;
-    if (threadIdx.x == 0) {
+    for (int64_t i = threadIdx.x + (int64_t)bid * blockDim.x; i < n; i += (int64_t)nblk * blockDim.x) cnt[i] = 0;
+    if (bid == 0 && threadIdx.x == 0) {
         *ticket = 0;
         *err = 0;
         *info = 0;

@@ -59,6 +59,13 @@ static Lay to_dev(const stiles_layout& s) {
     return l;
 }
 
+static int grid_for(int64_t work) {
+    int64_t g = (work + NT - 1) / NT;
+    if (g > 65536) g = 65536;
+    if (g < 1) g = 1;
+    return (int)g;
+}
+
 // ---------------------------------------------------------------------------
 // Small kernels
 // ---------------------------------------------------------------------------
@@ -246,7 +253,6 @@ __device__ inline void zero_unused_body(double* T, const Lay& L, int bid, int nb
         T[L.band(J, (int)d) + e] = 0.0;
     }
 }
-__global__ __launch_bounds__(NT) void k_zero_unused(double* T, Lay L) { zero_unused_body(T, L, blockIdx.x, gridDim.x); }
 
 // ---------------------------------------------------------------------------
 // Factor kernels
@@ -361,9 +367,6 @@ __device__ inline void factor_tail(double* Lm, const Lay& L, int bid, double* ld
 __global__ __launch_bounds__(NT) void k_factor_tail(double* Lm, Lay L, double* ldp, double* T) {
     factor_tail(Lm, L, blockIdx.x, ldp, T);
 }
-__global__ __launch_bounds__(NT) void k_corner_out(double* Lm, Lay L, const double* T, double* ldp) {
-    corner_out_body(Lm, L, blockIdx.x, T, ldp);
-}
 
 // Group and index inside it of task t of one matrix.
 __device__ inline void fac_ticket(const FacCtx& x, int t, int& c, int& u) {
@@ -423,6 +426,15 @@ __device__ inline void factor_final_body(const double* ldp, int nparts, const in
     const int f = (*err != 0) ? *err : *info_ws;
     *info = (f == 0x7fffffff) ? 0 : f;
     *logdet = (f == 0x7fffffff) ? (s + c) : __builtin_nan("");
+}
+// The corner back to its place; the workgroup that has its log det then ends the
+// factor.
+__global__ __launch_bounds__(NT) void k_corner_out(double* Lm, Lay L, const double* T, double* ldp, const int* info_ws,
+                                                   const int* err, double* logdet, int* info) {
+    corner_out_body(Lm, L, blockIdx.x, T, ldp);
+    if ((int)blockIdx.x != corner_out_blocks(L) - 1 || threadIdx.x >= 64) return;
+    __threadfence();   // the corner's own part of ldp, by lane 0
+    factor_final_body(ldp, (int)L.nt + 1, info_ws, err, logdet, info);
 }
 __global__ __launch_bounds__(64) void k_factor_final(const double* ldp, int nparts, const int* info_ws, const int* err,
                                                      double* logdet, int* info) {
@@ -562,8 +574,17 @@ __global__ __launch_bounds__(NT) void k_lauum_all(const double* W, double* S, La
     lauum_body(W, L, S, L, xcd_block((int)blockIdx.x, (int)gridDim.x) + j0 * lauum_per(L), smem);
 }
 
-__global__ void k_selinv_setup(Lay L, int* cnt, int* ticket, int* err, int* info) {
-    p2_setup_body(L, cnt, ticket, err, info);
+// Before a selected inverse (Sigma in layout L): no task done, first ticket, no
+// error, and zero the band tiles of S that lie outside the matrix (S null: none).
+__device__ inline void selinv_setup_body(const Lay& L, double* S, int* cnt, int* ticket, int* err, int* info, int bid, int nblk) {
+    p2_setup_body(L, cnt, ticket, err, info, bid, nblk);
+    if (S && L.bt > 0) zero_unused_body(S, L, bid, nblk);
+}
+__global__ __launch_bounds__(NT) void k_selinv_setup(Lay L, double* S, int* cnt, int* ticket, int* err, int* info) {
+    selinv_setup_body(L, S, cnt, ticket, err, info, blockIdx.x, gridDim.x);
+}
+static int selinv_setup_grid(const Lay& L) {
+    return std::min(grid_for((int64_t)L.bt * (L.bt + 1) / 2 * L.b * L.b), 2048);
 }
 __global__ __launch_bounds__(P2Cfg<8>::NTH, 2) void k_phase2(P2 p, Sched sc) {
     __shared__ __attribute__((aligned(128))) double smem[P2Cfg<8>::SMEM];
@@ -813,17 +834,11 @@ __global__ __launch_bounds__(64) void kb_factor_final(const BInst* bi, const int
     factor_final_body(f.ldp, I.nparts, f.winfo, err, I.logdet, I.info);
 }
 
-// Selinv set-up of every matrix (one workgroup per matrix): info word and the
-// Phase 2 ticket, error word and counters.
-__global__ __launch_bounds__(NT) void kb_selinv_setup(const BInst* bi) {
-    const BInst& I = bi[blockIdx.x];
-    const SelinvWs v = selinv_ws(I.L, I.ws);
-    p2_setup_body(I.L, v.flags, v.ticket, v.err, v.winfo);
-}
-
-__global__ __launch_bounds__(NT) void kb_zero_unused(BArgs a) {
+// Selinv set-up of every matrix.
+__global__ __launch_bounds__(NT) void kb_selinv_setup(BArgs a) {
     BATCH_DECODE(a, I, bid, nblk);
-    zero_unused_body(I.S, I.L, bid, nblk);
+    const SelinvWs v = selinv_ws(I.L, I.ws);
+    selinv_setup_body(I.L, I.S, v.flags, v.ticket, v.err, v.winfo, bid, nblk);
 }
 
 __global__ __launch_bounds__(NT, 2) void kb_trtri(BArgs a) {
@@ -1174,12 +1189,6 @@ static int fac_grid(const FacCtx& x, int most) {
     return std::min(most, 2 + FAC_AHEAD * g);
 }
 
-static int grid_for(int64_t work) {
-    int64_t g = (work + NT - 1) / NT;
-    if (g > 65536) g = 65536;
-    if (g < 1) g = 1;
-    return (int)g;
-}
 
 // log det partial pairs: one per band tile column, one or two for the corner
 static int factor_nparts(const Lay& L) { return (int)L.nt + (L.ap > 0 ? 1 : 0); }
@@ -1401,7 +1410,8 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
         LAUNCH(STILES_TK_POTRF, k_factor_all, dim3((unsigned)corner_grid(L)), dim3(FAC_NT), 0, st, xc, (int)fac_tasks(xc), sc,
                f.winfo);
         LAUNCH(STILES_TK_OTHER, k_corner_out, dim3((unsigned)corner_out_blocks(L)), dim3(NT), 0, st, Lm, L,
-               (const double*)f.Tc, f.ldp);
+               (const double*)f.Tc, f.ldp, (const int*)f.winfo, (const int*)f.err, logdet, (int*)info);
+        return 0;
     }
     LAUNCH(STILES_TK_OTHER, k_factor_final, dim3(1), dim3(64), 0, st, (const double*)f.ldp, factor_nparts(L),
            (const int*)f.winfo, (const int*)f.err, logdet, (int*)info);
@@ -1420,11 +1430,8 @@ static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, in
     if (ntasks > 0x7fffffff) return -3;
     const int64_t j1 = std::min<int64_t>(jf, L.nt - 1);
 
-    LAUNCH(STILES_TK_OTHER, k_selinv_setup, dim3(1), dim3(NT), 0, st, L, v.flags, v.ticket, v.err, v.winfo);
-    if (L.bt > 0) {
-        const int64_t tail = (int64_t)L.bt * (L.bt + 1) / 2 * L.b * L.b;
-        LAUNCH(STILES_TK_OTHER, k_zero_unused, dim3(grid_for(tail)), dim3(NT), 0, st, S, L);
-    }
+    LAUNCH(STILES_TK_OTHER, k_selinv_setup, dim3((unsigned)selinv_setup_grid(L)), dim3(NT), 0, st, L, S, v.flags, v.ticket,
+           v.err, v.winfo);
     // Phase 1
     LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)(trtri_blocks(L) - j1 * trtri_per(L))), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
            j1);
@@ -1570,7 +1577,8 @@ int stiles_inverse(const double* Lm, double* Ainv, int64_t n, int64_t bandwidth,
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
 
-    LAUNCH(STILES_TK_OTHER, k_selinv_setup, dim3(1), dim3(NT), 0, st, F, cnt, v.ticket, v.err, v.winfo);
+    LAUNCH(STILES_TK_OTHER, k_selinv_setup, dim3(64), dim3(NT), 0, st, F, (double*)nullptr, cnt, v.ticket, v.err,
+           v.winfo);
     // Phase 1: X_J, Lhat (as for stiles_selinv)
     LAUNCH(STILES_TK_PHASE1, k_trtri_all, dim3((unsigned)trtri_blocks(L)), dim3(NT), 0, st, Lm, v.W, L, v.winfo,
            (int64_t)0);
@@ -1817,11 +1825,7 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     auto close = [&](Launch& l) { l.at = t.begin; l.grid = t.grid; l.n = t.finish(segs); };
     Launch zu, tr, tm, la, p2;
     t.start(segs.size());
-    for (int k = 0; k < count; ++k) {
-        const Lay& L = bi[k].L;
-        const int64_t tail = (int64_t)L.bt * (L.bt + 1) / 2 * L.b * L.b;
-        if (L.bt > 0) t.add(segs, k, std::min(grid_for(tail), 256));
-    }
+    for (int k = 0; k < count; ++k) t.add(segs, k, std::min(selinv_setup_grid(bi[k].L), 256));
     close(zu);
     t.start(segs.size());
     for (int k = 0; k < count; ++k) t.add(segs, k, trtri_blocks(bi[k].L));
@@ -1865,8 +1869,7 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     const int64_t spin = spin_limit_ticks(di);
     auto args = [&](const Launch& l) { return BArgs{dbi, dseg + l.at, l.n, spin}; };
 
-    LAUNCH(STILES_TK_OTHER, kb_selinv_setup, dim3(count), dim3(NT), 0, st, dbi);
-    if (zu.grid > 0) LAUNCH(STILES_TK_OTHER, kb_zero_unused, dim3((unsigned)zu.grid), dim3(NT), 0, st, args(zu));
+    LAUNCH(STILES_TK_OTHER, kb_selinv_setup, dim3((unsigned)zu.grid), dim3(NT), 0, st, args(zu));
     LAUNCH(STILES_TK_PHASE1, kb_trtri, dim3((unsigned)tr.grid), dim3(NT), 0, st, args(tr));
     if (tm.grid > 0) LAUNCH(STILES_TK_PHASE1, kb_trmm, dim3((unsigned)tm.grid), dim3(NT), 0, st, args(tm));
     LAUNCH(STILES_TK_PHASE1, kb_lauum, dim3((unsigned)la.grid), dim3(NT), 0, st, args(la));
