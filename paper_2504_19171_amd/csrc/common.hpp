@@ -78,14 +78,8 @@ __device__ inline double ld_s(const double* base, uint32_t idx) {
     return *(const GLOBAL_AS double*)((const char*)base + o);
 }
 
-__device__ inline void st_s(double* base, uint32_t idx, double v) {
-    uint32_t o = idx << 3;
-    asm volatile("" : "+v"(o));
-    *(GLOBAL_AS double*)((char*)base + o) = v;
-}
-
 // base[idx] = v as a device-coherent store (see st_coh below), with the same
-// scalar-base + 32-bit offset addressing as st_s.
+// scalar-base + 32-bit offset addressing as ld_s.
 __device__ inline void st_coh_s(double* base, uint32_t idx, double v) {
     uint32_t o = idx << 3;
     asm volatile("" : "+v"(o));

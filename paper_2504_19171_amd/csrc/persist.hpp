@@ -80,12 +80,11 @@ __device__ inline bool sched_wait(const Sched& s, int* flag, int target, int* sh
     return ok;
 }
 
-// Wait until flag[i] >= target[i] for every i < n (n <= SCHED_MAX_DEPS), then
+// Wait until flag[i] >= target[i] for every i < n (n <= 3), then
 // acquire for every thread.  Thread 0 reads all the counters at once; while
 // some are short it polls only the first of those (one hot counter per
 // waiting workgroup: the polls of hundreds of waiting workgroups share the
 // memory channels of a few counters).  Returns false if the kernel must stop.
-#define SCHED_MAX_DEPS 3
 // (three named slots rather than an array: an array indexed by the running
 // count would live in scratch memory, whose loads count on the same memory
 // counter as the task's own loads)
