@@ -3,8 +3,7 @@ the factorization and selected inversion of the actual matrices with each
 candidate b (no model of the cost).
 
 The tile size is a free parameter of the method (the paper tunes it per
-platform, Sec. IV-D); for a batch the tile-column launches run in step
-across the matrices, so one b serves the whole batch.  Every timed run is the
+platform, Sec. IV-D); for a batch one b serves all its matrices.  Every timed run is the
 library's own HIP path; the candidates' buffers are released between runs.
 """
 from __future__ import annotations
