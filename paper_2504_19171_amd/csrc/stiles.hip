@@ -860,6 +860,11 @@ __global__ __launch_bounds__(NT) void kb_lauum(BArgs a) {
     lauum_body(selinv_ws(I.L, I.ws).W, I.L, I.S, I.L, bid, smem);
 }
 
+// What `tasks` Phase 2 tasks of a matrix weigh: the length of their sums and a
+// fixed cost of 256 (shares by task counts: 64 matrices 17.6 against 16.8 ms, 8
+// served ones 8.5 against 7.7; without the fixed cost 17.5 and 7.5, but 1.55
+// against 1.43 for 32 narrow ones).
+__host__ __device__ inline double p2_work(const Lay& L, int tasks) { return (double)tasks * (double)(L.bt * L.b + L.ap + 256); }
 #define P2_WIDE_TASKS 512.0
 // Phase 2 of every matrix in one persistent launch: each matrix starts on its
 // own share of the workgroups, with its own tickets, and a workgroup whose
@@ -882,7 +887,7 @@ __global__ __launch_bounds__(P2Cfg<NW>::NTH, 2) void kb_phase2(BArgs a, int coun
             const BInst& M = a.bi[m];
             const SelinvWs u = selinv_ws(M.L, M.ws);
             const int left = ld_coh_i(u.err) == 0 ? M.p2_tasks - ld_coh_i(u.ticket) : 0;
-            return left > 0 ? (float)left * (float)(M.L.bt * M.L.b + M.L.ap + M.L.b) : 0.0f;
+            return left > 0 ? (float)p2_work(M.L, left) : 0.0f;
         });
     }
 }
@@ -1848,13 +1853,15 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     double column = 0.0;
     for (int k = 0; k < count; ++k) column += (double)bi[k].p2_tasks / (double)bi[k].L.nt;
     const bool wide = column <= P2_WIDE_TASKS;
-    // Phase 2: the resident workgroups shared in proportion to the task
-    // counts, at least one per matrix
+    // Phase 2: the resident workgroups shared in proportion to the work, at
+    // least one per matrix
     t.start(segs.size());
     {
+        double work = 0.0;
+        for (int k = 0; k < count; ++k) work += p2_work(bi[k].L, bi[k].p2_tasks);
         const int64_t total = std::min<int64_t>(sum_tasks, (wide ? P2Cfg<8>::WG_PER_CU : P2Cfg<4>::WG_PER_CU) * (int64_t)di.cus);
         for (int k = 0; k < count; ++k) {
-            const int64_t want = total * bi[k].p2_tasks / std::max<int64_t>(1, sum_tasks);
+            const int64_t want = (int64_t)((double)total * p2_work(bi[k].L, bi[k].p2_tasks) / work);
             t.add(segs, k, (int)std::max<int64_t>(1, std::min<int64_t>(bi[k].p2_tasks, want)));
         }
     }
