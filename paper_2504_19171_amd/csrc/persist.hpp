@@ -39,8 +39,11 @@ struct Sched {
 
 // Thread 0 takes a ticket; broadcast to the workgroup.  Returns -1 when the
 // kernel is done or stopped.
+// *sh, here and below: a word in LDS that every one of these functions may
+// write as soon as it is called, as each of them ends with a barrier behind the
+// reads of the last one.  (Without it a delayed wavefront takes what the next
+// wait writes for its ticket.  So no barrier is needed in front of the write.)
 __device__ inline int sched_next(const Sched& s, int ntasks, int* sh) {
-    __syncthreads();
     if (threadIdx.x == 0) {
         // both requests in flight at once: a ticket taken after an error is
         // simply dropped
@@ -52,7 +55,9 @@ __device__ inline int sched_next(const Sched& s, int ntasks, int* sh) {
     __syncthreads();
     // uniform across the workgroup: keep it (and all that derives from it) in
     // scalar registers
-    return __builtin_amdgcn_readfirstlane(*sh);
+    const int t = __builtin_amdgcn_readfirstlane(*sh);
+    __syncthreads();
+    return t;
 }
 
 // Wait until *flag >= target (thread 0 polls), then acquire for every thread.
