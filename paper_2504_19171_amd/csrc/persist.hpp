@@ -150,6 +150,38 @@ __device__ inline void sched_signal(const Sched& s, int* flag, int ticket) {
     if (threadIdx.x == 0 && ticket != s.withhold) add_coh_i(flag, 1);
 }
 
+// A workgroup's way through matrices [k0, k1) of a batch: run(k) for matrix k,
+// then, until there is none or run() says to stop, for the one with the most
+// work left (work(m), 0: none).  *err: the launch's error word (nullptr: run()
+// and work() look at the matrices' own).  Only one wavefront looks at the error
+// and at the work, as they change meanwhile: every wavefront has to take the
+// same way, or they meet at different barriers.
+template <class R, class F>
+__device__ inline void sched_batch(int k, int k0, int k1, const int* err, int* sh, R&& run, F&& work) {
+    while (k >= 0) {
+        if (!run(k)) return;
+        if (threadIdx.x < 64) {
+            float best = 0.0f;
+            int at = -1;
+            for (int m = k0 + threadIdx.x; m < k1; m += 64) {
+                const float w = work(m);
+                if (w > best) { best = w; at = m; }
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                const float ob = __shfl_xor(best, o);
+                const int oa = __shfl_xor(at, o);
+                if (ob > best || (ob == best && oa > at)) { best = ob; at = oa; }
+            }
+            if (err && ld_coh_i(err) != 0) at = -1;
+            if (threadIdx.x == 0) *sh = at;
+        }
+        __syncthreads();
+        k = __builtin_amdgcn_readfirstlane(*sh);
+        __syncthreads();   // read by all before it is written again
+    }
+}
+
 // Optional task tracing, compiled in with -DSTILES_TASK_TRACE (diagnostics
 // builds only): per task, wall-clock ticks at dequeue, after its waits and
 // after its signal, plus its kind / tile column / workgroup.

@@ -746,31 +746,6 @@ __global__ __launch_bounds__(NT) void kb_factor_setup(const BInst* bi) {
     factor_setup_body(I.L, factor_ws(I.L, I.ws), threadIdx.x + (int64_t)(blockIdx.x & 7) * NT, 8 * NT);
 }
 
-// The matrix [k0, k1) with the most work left (of each, left and its weight:
-// work(k, left, weight)), or -1.
-template <class F>
-__device__ inline int batch_busiest(int k0, int k1, int* sh, F&& work) {
-    if (threadIdx.x < 64) {
-        float best = 0.0f;
-        int at = -1;
-        for (int k = k0 + threadIdx.x; k < k1; k += 64) {
-            const float w = work(k);
-            if (w > best) { best = w; at = k; }
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ob = __shfl_xor(best, o);
-            const int oa = __shfl_xor(at, o);
-            if (ob > best || (ob == best && oa > at)) { best = ob; at = oa; }
-        }
-        if (threadIdx.x == 0) *sh = at;
-    }
-    __syncthreads();
-    const int k = __builtin_amdgcn_readfirstlane(*sh);
-    __syncthreads();   // read by all before it is written again
-    return k;
-}
-
 // The band factors of matrices [k0, k1), at most KB_SLICE a launch: each starts
 // on its own share of the workgroups (two or more), with its own tickets, the
 // first of which is its chain.  (With one queue over all matrices, chunk after
@@ -782,23 +757,24 @@ __device__ inline int batch_busiest(int k0, int k1, int* sh, F&& work) {
 #define KB_SLICE 128
 __global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BArgs a, int k0, int k1, int* err) {
     __shared__ FacSmem sm;
-    for (int k = a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst; k >= 0;) {
-        const BInst& I = a.bi[k];
-        const FactorWs f = factor_ws(I.L, I.ws);
-        Sched sc;
-        sc.ticket = f.ticket;
-        sc.err = err;
-        sc.spin_limit = a.spin_limit;
-        sc.withhold = -1;
-        const FacCtx x = fac_ctx(I.L, I.Lm, f.Yd, f.flags);
-        if (!fac_run(x, I.fac_ntask, sc, sm, f.winfo)) return;
-        if (ld_coh_i(err) != 0) return;
-        k = batch_busiest(k0, k1, &sm.sh, [&](int m) {
+    sched_batch(
+        a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst, k0, k1, err, &sm.sh,
+        [&](int k) {
+            const BInst& I = a.bi[k];
+            const FactorWs f = factor_ws(I.L, I.ws);
+            Sched sc;
+            sc.ticket = f.ticket;
+            sc.err = err;
+            sc.spin_limit = a.spin_limit;
+            sc.withhold = -1;
+            const FacCtx x = fac_ctx(I.L, I.Lm, f.Yd, f.flags);
+            return fac_run(x, I.fac_ntask, sc, sm, f.winfo);
+        },
+        [&](int m) {
             const BInst& M = a.bi[m];
             const int t = ld_coh_i(factor_ws(M.L, M.ws).ticket), left = 1 + M.fac_ntask - t;
             return t > 0 && left > 0 ? (float)left * (float)(fac_wc(M.L) + 4) : 0.0f;
         });
-    }
 }
 
 __global__ __launch_bounds__(NT) void kb_factor_tail(BArgs a) {
@@ -874,22 +850,24 @@ template <int NW>
 __global__ __launch_bounds__(P2Cfg<NW>::NTH, 2) void kb_phase2(BArgs a, int count) {
     __shared__ __attribute__((aligned(128))) double smem[P2Cfg<NW>::SMEM];
     __shared__ int sh[2];
-    for (int k = a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst; k >= 0;) {
-        const BInst& I = a.bi[k];
-        const SelinvWs v = selinv_ws(I.L, I.ws);
-        Sched sc;
-        sc.ticket = v.ticket;
-        sc.err = v.err;
-        sc.spin_limit = a.spin_limit;
-        sc.withhold = -1;
-        if (!p2_run<NW>(make_p2(I.S, I.L, v.W, I.L, v.flags, I.p2_tasks, 0), sc, smem, sh)) return;
-        k = batch_busiest(0, count, &sh[1], [&](int m) {
+    sched_batch(
+        a.seg[bseg_find(a.seg, a.nseg, (int)blockIdx.x)].inst, 0, count, nullptr, &sh[1],
+        [&](int k) {
+            const BInst& I = a.bi[k];
+            const SelinvWs v = selinv_ws(I.L, I.ws);
+            Sched sc;
+            sc.ticket = v.ticket;
+            sc.err = v.err;
+            sc.spin_limit = a.spin_limit;
+            sc.withhold = -1;
+            return p2_run<NW>(make_p2(I.S, I.L, v.W, I.L, v.flags, I.p2_tasks, 0), sc, smem, sh);
+        },
+        [&](int m) {
             const BInst& M = a.bi[m];
             const SelinvWs u = selinv_ws(M.L, M.ws);
             const int left = ld_coh_i(u.err) == 0 ? M.p2_tasks - ld_coh_i(u.ticket) : 0;
             return left > 0 ? (float)p2_work(M.L, left) : 0.0f;
         });
-    }
 }
 
 __global__ void kb_selinv_final(const BInst* bi) {

@@ -20,6 +20,7 @@ struct EmuIdx {
 inline thread_local EmuIdx threadIdx;
 inline pthread_barrier_t emu_barrier;
 inline int emu_late = -1;
+inline int* emu_raise = nullptr;   // a word that becomes 1 with its first read
 
 inline void __syncthreads() { pthread_barrier_wait(&emu_barrier); }
 inline void emu_hold() {
@@ -39,6 +40,10 @@ template <class T>
 T emu_load(const T* p) {
     T v;
     __atomic_load(p, &v, __ATOMIC_SEQ_CST);
+    if ((const void*)p == emu_raise) {
+        int up = 1;
+        __atomic_store(emu_raise, &up, __ATOMIC_SEQ_CST);
+    }
     return v;
 }
 template <class T>

@@ -58,5 +58,18 @@ int main(int argc, char** argv) {
         ok[w] = sched_next(s, 8, &sh);
     });
     good = agree("ticket before a ticket", got, 7) && agree("no ticket left", ok, -1) && good;
+    // a batch: an error comes up right after the first look at its word, so all go
+    // on with the same matrix once more and all leave after that
+    workgroup([&](int w) {
+        got[w] = 0;
+        sched_batch(
+            0, 0, 1, &err, &sh,
+            [&](int) {
+                if (++got[w] == 1 && w == 0) emu_raise = &err;
+                return got[w] < 4;
+            },
+            [](int) { return 1.0f; });
+    });
+    good = agree("matrices until the error", got, 2) && good;
     return good ? 0 : 1;
 }
