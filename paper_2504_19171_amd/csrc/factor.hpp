@@ -31,6 +31,10 @@
 // the launch does, and launches have at least two workgroups when they have
 // tasks: as long as some other launch's workgroups leave room in the end, no
 // wait can last.
+// Without blocks below the diagonal ones (w = 0, or a single chunk) the chunks
+// do not depend on each other: each is a chain of its own, and these take the
+// first tickets (nb 200,000, w 0, tile 64: 16.9 ms with one chain for all, MEASURED
+// so).
 //
 // Every block is written once in its final form (P and H parts before that
 // are read only by the task or chain that goes on with them) with
@@ -109,6 +113,8 @@ __host__ __device__ inline int fac_group(const FacCtx& x, int c) {
 // Leading chunks whose groups are all alike (but for the corner tasks of
 // every fourth), rounded down to a multiple of four.
 __host__ __device__ inline int fac_full4(const FacCtx& x) { return imax_(0, x.nc - 1 - imax_(x.wc, 4)) & ~3; }
+// Chains: tickets in front of the tasks.
+__host__ __device__ inline int fac_chains(const FacCtx& x) { return x.wc == 0 ? x.nc : 1; }
 __host__ __device__ inline int64_t fac_tasks(const FacCtx& x) {
     const int f4 = fac_full4(x);
     int64_t t = 0;
@@ -134,8 +140,7 @@ enum {
     CW_L = 4,     // [4] 4 c + panels of row t there
     CW_R = 8,     // [4] 4 c + panels of strip s there
     CW_D = 12,    // [4] chunks for which wavefront t has read R
-    CW_FIN = 16,  // [4] chunks wavefront t is done with
-    CW_X = 20     // [1] chunks whose X is there
+    CW_X = 16     // [1] chunks whose X is there
 };
 struct TaskSmem {
     double st[FAC_STAGES][2][16 * 64];   // per stage: 16 columns of the column-side rows, then of the row-side rows
@@ -821,19 +826,7 @@ __device__ inline bool fac_chain_wave(const FacCtx& x, const Sched& sc, FacSmem&
     dbl4 y[4];        // strip S of the block row below this chunk
     int* pend_po = nullptr;   // flag to raise once this wavefront's stores are in memory
     bool have_z = false;
-    if (c0 > 0 && x.wc >= 1) {   // a later launch of the same factor: that block row from memory
-        fac_load(fac_band(x, c0, c0 - 1), b0, S, o, 4);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            ch_put(sm.R[S][p], o[p], lane);
-            ch_mma(dd, o[p], o[p]);
-        }
-        ch_set(fs, CW_R + S, 4 * c0);
-    }
     for (int c = c0; c < c1; ++c) {
-        if (x.wc == 0 && c > c0 + 1) {   // nothing else keeps the wavefronts within two chunks
-            if (!ch_wait(sc, fs, CW_FIN, CW_FIN + 4, c - 1)) return false;
-        }
         const int b = fac_opaque(b0);
         double(&Yc)[4][16 * 17] = sm.Y[c & 1];
         double(&Lc)[6][256] = sm.Lt[c & 1];
@@ -933,7 +926,7 @@ __device__ inline bool fac_chain_wave(const FacCtx& x, const Sched& sc, FacSmem&
                 fac_load(Rb, b, S, y, 4);
             }
             // the next diagonal block's row, if it is there too
-            if (c + 1 < c1 && (x.wc < 2 || c + 1 < 2 || __builtin_amdgcn_readfirstlane(ld_coh_i(hx + 1)) != 0)) {
+            if (x.wc < 2 || c + 1 < 2 || __builtin_amdgcn_readfirstlane(ld_coh_i(hx + 1)) != 0) {
                 ch_load_row(fac_band(x, c + 1, c + 1), b, S, z, zd);
                 have_z = true;
             }
@@ -984,14 +977,14 @@ __device__ inline bool fac_chain_wave(const FacCtx& x, const Sched& sc, FacSmem&
                 pend_po = nullptr;
             }
         }
-        ch_set(fs, CW_FIN + S, c + 1);
     }
     fac_vm0();
     if (lane == 0 && pend_po && !quiet) fac_up(pend_po, 1);
     return true;
 }
 
-// Chunks c0 .. c1 - 1 of one matrix; false when the kernel must stop.
+// Chunks c0 .. c1 - 1 of one matrix, all of them or (with wc 0) one; false when
+// the kernel must stop.
 __device__ inline bool fac_chain(const FacCtx& x, const Sched& sc, FacSmem& sm, int c0, int c1, int* info, bool quiet) {
     __syncthreads();
     if (threadIdx.x < 32) sm.ch.w[threadIdx.x] = 0;

@@ -390,20 +390,21 @@ __device__ inline void fac_ticket(const FacCtx& x, int t, int& c, int& u) {
     u = t;
 }
 
-// The band factor of one matrix in one persistent launch (factor.hpp): ticket
-// 0 is the chain, ticket 1 + t task t.
+// The band factor of one matrix in one persistent launch (factor.hpp): the first
+// tickets are the chains, the next ones the tasks.
 // Until no tickets are left (true) or the kernel must stop.
 __device__ inline bool fac_run(const FacCtx& x, int ntask, const Sched& sc, FacSmem& sm, int* info) {
     if (threadIdx.x == 0) sm.dead = 0;
+    const int nch = fac_chains(x);
     for (;;) {
-        const int g = sched_next(sc, 1 + ntask, &sm.sh);
+        const int g = sched_next(sc, nch + ntask, &sm.sh);
         if (g < 0) return true;
-        if (g == 0) {
-            if (!fac_chain(x, sc, sm, 0, x.nc, info, g == sc.withhold)) return false;
+        if (g < nch) {
+            if (!fac_chain(x, sc, sm, g, nch > 1 ? g + 1 : x.nc, info, g == sc.withhold)) return false;
             continue;
         }
         int c, u;
-        fac_ticket(x, g - 1, c, u);
+        fac_ticket(x, g - nch, c, u);
         if (!fac_task(x, sc, sm, c, u, g)) return false;
     }
 }
@@ -703,6 +704,7 @@ struct BInst {
     int* info;        // [0] factor, [1] selinv
     char* ws;         // this matrix's workspace (factor or selinv layout)
     int fac_ntask;    // factor task count
+    int fac_nticket;  // ... and with the chains
     int p2_tasks;     // Phase 2 task count
     int nparts;       // log det partial pairs (tile columns + corner blocks)
 };
@@ -772,7 +774,7 @@ __global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BArgs a, int k0, int k1, 
         },
         [&](int m) {
             const BInst& M = a.bi[m];
-            const int t = ld_coh_i(factor_ws(M.L, M.ws).ticket), left = 1 + M.fac_ntask - t;
+            const int t = ld_coh_i(factor_ws(M.L, M.ws).ticket), left = M.fac_nticket - t;
             return t > 0 && left > 0 ? (float)left * (float)(fac_wc(M.L) + 4) : 0.0f;
         });
 }
@@ -1166,7 +1168,9 @@ static int debug_withhold() {
 // 24 chunks' tasks fill the chip anyway.  Below 16 some widths lose (w 2,001,
 // nb 100,000: 21.1 ms with 24, 24.6 with 8).
 #define FAC_AHEAD 24
+// With a chain per chunk (wc 0) the chains wait for nothing: as many as fit.
 static int fac_grid(const FacCtx& x, int most) {
+    if (fac_chains(x) > 1) return most;
     int g = 0;
     for (int c = 0; c < std::min(4, x.nc); ++c) g = std::max(g, fac_group(x, c));
     return std::min(most, 2 + FAC_AHEAD * g);
@@ -1180,8 +1184,8 @@ static int factor_nparts(const Lay& L) { return (int)L.nt + (L.ap > 0 ? 1 : 0); 
 // most eight block rows).
 static int corner_grid(const Lay& L) {
     if (L.ap == 0) return 0;
-    const int64_t n = fac_tasks(fac_ctx(corner_lay(L), nullptr, nullptr, nullptr));
-    return (int)std::min<int64_t>(1 + n, 32);
+    const FacCtx x = fac_ctx(corner_lay(L), nullptr, nullptr, nullptr);
+    return (int)std::min<int64_t>(fac_chains(x) + fac_tasks(x), 32);
 }
 
 static int64_t p2_total_tasks(const Lay& L) {
@@ -1369,8 +1373,8 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
     const FacCtx x = fac_ctx(L, Lm, f.Yd, f.flags);
-    const int64_t ntask = fac_tasks(x);
-    if (ntask >= 0x7fffffff) return -3;
+    const int64_t ntask = fac_tasks(x), nticket = fac_chains(x) + ntask;
+    if (nticket > 0x7fffffff) return -3;
     Sched sc;
     sc.ticket = f.ticket;
     sc.err = f.err;
@@ -1383,7 +1387,7 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
         tm_end(tm, STILES_TK_OTHER, st);
     }
     LAUNCH(STILES_TK_OTHER, k_factor_setup, dim3(grid_for(fac_ints(L) + fac_ints(corner_lay(L)))), dim3(NT), 0, st, L, f);
-    LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(1 + ntask, fac_grid(x, 2 * di.cus))),
+    LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(nticket, fac_grid(x, 2 * di.cus))),
            dim3(FAC_NT), 0, st, x, (int)ntask, sc, f.winfo);
     LAUNCH(STILES_TK_OTHER, k_factor_tail, dim3((unsigned)factor_tail_blocks(L)), dim3(NT), 0, st, Lm, L, f.ldp, f.Tc);
     if (L.ap > 0) {
@@ -1702,9 +1706,11 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
         I.info = items[k].info;
         I.ws = ws + pl.off[k];
         I.nparts = factor_nparts(I.L);
-        const int64_t n = fac_tasks(fac_ctx(I.L, nullptr, nullptr, nullptr));
-        if (n >= 0x7fffffff) return -1;
+        const FacCtx x = fac_ctx(I.L, nullptr, nullptr, nullptr);
+        const int64_t n = fac_tasks(x), nticket = fac_chains(x) + n;
+        if (nticket > 0x7fffffff) return -1;
         I.fac_ntask = (int)n;
+        I.fac_nticket = (int)nticket;
     }
     const size_t seg0 = align256(sizeof(BInst) * (size_t)count);
     const size_t int0 = seg0 + align256(sizeof(BSeg) * batch_nseg(count));
@@ -1724,17 +1730,17 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     for (int k = 0; k < count; ++k)
         if (bi[k].L.ap > 0) t.add(segs, k, corner_out_blocks(bi[k].L));
     close(corner_back);
-    // the factor: the resident workgroups shared in proportion to the tasks,
-    // at least two per matrix (one when it has no tasks)
+    // the factor: the resident workgroups shared in proportion to the tickets,
+    // at least two per matrix (one when it has only its chain)
     std::vector<Launch> fac;
     for (int k0 = 0; k0 < count; k0 += KB_SLICE) {
         const int k1 = std::min(count, k0 + KB_SLICE);
         int64_t sum = 0;
-        for (int k = k0; k < k1; ++k) sum += bi[k].fac_ntask;
+        for (int k = k0; k < k1; ++k) sum += bi[k].fac_nticket;
         t.start(segs.size());
         for (int k = k0; k < k1; ++k) {
-            const int64_t n = bi[k].fac_ntask, want = 2 * (int64_t)di.cus * n / std::max<int64_t>(1, sum);
-            t.add(segs, k, (int)std::min<int64_t>(1 + n, std::max<int64_t>(2, want)));
+            const int64_t n = bi[k].fac_nticket, want = 2 * (int64_t)di.cus * n / sum;
+            t.add(segs, k, (int)std::min<int64_t>(n, std::max<int64_t>(2, want)));
         }
         Launch l;
         close(l);
