@@ -35,6 +35,9 @@
  * - Pointers named "device" are HIP device pointers; the caller allocates and
  *   frees every buffer.  The library never retains or frees caller memory and
  *   allocates no device memory.
+ * - A, L and the band form may start at any double and a workspace at any byte;
+ *   Sigma has to start at a multiple of 16 bytes (Phase 2 reads it 16 bytes at a
+ *   time), as every allocation does.  The factor is fastest when L does too.
  * - `stream` is a hipStream_t (NULL = the default stream).  Every call only
  *   enqueues work on `stream` and returns; results are ready when the stream
  *   is.  Calls on different streams may overlap if they use different buffers

@@ -34,7 +34,7 @@
 // Without blocks below the diagonal ones (w = 0, or a single chunk) the chunks
 // do not depend on each other: each is a chain of its own, and these take the
 // first tickets (nb 200,000, w 0, tile 64: 16.9 ms with one chain for all, 0.15
-// so).
+// ms so).
 //
 // Every block is written once in its final form (P and H parts before that
 // are read only by the task or chain that goes on with them) with
@@ -269,34 +269,59 @@ __device__ inline int fac_lane() {
     return l;
 }
 
+// Bytes a lane takes from memory per load into LDS: 16 where L starts at a
+// multiple of 16 bytes, which every block then does (tile sizes, a_p and leading
+// dimensions are even), else 4: the caller may place L at any double (nb 100,000
+// w 1,024 a 100 tile 256: 19.5 and 24.9 ms with the copy of A; nb 31,987 w 32 4.6
+// and 5.2).
+#define FAC_WIDE 16
+#define FAC_NARROW 4
+__host__ __device__ inline bool fac_wide(const void* Lm) { return ((uintptr_t)Lm & 15) == 0; }
+
+// One kilobyte (128 doubles) straight into LDS, double p of it from at(p) (pairs
+// p, p + 1, p even, are contiguous): one load of 16 bytes a lane, or four of 4.
+template <int LD, class F>
+__device__ inline void fac_fetch(int l, double* st, F&& at) {
+    if constexpr (LD == FAC_WIDE) {
+        __builtin_amdgcn_global_load_lds((const void*)at(2 * l), (lds_void_t*)st, 16, 0, 16);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            __builtin_amdgcn_global_load_lds((const void*)((const char*)at(32 * j + (l >> 1)) + 4 * (l & 1)),
+                                             (lds_void_t*)(st + 32 * j), 4, 0, 16);
+    }
+}
+
 // Issue the loads of stage `q` (16 columns) of block column k: columns 4 v ..
 // 4 v + 3 of the column-side rows and of the row-side rows, straight into LDS
 // (element (row x, column k) at k * 64 + (x ^ 16 (k & 3)): the four columns
-// that one matrix-core operand takes fall in different banks).
+// that one matrix-core operand takes fall in different banks).  Rows past va
+// (vb) repeat the last two.
+template <int LD>
 __device__ inline void fac_issue(const double* A, int lda, int va, const double* B, int ldb, int vb, int q,
                                  double (*st)[16 * 64]) {
     const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = fac_lane();
-    const int half = l >> 5, s = 2 * (l & 31);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int col = 4 * v + 2 * u + half;
-        const int row = s ^ (16 * ((2 * u + half) & 3));
-        const double* ga = A + imin_(row, va - 2) + (int64_t)(16 * q + col) * lda;
-        const double* gb = B + imin_(row, vb - 2) + (int64_t)(16 * q + col) * ldb;
-        __builtin_amdgcn_global_load_lds((const void*)ga, (lds_void_t*)(st[0] + (4 * v + 2 * u) * 64), 16, 0, 16);
-        __builtin_amdgcn_global_load_lds((const void*)gb, (lds_void_t*)(st[1] + (4 * v + 2 * u) * 64), 16, 0, 16);
+        auto from = [&](const double* P, int ld, int valid) {
+            return [=](int p) {
+                const int half = p >> 6, row = (p & 63) ^ (16 * ((2 * u + half) & 3));
+                return P + imin_(row & ~1, valid - 2) + (p & 1) + (int64_t)(16 * q + 4 * v + 2 * u + half) * ld;
+            };
+        };
+        fac_fetch<LD>(l, st[0] + (4 * v + 2 * u) * 64, from(A, lda, va));
+        fac_fetch<LD>(l, st[1] + (4 * v + 2 * u) * 64, from(B, ldb, vb));
     }
 }
+template <int LD>
 __device__ inline void fac_issue_a(const double* A, int lda, int q, double* st) {
     const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = fac_lane();
-    const int half = l >> 5, s = 2 * (l & 31);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int col = 4 * v + 2 * u + half;
-        const int row = s ^ (16 * ((2 * u + half) & 3));
-        __builtin_amdgcn_global_load_lds((const void*)(A + row + (int64_t)(16 * q + col) * lda),
-                                         (lds_void_t*)(st + (4 * v + 2 * u) * 64), 16, 0, 16);
-    }
+    for (int u = 0; u < 2; ++u)
+        fac_fetch<LD>(l, st + (4 * v + 2 * u) * 64, [=](int p) {
+            const int half = p >> 6;
+            return A + ((p & 63) ^ (16 * ((2 * u + half) & 3))) + (int64_t)(16 * q + 4 * v + 2 * u + half) * lda;
+        });
 }
 
 typedef double dbl2 __attribute__((ext_vector_type(2)));
@@ -328,22 +353,20 @@ __device__ inline void fac_read_a(uint32_t a0, uint32_t a1, uint32_t a2, uint32_
 }
 
 // Wait until the oldest of this wavefront's load stages has landed, `later`
-// stages (4 loads each, 2 for the one-operand form) issued after it.
-template <int PER>
+// stages (PER loads of 16 bytes a lane each, or four times as many of 4) issued
+// after it.
+template <int LD, int PER>
 __device__ inline void fac_landed(int later) {
-    if (PER == 4) {
-        if (later >= 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if (later == 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    } else {
-        if (later >= 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else if (later == 1) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
+    constexpr int N = PER * (FAC_WIDE / LD);   // 2 to 16; the counter goes to 63
+    if (later >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * N) : "memory");
+    else if (later == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * N) : "memory");
+    else if (later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // acc[t] += (row w, k) (col-side row u, k)^T over k0 <= k < k1, tiles t < nt,
 // as the blocks' flags come up.  act: this wavefront's strip has rows.
+template <int LD>
 __device__ inline bool fac_acc(const FacCtx& x, const Sched& sc, FacSmem& sm, dbl4 (&acc)[4], FacRow w, FacRow u,
                                int k0, int k1, int nt, bool act) {
     const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -353,6 +376,7 @@ __device__ inline bool fac_acc(const FacCtx& x, const Sched& sc, FacSmem& sm, db
 #pragma unroll
     for (int t = 0; t < 4; ++t) oa[t] = lds_addr(sm.tk.st[0][0]) + 8u * (uint32_t)(lk * 64 + 16 * (t ^ lk) + li);
     const uint32_t ob = lds_addr(sm.tk.st[0][1]) + 8u * (uint32_t)(lk * 64 + 16 * (v ^ lk) + li);
+    if (LD == FAC_NARROW) fac_vm0();   // (with the block's own loads there would be more in flight than can be counted)
     for (int k = k0; k < k1;) {
         // leading blocks that are ready, up to 32: lanes 0..31 read the row
         // side's flags, lanes 32..63 the column side's
@@ -386,13 +410,13 @@ __device__ inline bool fac_acc(const FacCtx& x, const Sched& sc, FacSmem& sm, db
         const int total = 4 * n;
         auto issue = [&](int it) {
             const int kk = k + (it >> 2);
-            fac_issue(uniform_ptr(fac_ptr(x, u, kk)), ldu, vu, uniform_ptr(fac_ptr(x, w, kk)), ldw, vw, it & 3,
+            fac_issue<LD>(uniform_ptr(fac_ptr(x, u, kk)), ldu, vu, uniform_ptr(fac_ptr(x, w, kk)), ldw, vw, it & 3,
                       sm.tk.st[it & 3]);
         };
 #pragma unroll
         for (int it = 0; it < FAC_STAGES - 1; ++it) issue(it);   // a block has four stages
         for (int it = 0; it < total; ++it) {
-            fac_landed<4>(total - 1 - it);
+            fac_landed<LD, 4>(imin_(total - 1 - it, FAC_STAGES - 2));
             fac_bar();   // ... for every wavefront, and stage it - 1 has been read
             if (it + FAC_STAGES - 1 < total) issue(it + FAC_STAGES - 1);
             if (act) {
@@ -542,6 +566,7 @@ __device__ inline FacTask fac_pick(const FacCtx& x, int c, int u) {
 // ticket (the test hook Sched::withhold names one whose signal is not sent).
 // The kinds share one copy of the sum and of the solve: with a copy for each,
 // the kernel's code would not fit the instruction cache.
+template <int LD>
 __device__ inline bool fac_task(const FacCtx& x, const Sched& sc, FacSmem& sm, int c, int u, int ticket) {
     const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const FacTask k = fac_pick(x, c, u);
@@ -592,7 +617,7 @@ __device__ inline bool fac_task(const FacCtx& x, const Sched& sc, FacSmem& sm, i
         fac_bar();
         if (threadIdx.x == 0) fac_up(x.pp + i * (int64_t)4 + 3, 1);
     }
-    if (!fac_acc(x, sc, sm, acc, w, cr, k0, k1, nt, act)) return false;
+    if (!fac_acc<LD>(x, sc, sm, acc, w, cr, k0, k1, nt, act)) return false;
     int* cnt = x.cc + (i * (i + 1) / 2 + k.j);
     if (k.kind == FT_CORNER) {
         if (!sched_wait(sc, cnt, c >> 2, &sm.sh)) return false;
@@ -649,12 +674,12 @@ __device__ inline bool fac_task(const FacCtx& x, const Sched& sc, FacSmem& sm, i
 #pragma unroll
         for (int t = 0; t < 4; ++t) oa[t] = lds_addr(sm.tk.st[0][0]) + 8u * (uint32_t)(lk * 64 + 16 * (t ^ lk) + li);
         fac_load(O, b, v, z, 4);
+        if (LD == FAC_NARROW) fac_vm0();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) fac_issue_a(A, b, q, sm.tk.st[q][0]);
+        for (int q = 0; q < 4; ++q) fac_issue_a<LD>(A, b, q, sm.tk.st[q][0]);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (q == 0) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-            else fac_landed<2>(3 - q);
+            fac_landed<LD, 2>(3 - q);
             fac_bar();
 #pragma unroll
             for (int h = 0; h < 2; ++h) {

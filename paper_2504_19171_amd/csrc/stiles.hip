@@ -393,6 +393,7 @@ __device__ inline void fac_ticket(const FacCtx& x, int t, int& c, int& u) {
 // The band factor of one matrix in one persistent launch (factor.hpp): the first
 // tickets are the chains, the next ones the tasks.
 // Until no tickets are left (true) or the kernel must stop.
+template <int LD>
 __device__ inline bool fac_run(const FacCtx& x, int ntask, const Sched& sc, FacSmem& sm, int* info) {
     if (threadIdx.x == 0) sm.dead = 0;
     const int nch = fac_chains(x);
@@ -405,12 +406,13 @@ __device__ inline bool fac_run(const FacCtx& x, int ntask, const Sched& sc, FacS
         }
         int c, u;
         fac_ticket(x, g - nch, c, u);
-        if (!fac_task(x, sc, sm, c, u, g)) return false;
+        if (!fac_task<LD>(x, sc, sm, c, u, g)) return false;
     }
 }
+template <int LD>
 __global__ __launch_bounds__(FAC_NT, 2) void k_factor_all(FacCtx x, int ntask, Sched sc, int* info) {
     __shared__ FacSmem sm;
-    fac_run(x, ntask, sc, sm, info);
+    fac_run<LD>(x, ntask, sc, sm, info);
 }
 
 // Final log det (compensated sum of the partial pairs in a fixed order: each
@@ -757,6 +759,7 @@ __global__ __launch_bounds__(NT) void kb_factor_setup(const BInst* bi) {
 // among those whose chain is under way: so no workgroup becomes a chain that
 // waits for others that have all become chains too.
 #define KB_SLICE 128
+template <int LD>
 __global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BArgs a, int k0, int k1, int* err) {
     __shared__ FacSmem sm;
     sched_batch(
@@ -770,7 +773,7 @@ __global__ __launch_bounds__(FAC_NT, 2) void kb_factor(BArgs a, int k0, int k1, 
             sc.spin_limit = a.spin_limit;
             sc.withhold = -1;
             const FacCtx x = fac_ctx(I.L, I.Lm, f.Yd, f.flags);
-            return fac_run(x, I.fac_ntask, sc, sm, f.winfo);
+            return fac_run<LD>(x, I.fac_ntask, sc, sm, f.winfo);
         },
         [&](int m) {
             const BInst& M = a.bi[m];
@@ -798,7 +801,7 @@ __global__ __launch_bounds__(FAC_NT, 2) void kb_corner(BArgs a, int* err) {
     sc.spin_limit = a.spin_limit;
     sc.withhold = -1;
     const FacCtx x = corner_ctx(I.L, f);
-    fac_run(x, (int)fac_tasks(x), sc, sm, f.winfo);
+    fac_run<FAC_WIDE>(x, (int)fac_tasks(x), sc, sm, f.winfo);
 }
 __global__ __launch_bounds__(NT) void kb_corner_out(BArgs a) {
     BATCH_DECODE(a, I, bid, nblk);
@@ -1197,6 +1200,11 @@ static int64_t p2_total_tasks(const Lay& L) {
 // Batch plan: layouts, the table area at the start of the workspace (the
 // matrices, then the launch segment tables) and each matrix's workspace.
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
+// The kernels read their workspaces with 16-byte loads, and a caller may place
+// one anywhere: it is used from its first multiple of 16 bytes on, and every
+// workspace size has that much to spare.
+#define WS_ALIGN 16
+static char* ws_base(void* p) { return (char*)(((uintptr_t)p + WS_ALIGN - 1) / WS_ALIGN * WS_ALIGN); }
 struct BPlan {
     std::vector<stiles_layout> lay;
     std::vector<size_t> off;   // workspace offset of each matrix
@@ -1245,7 +1253,7 @@ static int batch_plan(const stiles_batch_item* items, int count, bool need_sigma
         pl.off[k] = o;
         o += align256(std::max(fws_bytes(pl.lay[k]), sws_bytes(pl.lay[k])));
     }
-    pl.total = o;
+    pl.total = WS_ALIGN + o;
     return 0;
 }
 
@@ -1337,9 +1345,9 @@ int stiles_layout_init(int64_t n, int64_t bandwidth, int64_t arrow, int32_t tile
     return make_layout(n, bandwidth, arrow, tile, out);
 }
 
-size_t stiles_factor_workspace_bytes(const stiles_layout* lay) { return lay ? fws_bytes(*lay) : 0; }
+size_t stiles_factor_workspace_bytes(const stiles_layout* lay) { return lay ? WS_ALIGN + fws_bytes(*lay) : 0; }
 
-size_t stiles_selinv_workspace_bytes(const stiles_layout* lay) { return lay ? sws_bytes(*lay) : 0; }
+size_t stiles_selinv_workspace_bytes(const stiles_layout* lay) { return lay ? WS_ALIGN + sws_bytes(*lay) : 0; }
 
 int stiles_pack(const double* ab, const double* arrow_rows, const double* corner, double* tiles,
                 int64_t n, int64_t bandwidth, int64_t arrow, int32_t tile, void* stream) {
@@ -1369,7 +1377,7 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
     if (!workspace || workspace_bytes < stiles_factor_workspace_bytes(&lay)) return -9;
     hipStream_t st = S_(stream);
     Lay L = to_dev(lay);
-    const FactorWs f = factor_ws(L, (char*)workspace);
+    const FactorWs f = factor_ws(L, ws_base(workspace));
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
     const FacCtx x = fac_ctx(L, Lm, f.Yd, f.flags);
@@ -1387,14 +1395,14 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
         tm_end(tm, STILES_TK_OTHER, st);
     }
     LAUNCH(STILES_TK_OTHER, k_factor_setup, dim3(grid_for(fac_ints(L) + fac_ints(corner_lay(L)))), dim3(NT), 0, st, L, f);
-    LAUNCH(STILES_TK_FACTOR, k_factor_all, dim3((unsigned)std::min<int64_t>(nticket, fac_grid(x, 2 * di.cus))),
-           dim3(FAC_NT), 0, st, x, (int)ntask, sc, f.winfo);
+    LAUNCH(STILES_TK_FACTOR, fac_wide(Lm) ? k_factor_all<FAC_WIDE> : k_factor_all<FAC_NARROW>,
+           dim3((unsigned)std::min<int64_t>(nticket, fac_grid(x, 2 * di.cus))), dim3(FAC_NT), 0, st, x, (int)ntask, sc, f.winfo);
     LAUNCH(STILES_TK_OTHER, k_factor_tail, dim3((unsigned)factor_tail_blocks(L)), dim3(NT), 0, st, Lm, L, f.ldp, f.Tc);
     if (L.ap > 0) {
         const FacCtx xc = corner_ctx(L, f);
         sc.ticket = f.cticket;
         sc.withhold = -1;
-        LAUNCH(STILES_TK_POTRF, k_factor_all, dim3((unsigned)corner_grid(L)), dim3(FAC_NT), 0, st, xc, (int)fac_tasks(xc), sc,
+        LAUNCH(STILES_TK_POTRF, k_factor_all<FAC_WIDE>, dim3((unsigned)corner_grid(L)), dim3(FAC_NT), 0, st, xc, (int)fac_tasks(xc), sc,
                f.winfo);
         LAUNCH(STILES_TK_OTHER, k_corner_out, dim3((unsigned)corner_out_blocks(L)), dim3(NT), 0, st, Lm, L,
                (const double*)f.Tc, f.ldp, (const int*)f.winfo, (const int*)f.err, logdet, (int*)info);
@@ -1410,7 +1418,7 @@ int stiles_factor(const double* A, double* Lm, int64_t n, int64_t bandwidth, int
 static int selinv_impl(const double* Lm, double* S, const stiles_layout& lay, int64_t jf, int32_t* info,
                        void* workspace, hipStream_t st) {
     Lay L = to_dev(lay);
-    const SelinvWs v = selinv_ws(L, (char*)workspace);
+    const SelinvWs v = selinv_ws(L, ws_base(workspace));
     const int nb64 = L.b / 64, nab = arrow_blocks(L.ap);
     int64_t ntasks = 0;
     for (int64_t J = jf; J < L.nt; ++J) ntasks += p2_group_tasks(L, J, jf);
@@ -1540,7 +1548,7 @@ size_t stiles_inverse_workspace_bytes(const stiles_layout* lay) {
     if (!lay) return 0;
     const Lay F = full_lay(to_dev(*lay));
     const size_t np = (size_t)(lay->nt * lay->tile + lay->arrow_ld);
-    return align256(sws_bytes(*lay)) +
+    return WS_ALIGN + align256(sws_bytes(*lay)) +
            std::max(sizeof(double) * np * np, sizeof(double) * (size_t)F.total + sizeof(int) * (size_t)((F.bt + 2) * F.nt));
 }
 
@@ -1555,8 +1563,8 @@ int stiles_inverse(const double* Lm, double* Ainv, int64_t n, int64_t bandwidth,
     if (!workspace || workspace_bytes < stiles_inverse_workspace_bytes(&lay)) return -8;
     hipStream_t st = S_(stream);
     const Lay L = to_dev(lay), F = full_lay(L);
-    const SelinvWs v = selinv_ws(L, (char*)workspace);
-    double* D = (double*)((char*)workspace + align256(sws_bytes(lay)));
+    const SelinvWs v = selinv_ws(L, ws_base(workspace));
+    double* D = (double*)(ws_base(workspace) + align256(sws_bytes(lay)));
     int* cnt = (int*)(D + F.total);
     const int nb64 = L.b / 64, nab = arrow_blocks(L.ap);
     const int64_t ntasks = p2_total_tasks(F), n64 = (lay.n + 63) / 64;
@@ -1693,7 +1701,7 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     hipStream_t st = S_(stream);
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
-    char* ws = (char*)workspace;
+    char* ws = ws_base(workspace);
     std::vector<BInst> bi(count);
     for (int k = 0; k < count; ++k) {
         BInst& I = bi[k];
@@ -1767,8 +1775,10 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
     }
     LAUNCH(STILES_TK_OTHER, kb_factor_setup, dim3((unsigned)(8 * count)), dim3(NT), 0, st, dbi);
     auto args = [&](const Launch& l) { return BArgs{dbi, dseg + l.at, l.n, spin}; };
+    bool wide = true;   // every L
+    for (int k = 0; k < count; ++k) wide = wide && fac_wide(bi[k].Lm);
     for (size_t q = 0; q < fac.size(); ++q)
-        LAUNCH(STILES_TK_FACTOR, kb_factor, dim3((unsigned)fac[q].grid), dim3(FAC_NT), 0, st, args(fac[q]),
+        LAUNCH(STILES_TK_FACTOR, wide ? kb_factor<FAC_WIDE> : kb_factor<FAC_NARROW>, dim3((unsigned)fac[q].grid), dim3(FAC_NT), 0, st, args(fac[q]),
                (int)q * KB_SLICE, std::min<int>(count, ((int)q + 1) * KB_SLICE), dint);
     LAUNCH(STILES_TK_OTHER, kb_factor_tail, dim3((unsigned)tail.grid), dim3(NT), 0, st, args(tail));
     if (corner.grid > 0) {
@@ -1790,7 +1800,7 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     hipStream_t st = S_(stream);
     DevInfo di;
     if (dev_info(&di)) return STILES_EHIP;
-    char* ws = (char*)workspace;
+    char* ws = ws_base(workspace);
     char* tab = ws + pl.table_f;   // this call's table area
     std::vector<BInst> bi(count);
     int64_t sum_tasks = 0;
