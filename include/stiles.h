@@ -108,7 +108,9 @@ size_t stiles_selinv_workspace_bytes(const stiles_layout* lay);
 /*
  * Tile Cholesky A = L L^T on the band and arrow tiles, and log det A.
  *   A         device, tile layout, read only the lower triangles of diagonal
- *             tiles and of the corner.
+ *             tiles and of the corner.  Entries of band tiles outside the
+ *             element band have to be 0, as stiles_pack writes them (blocks
+ *             that lie there whole are not read).
  *   L         device, tile layout, output.  L may equal A (in place).  The
  *             upper triangles of the diagonal tiles and the corner are set to
  *             0; entries of band tiles outside the element band come out 0.
@@ -153,7 +155,9 @@ int stiles_selinv(const double* L, double* Sigma, int64_t n, int64_t bandwidth, 
  * The factor and Phase 2 are one launch each (the factor one per 128 matrices):
  * a workgroup whose matrix has no tasks left joins the one with the most work
  * left, so a batch takes about as long as its work divided over the device, or
- * as its longest matrix alone.
+ * as its longest matrix alone.  (The environment variables STILES_KB_COLS, tile
+ * columns per launch, and STILES_P2_SPLIT of earlier versions have nothing left
+ * to set and are not read; results never depended on the first.)
  *
  * items (host array of `count` entries, read during the call only):
  *   n, bandwidth, arrow, tile   as for stiles_layout_init; reserved must be 0
@@ -264,7 +268,8 @@ int stiles_gather(const double* Sigma, int64_t n, int64_t bandwidth, int64_t arr
  * (N b + a_p)^2 doubles, and the work grows as n^2 (w + a).
  *   L         device, tile layout, a factor produced by stiles_factor (read only)
  *   Ainv      device, n x n column-major (leading dimension n), full symmetric
- *   info      device, one int32: 0, or STILES_EBADL as for stiles_selinv
+ *   info      device, one int32: 0, STILES_EBADL or STILES_ETIMEOUT as for
+ *             stiles_selinv
  *   workspace device, at least stiles_inverse_workspace_bytes()
  */
 size_t stiles_inverse_workspace_bytes(const stiles_layout* lay);

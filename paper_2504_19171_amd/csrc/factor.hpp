@@ -26,11 +26,13 @@
 //     chain;
 //   C(r, s; q): chunks 4q .. 4q + 3 into corner block (r, s).
 // Tasks are dealt by tickets in the order of fac_group; a task waits only for
-// tasks of smaller tickets and for the chain, the chain only for tasks.  The
-// chain takes the launch's first ticket, so it runs whenever any workgroup of
-// the launch does, and launches have at least two workgroups when they have
-// tasks: as long as some other launch's workgroups leave room in the end, no
-// wait can last.
+// tasks of smaller tickets and for the chain, the chain only for tasks, which
+// have larger tickets than it: it gets no further unless a second workgroup of
+// the launch runs.  A launch has at least two per matrix when it has tasks, next
+// to each other, so of all launches that run at once those that cannot go on
+// hold one workgroup of the chip each; with fewer launches than workgroups fit
+// it (256 and more) the others end and make room.  Such a wait counts towards
+// the spin limit.
 // Without blocks below the diagonal ones (w = 0, or a single chunk) the chunks
 // do not depend on each other: each is a chain of its own, and these take the
 // first tickets (nb 200,000, w 0, tile 64: 16.9 ms with one chain for all, 0.15

@@ -2,10 +2,12 @@
 //
 // A persistent kernel is launched with a fixed number of workgroups; each one
 // repeatedly takes the next ticket from a global counter and runs the task
-// with that number.  Tickets follow a topological order of the task graph
-// (every task depends only on tasks with smaller tickets), so a task that
-// waits is always waiting for work that a running workgroup already owns:
-// the scheme cannot deadlock, whether or not all workgroups are resident.
+// with that number.  In Phase 2 tickets follow a topological order of the task
+// graph (every task depends only on tasks with smaller tickets), so a task that
+// waits is always waiting for work that a running workgroup already owns: it
+// cannot deadlock, whether or not all workgroups are resident.  The factor's
+// tasks do the same, but its first ticket, the chain, waits for later ones and
+// needs a second workgroup beside it (see factor.hpp).
 //
 // Dependencies are counters in device memory: a producer adds 1 once its
 // output is written; a consumer spins until the counter reaches the number of

@@ -450,10 +450,11 @@ __global__ __launch_bounds__(64) void k_factor_final(const double* ldp, int npar
 
 // Phase 1, diagonal tiles: X_J = L_JJ^{-1} ("TRSM(L_ii^T, I)"), stored in the
 // diagonal slots of the workspace; the corner inverse likewise, one workgroup
-// per 64 columns.  A tile takes one workgroup per 64 columns too when that
-// leaves no more workgroups than fit the chip at once, or when it has 64 (79
-// tiles of 256: 131 against 188 us; 27,000 of 64: 0.87 against 1.13 ms), else
-// one, which inverts each diagonal block once (391 of 256: 303 against 442 us).
+// per 64 columns.  A tile takes one workgroup per 64 columns too when the whole
+// matrix (a range of its columns counts as the whole) has at most 512 of them,
+// two per CU, or when a tile has 64 (79 tiles of 256: 131 against 188 us; 27,000
+// of 64: 0.87 against 1.13 ms), else one, which inverts each diagonal block once
+// (391 of 256: 303 against 442 us).
 __host__ __device__ inline int trtri_per(const Lay& L) { return L.b == 64 || L.nt * (L.b / 64) <= 512 ? L.b / 64 : 1; }
 __host__ __device__ inline int trtri_blocks(const Lay& L) { return (int)L.nt * trtri_per(L) + arrow_blocks(L.ap); }
 __device__ inline void trtri_body(const double* Lm, double* W, const Lay& L, int* info, int bid, double* smem) {
@@ -708,7 +709,7 @@ struct BInst {
     int fac_ntask;    // factor task count
     int fac_nticket;  // ... and with the chains
     int p2_tasks;     // Phase 2 task count
-    int nparts;       // log det partial pairs (tile columns + corner blocks)
+    int nparts;       // log det partial pairs (factor_nparts)
 };
 // Workgroups [first, next first) of a launch belong to matrix inst; a table
 // of nseg segments ends with a sentinel holding the launch's grid size.
@@ -1180,7 +1181,7 @@ static int fac_grid(const FacCtx& x, int most) {
 }
 
 
-// log det partial pairs: one per band tile column, one or two for the corner
+// log det partial pairs: one per band tile column, one for the corner
 static int factor_nparts(const Lay& L) { return (int)L.nt + (L.ap > 0 ? 1 : 0); }
 
 // Workgroups of a corner's factor: the chain and up to 31 for its tasks (at
@@ -1243,10 +1244,9 @@ static int batch_plan(const stiles_batch_item* items, int count, bool need_sigma
         if (need_sigma && p2_total_tasks(to_dev(pl.lay[k])) > 0x7fffffff) return -1;
     }
     // segment tables of at most six per-matrix launches and a sentinel per
-    // launch of the factor; ints: the error word
+    // launch of the factor, then the factor's error word
     const size_t nseg = batch_nseg(count);
-    const size_t nint = 1;
-    pl.table_f = align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg) + align256(sizeof(int) * nint);
+    pl.table_f = align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg) + align256(sizeof(int));
     pl.table = pl.table_f + align256(sizeof(BInst) * (size_t)count) + align256(sizeof(BSeg) * nseg);
     size_t o = pl.table;
     for (int k = 0; k < count; ++k) {
@@ -1259,7 +1259,6 @@ static int batch_plan(const stiles_batch_item* items, int count, bool need_sigma
 
 // Segment table builder: workgroup shares of one launch.
 struct SegTab {
-    std::vector<BSeg> v;
     size_t begin = 0;
     int grid = 0;
     void start(size_t b) { begin = b; grid = 0; }
@@ -1540,7 +1539,6 @@ int stiles_mfma_peak(double* sink, int64_t sink_doubles, int32_t iters, double* 
 
 size_t stiles_trace_workspace_bytes(void) { return sizeof(double) * TP_BLOCKS; }
 
-// padded order of the dense inverse: N b band rows and a_p arrow rows
 // inverse workspace: the selected inverse's, Sigma in the dense layout, its
 // Phase 2 counters; never less than a dense matrix beside the first, which
 // callers may count on
@@ -1675,18 +1673,16 @@ static int pinned_upload(void* dst, const void* src, size_t n, hipStream_t st) {
     return 0;
 }
 
-static int batch_upload(const std::vector<BInst>& bi, const std::vector<BSeg>& segs, const std::vector<int>& idx,
-                        char* ws, hipStream_t st) {
-    const size_t o1 = align256(sizeof(BInst) * bi.size()), o2 = o1 + align256(sizeof(BSeg) * batch_nseg((int)bi.size()));
-    std::vector<char> h(o2 + sizeof(int) * idx.size());
+static int batch_upload(const std::vector<BInst>& bi, const std::vector<BSeg>& segs, char* ws, hipStream_t st) {
+    const size_t o1 = align256(sizeof(BInst) * bi.size());
+    std::vector<char> h(o1 + sizeof(BSeg) * segs.size());
     memcpy(h.data(), bi.data(), sizeof(BInst) * bi.size());
     memcpy(h.data() + o1, segs.data(), sizeof(BSeg) * segs.size());
-    if (!idx.empty()) memcpy(h.data() + o2, idx.data(), sizeof(int) * idx.size());
     return pinned_upload(ws, h.data(), h.size(), st);
 }
 
-// What a batched call does: upload its tables (host -> workspace, a copy
-// from pageable memory staged before the call returns), enqueue its kernels
+// What a batched call does: upload its tables (host -> workspace), enqueue its
+// kernels
 // (device work only, reading the tables; what a HIP graph can capture), or both.
 #define BATCH_UPLOAD 1
 #define BATCH_LAUNCH 2
@@ -1754,10 +1750,8 @@ static int factor_batched_impl(const stiles_batch_item* items, int32_t count, vo
         close(l);
         fac.push_back(l);
     }
-    const std::vector<int> ints(1, 0);   // the error word
-    int rc = 0;
     if (mode & BATCH_UPLOAD) {
-        rc = batch_upload(bi, segs, ints, ws, st);
+        const int rc = batch_upload(bi, segs, ws, st);
         if (rc) return rc;
     }
     if (!(mode & BATCH_LAUNCH)) return 0;
@@ -1861,7 +1855,7 @@ static int selinv_batched_impl(const stiles_batch_item* items, int32_t count, vo
     }
     close(p2);
     if (mode & BATCH_UPLOAD) {
-        const int rc = batch_upload(bi, segs, std::vector<int>(), tab, st);
+        const int rc = batch_upload(bi, segs, tab, st);
         if (rc) return rc;
     }
     if (!(mode & BATCH_LAUNCH)) return 0;
