@@ -64,3 +64,34 @@ def test_several_factor_launches_of_wide_bands():
     assert sum(-(-w // 64) >= 4 for _, w, _, _ in shapes) > 64
     print(f"batch of {len(shapes)}", flush=True)
     _compare(shapes, 1000)
+
+
+def test_expired_waits_end_the_batch(monkeypatch):
+    """With a spin limit of a microsecond some wait expires at once, while other
+    workgroups run tasks, look for another matrix or hold a chain: every launch
+    ends, every matrix reports it, and the next batch on the same buffers is
+    sound."""
+    import torch
+    from gpu_util import to_device
+    from paper_2504_19171_amd import stiles as st
+    shapes = [(400 + 211 * k, 30 * k, 5 * k, 64) for k in range(1, 14)]
+    lays, As = [], []
+    for k, (nb, w, a, b) in enumerate(shapes):
+        M = inputs.arrowhead_spd(nb, w, a, seed=2000 + k)
+        lays.append(st.layout(M.n, M.w, M.a, b))
+        As.append(st.pack(*to_device(M, "cuda:0"), lays[-1]))
+    ws = torch.empty(st.batch_workspace_bytes(lays), dtype=torch.uint8, device="cuda:0")
+    Ls = [torch.empty_like(A) for A in As]
+    monkeypatch.setenv("STILES_SPIN_LIMIT_MS", "0.001")
+    print("batch with a spin limit of 1 us", flush=True)
+    _, ld, info = st.factor_batched(As, lays, outs=Ls, workspace=ws)
+    torch.cuda.synchronize()
+    assert info[:, 0].tolist() == [st.STILES_ETIMEOUT] * len(shapes)
+    assert torch.isnan(ld).all()
+    monkeypatch.delenv("STILES_SPIN_LIMIT_MS")
+    _, ld, info = st.factor_batched(As, lays, outs=Ls, workspace=ws)
+    torch.cuda.synchronize()
+    assert int(info[:, 0].abs().max().item()) == 0
+    for k, (A, lay) in enumerate(zip(As, lays)):
+        L, one, _ = st.factor(A, lay)
+        assert torch.equal(L.ravel(), Ls[k].ravel()) and float(one.item()) == float(ld[k].item()), shapes[k]
